@@ -61,7 +61,11 @@ typedef struct {
                           32); 0 -> the larger of 8 and the smaller of
                           bucket_words and 64                                  */
   uint32_t keys_per_subgroup; /* keys a subgroup keeps in flight: 1, 2, 4 or 8,
-                                 at most subgroup; 0 -> 1                        */
+                                 at most subgroup; 0 -> 1.  (4-lane subgroups
+                                 of find-or-put always have four in flight, and
+                                 its launches of few keys, at most 2048 per
+                                 compute unit, use 4-lane subgroups with
+                                 buckets of at most 32 words)                   */
   uint32_t reserved;
 } gx_table_opts;
 

@@ -327,6 +327,42 @@ __device__ inline void flush_stats(const TableDev& t, const LaneStats& st, uint6
   if (mj) atomicMax(reinterpret_cast<unsigned long long*>(&c[kCntMaxJ]), mj);
 }
 
+// The same for a whole workgroup of a kernel whose wavefronts all come here:
+// one set of atomics per workgroup.  All atomics on one address are carried
+// out one after the other, about 9 ns each, so one per wavefront of a full
+// grid costs a launch 70 us.
+__device__ inline void flush_stats_block(const TableDev& t, const LaneStats& st, uint64_t* n_new) {
+  __shared__ uint32_t part[16][6];
+  const uint32_t probes = wave_sum(st.probes);
+  const uint32_t mj = wave_max(st.max_j);
+  const uint32_t wave = threadIdx.x >> 6;
+  if (__lane_id() == 0) {
+    part[wave][0] = st.stored;
+    part[wave][1] = st.lookups;
+    part[wave][2] = probes;
+    part[wave][3] = st.full;
+    part[wave][4] = st.invalid;
+    part[wave][5] = mj;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 6) return;
+  uint64_t x = 0;
+  for (uint32_t w = 0; w < blockDim.x / 64; ++w) {
+    const uint64_t y = part[w][threadIdx.x];
+    x = threadIdx.x == 5 ? (y > x ? y : x) : x + y;
+  }
+  if (x == 0) return;
+  if (threadIdx.x == 0 && n_new) atomicAdd(reinterpret_cast<unsigned long long*>(n_new), x);
+  if (t.counters == nullptr) return;  // a table that keeps no statistics
+  static_assert(kCntStored == 0 && kCntLookups == 1 && kCntProbes == 2 && kCntFull == 3 &&
+                    kCntInvalid == 4 && kCntMaxJ == 5,
+                "counter order");
+  auto* c = reinterpret_cast<unsigned long long*>(
+      t.counters + static_cast<uint64_t>(blockIdx.x % t.ctr_slots) * kNumCounters + threadIdx.x);
+  if (threadIdx.x == 5) atomicMax(c, x);
+  else atomicAdd(c, x);
+}
+
 // Find-or-put of U keys per subgroup.  Every lane of a subgroup holds the same
 // U keys (slot format, no word kEmpty), their 64-bit mixes and first buckets.
 // act[u] false: no key.  On return res[u] is kNew / kSeen / kFull for active
@@ -500,6 +536,215 @@ __device__ inline void find_or_put(const TableDev& t, const uint32_t (&key)[U][S
   }
 }
 
+// ----------------------------------------------- 4-lane subgroups ("quads")
+// Value of lane R of the caller's group of four lanes.  Every lane of the
+// wavefront must be active.
+template <int R>
+__device__ __forceinline__ uint32_t quad_bcast(uint32_t x) {
+  return static_cast<uint32_t>(
+      __builtin_amdgcn_mov_dpp(static_cast<int>(x), R * 0x55, 0xf, 0xf, true));
+}
+
+// What one lane sees of a key's bucket piece (four words of it) in a byte:
+// bit 0 a slot equals the key, bit 1 a slot is PARTIAL, bits 2.. the EMPTY
+// slots (4/S of them).  A key word is never kEmpty, so an EMPTY or PARTIAL
+// slot never equals the key.
+template <int S>
+__device__ __forceinline__ uint32_t quad_code(const uint4& v, const uint32_t (&k)[S]) {
+  if constexpr (S == 1) {
+    const uint32_t m = static_cast<uint32_t>(v.x == k[0]) | static_cast<uint32_t>(v.y == k[0]) |
+                       static_cast<uint32_t>(v.z == k[0]) | static_cast<uint32_t>(v.w == k[0]);
+    return m | static_cast<uint32_t>(v.x == kEmpty) << 2 |
+           static_cast<uint32_t>(v.y == kEmpty) << 3 | static_cast<uint32_t>(v.z == kEmpty) << 4 |
+           static_cast<uint32_t>(v.w == kEmpty) << 5;
+  } else if constexpr (S == 2) {
+    const bool e0 = (v.x & v.y) == kEmpty, e1 = (v.z & v.w) == kEmpty;
+    const bool p0 = max(v.x, v.y) == kEmpty, p1 = max(v.z, v.w) == kEmpty;
+    const bool m = (v.x == k[0] && v.y == k[1]) || (v.z == k[0] && v.w == k[1]);
+    return static_cast<uint32_t>(m) | static_cast<uint32_t>((p0 && !e0) || (p1 && !e1)) << 1 |
+           static_cast<uint32_t>(e0) << 2 | static_cast<uint32_t>(e1) << 3;
+  } else {
+    const bool e = (v.x & v.y & v.z & v.w) == kEmpty;
+    const bool p = max(max(v.x, v.y), max(v.z, v.w)) == kEmpty;
+    const bool m = v.x == k[0] && v.y == k[1] && v.z == k[2] && v.w == k[3];
+    return static_cast<uint32_t>(m) | static_cast<uint32_t>(p && !e) << 1 |
+           static_cast<uint32_t>(e) << 2;
+  }
+}
+
+// The find-or-put of 4-lane subgroups: every lane owns a key, and the four
+// keys of a subgroup are in flight together.  For each of them the subgroup
+// reads 64 bytes of the key's bucket (16 bytes a lane, one coalesced line),
+// every lane puts what it sees into a byte of its code word, and the owner
+// takes its byte from the four lanes: data moves between the lanes by
+// quad-permutes only.  Buckets wider than 16 words are read 64 bytes at a
+// time: slots fill from the lowest, so an EMPTY slot in one piece means that
+// no later piece holds anything.  All 64 claims of a wavefront are one
+// instruction.  A claim lost to another key goes on to the piece's next EMPTY
+// slot without another read, so that the keys that meet in a bucket cost a
+// claim each and not a read and a claim, and so that progress does not depend
+// on how fresh plain loads are.
+// Bound: random 64-byte reads (about 54 G/s from HBM, 57-67 G/s from the
+// last-level cache) and 27 G/s of random 64-bit claims; with one key in
+// flight per subgroup, four dependent rounds per wavefront, launches of up
+// to a few million keys were bound by the rounds' latency instead.
+template <int S, int B>
+__device__ inline uint8_t find_or_put_quads(const TableDev& t, const uint32_t (&key)[S], bool act,
+                                            LaneStats& st) {
+  constexpr int PW = B < 16 ? B : 16;  // words of a piece
+  constexpr int LQ = PW / 4;           // lanes holding them
+  constexpr uint32_t NP = B / PW;      // pieces per bucket
+  constexpr uint32_t SPL = 4 / S;      // slots per lane
+  const uint32_t li = static_cast<uint32_t>(__lane_id()) & 3u;
+  const char* mine = reinterpret_cast<const char*>(t.words) + li * 16;
+  uint8_t res = kSeen;
+  bool bad = false;
+#pragma unroll
+  for (int w = 0; w < S; ++w) bad |= key[w] == kEmpty;
+  if (act && bad) {
+    res = kInvalid;
+    act = false;
+  }
+  const uint64_t n_act = __ballot(act);
+  const uint64_t mix = key_mix<S>(key, t.seed);
+  uint64_t off = bucket_of(mix, t.a0, t.c0, t.n_buckets) * (B * 4);  // bytes, of the piece
+  uint32_t j = 0, piece = 0;
+  bool fresh = false;
+  if (act) ++st.probes;
+  while (__any(act)) {
+    uint4 v[4];
+    const uint32_t lo = static_cast<uint32_t>(off), hi = static_cast<uint32_t>(off >> 32);
+    // 0: no read, 1: plain read, 2: read past the caches
+    const uint32_t how = act ? (fresh ? 2u : 1u) : 0u;
+    auto read = [&](uint32_t l, uint32_t h, uint32_t m, uint4& x) {
+      x = make_uint4(0, 0, 0, 0);
+      if (static_cast<int>(li) >= LQ) return;
+      const char* p = mine + (static_cast<uint64_t>(h) << 32 | l);
+      if (m == 1) x = *reinterpret_cast<const uint4*>(p);
+    };
+    auto read_fresh = [&](uint32_t l, uint32_t h, uint32_t m, uint4& x) {
+      if (m != 2 || static_cast<int>(li) >= LQ) return;
+      uint32_t f[4];
+      load_view_fresh<4>(const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(
+                             mine + (static_cast<uint64_t>(h) << 32 | l))), f);
+      x = make_uint4(f[0], f[1], f[2], f[3]);
+    };
+    read(quad_bcast<0>(lo), quad_bcast<0>(hi), quad_bcast<0>(how), v[0]);
+    read(quad_bcast<1>(lo), quad_bcast<1>(hi), quad_bcast<1>(how), v[1]);
+    read(quad_bcast<2>(lo), quad_bcast<2>(hi), quad_bcast<2>(how), v[2]);
+    read(quad_bcast<3>(lo), quad_bcast<3>(hi), quad_bcast<3>(how), v[3]);
+    if (__any(how == 2)) {
+      read_fresh(quad_bcast<0>(lo), quad_bcast<0>(hi), quad_bcast<0>(how), v[0]);
+      read_fresh(quad_bcast<1>(lo), quad_bcast<1>(hi), quad_bcast<1>(how), v[1]);
+      read_fresh(quad_bcast<2>(lo), quad_bcast<2>(hi), quad_bcast<2>(how), v[2]);
+      read_fresh(quad_bcast<3>(lo), quad_bcast<3>(hi), quad_bcast<3>(how), v[3]);
+    }
+    uint32_t code = 0;
+    {
+      uint32_t k[S];
+#pragma unroll
+      for (int w = 0; w < S; ++w) k[w] = quad_bcast<0>(key[w]);
+      code |= quad_code<S>(v[0], k);
+#pragma unroll
+      for (int w = 0; w < S; ++w) k[w] = quad_bcast<1>(key[w]);
+      code |= quad_code<S>(v[1], k) << 8;
+#pragma unroll
+      for (int w = 0; w < S; ++w) k[w] = quad_bcast<2>(key[w]);
+      code |= quad_code<S>(v[2], k) << 16;
+#pragma unroll
+      for (int w = 0; w < S; ++w) k[w] = quad_bcast<3>(key[w]);
+      code |= quad_code<S>(v[3], k) << 24;
+    }
+    // the four lanes' views of this lane's key
+    constexpr uint32_t kSlotMask = (1u << SPL) - 1u;
+    uint32_t any, empty;
+    {
+      const uint32_t b0 = quad_bcast<0>(code) >> (8 * li);
+      any = b0;
+      empty = (b0 >> 2) & kSlotMask;
+      if constexpr (LQ >= 2) {
+        const uint32_t b1 = quad_bcast<1>(code) >> (8 * li);
+        any |= b1;
+        empty |= ((b1 >> 2) & kSlotMask) << SPL;
+      }
+      if constexpr (LQ == 4) {
+        const uint32_t b2 = quad_bcast<2>(code) >> (8 * li);
+        const uint32_t b3 = quad_bcast<3>(code) >> (8 * li);
+        any |= b2 | b3;
+        empty |= ((b2 >> 2) & kSlotMask) << (2 * SPL) | ((b3 >> 2) & kSlotMask) << (3 * SPL);
+      }
+    }
+    fresh = false;
+    if (act) {
+      if (any & 1u) {
+        act = false;  // SEEN
+      } else if (any & 2u) {
+        fresh = true;  // PARTIAL: look again
+        ++st.probes;
+      } else {
+        // the lowest EMPTY slot; lost to another key, the next one: every
+        // slot passed over holds a key this one was compared with
+        while (empty && act && !fresh) {
+          uint32_t* slot = t.words + off / 4 + static_cast<uint32_t>(__ffs(empty) - 1) * S;
+          empty &= empty - 1;
+          if constexpr (S == 1) {
+            uint32_t old = kEmpty;
+            __hip_atomic_compare_exchange_strong(slot, &old, key[0], __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (old == kEmpty) res = kNew;
+            act = old != kEmpty && old != key[0];
+          } else {
+            const uint64_t head =
+                static_cast<uint64_t>(key[0]) | static_cast<uint64_t>(key[1]) << 32;
+            uint64_t old = ~0ull;
+            __hip_atomic_compare_exchange_strong(reinterpret_cast<uint64_t*>(slot), &old, head,
+                                                 __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+            if constexpr (S == 2) {
+              if (old == ~0ull) res = kNew;
+              act = old != ~0ull && old != head;
+            } else if (old == ~0ull) {
+              // publish the tail in the same step as the claim is known
+              const uint64_t tail =
+                  static_cast<uint64_t>(key[2]) | static_cast<uint64_t>(key[3]) << 32;
+              __hip_atomic_store(reinterpret_cast<uint64_t*>(slot + 2), tail, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+              res = kNew;
+              act = false;
+            } else if (old == head) {
+              fresh = true;  // the tail decides, and may not be stored yet: look again
+              ++st.probes;
+            }
+          }
+        }
+        if (act && !fresh) {
+          // no slot left here: the bucket's next piece, or the next set of
+          // hash constants
+          ++piece;
+          off += PW * 4;
+          if (piece == NP) {
+            piece = 0;
+            ++j;
+            if (j >= t.H) {
+              res = kFull;
+              act = false;
+            } else {
+              off = bucket_of(mix, t.hc[2 * j], t.hc[2 * j + 1], t.n_buckets) * (B * 4);
+              ++st.probes;
+            }
+          }
+        }
+      }
+      if (!act && res != kFull && j > st.max_j) st.max_j = j;
+    }
+  }
+  st.lookups += static_cast<uint32_t>(__popcll(n_act));
+  st.invalid += static_cast<uint32_t>(__popcll(__ballot(res == kInvalid)));
+  st.stored += static_cast<uint32_t>(__popcll(__ballot(res == kNew)));
+  st.full += static_cast<uint32_t>(__popcll(__ballot(res == kFull)));
+  return res;
+}
+
 // Find-or-put of one key per lane: lane l of the wavefront owns key `own`
 // (slot format) when own_act.  Each lane hashes its own key (64 hashes per
 // wavefront, no redundant work); subgroup g then probes the keys owned by its
@@ -507,50 +752,54 @@ __device__ inline void find_or_put(const TableDev& t, const uint32_t (&key)[U][S
 // lane shuffles; the result comes back to the owner lane.  Returns the owner's
 // status (kNew / kSeen / kFull / kInvalid).  Must be reached by the whole
 // wavefront.
-template <int S, int B, int G, int U>
+template <int S, int B, int G, int U, bool kQuads = G == 4>
 __device__ inline uint8_t find_or_put_lanes(const TableDev& t, const uint32_t (&own)[S],
                                             bool own_act, LaneStats& st) {
   static_assert(U >= 1 && U <= G && (G % U) == 0, "keys in flight per subgroup");
-  const int lane = __lane_id();
-  const int li = lane % G;
-  const int first = lane - li;  // first lane of this subgroup
-  uint8_t own_res = kSeen;
-  bool bad = false;
+  if constexpr (kQuads) {
+    return find_or_put_quads<S, B>(t, own, own_act, st);
+  } else {
+    const int lane = __lane_id();
+    const int li = lane % G;
+    const int first = lane - li;  // first lane of this subgroup
+    uint8_t own_res = kSeen;
+    bool bad = false;
 #pragma unroll
-  for (int w = 0; w < S; ++w) bad |= own[w] == kEmpty;
-  if (own_act && bad) {
-    own_res = kInvalid;
-    own_act = false;
-  }
-  const uint64_t own_mix = key_mix<S>(own, t.seed);
-  const uint64_t own_bkt = bucket_of(own_mix, t.a0, t.c0, t.n_buckets);
-#pragma unroll 1
-  for (int c = 0; c < G; c += U) {
-    uint32_t key[U][S];
-    uint64_t mix[U], bkt[U];
-    bool act[U];
-    uint8_t res[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int src = first + c + u;
-#pragma unroll
-      for (int w = 0; w < S; ++w) key[u][w] = __shfl(own[w], src, 64);
-      mix[u] = (static_cast<uint64_t>(__shfl(static_cast<uint32_t>(own_mix >> 32), src, 64)) << 32) |
-               __shfl(static_cast<uint32_t>(own_mix), src, 64);
-      bkt[u] = (static_cast<uint64_t>(__shfl(static_cast<uint32_t>(own_bkt >> 32), src, 64)) << 32) |
-               __shfl(static_cast<uint32_t>(own_bkt), src, 64);
-      act[u] = __shfl(static_cast<int>(own_act), src, 64) != 0;
+    for (int w = 0; w < S; ++w) bad |= own[w] == kEmpty;
+    if (own_act && bad) {
+      own_res = kInvalid;
+      own_act = false;
     }
-    find_or_put<S, B, G, U>(t, key, mix, bkt, act, res, st);
+    const uint64_t own_mix = key_mix<S>(own, t.seed);
+    const uint64_t own_bkt = bucket_of(own_mix, t.a0, t.c0, t.n_buckets);
+#pragma unroll 1
+    for (int c = 0; c < G; c += U) {
+      uint32_t key[U][S];
+      uint64_t mix[U], bkt[U];
+      bool act[U];
+      uint8_t res[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (li == c + u && own_act) own_res = res[u];
+      for (int u = 0; u < U; ++u) {
+        const int src = first + c + u;
+#pragma unroll
+        for (int w = 0; w < S; ++w) key[u][w] = __shfl(own[w], src, 64);
+        mix[u] = (static_cast<uint64_t>(__shfl(static_cast<uint32_t>(own_mix >> 32), src, 64)) << 32) |
+                 __shfl(static_cast<uint32_t>(own_mix), src, 64);
+        bkt[u] = (static_cast<uint64_t>(__shfl(static_cast<uint32_t>(own_bkt >> 32), src, 64)) << 32) |
+                 __shfl(static_cast<uint32_t>(own_bkt), src, 64);
+        act[u] = __shfl(static_cast<int>(own_act), src, 64) != 0;
+      }
+      find_or_put<S, B, G, U>(t, key, mix, bkt, act, res, st);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (li == c + u && own_act) own_res = res[u];
+    }
+    st.lookups += static_cast<uint32_t>(__popcll(__ballot(own_act)));
+    st.invalid += static_cast<uint32_t>(__popcll(__ballot(own_res == kInvalid)));
+    st.stored += static_cast<uint32_t>(__popcll(__ballot(own_res == kNew)));
+    st.full += static_cast<uint32_t>(__popcll(__ballot(own_res == kFull)));
+    return own_res;
   }
-  st.lookups += static_cast<uint32_t>(__popcll(__ballot(own_act)));
-  st.invalid += static_cast<uint32_t>(__popcll(__ballot(own_res == kInvalid)));
-  st.stored += static_cast<uint32_t>(__popcll(__ballot(own_res == kNew)));
-  st.full += static_cast<uint32_t>(__popcll(__ballot(own_res == kFull)));
-  return own_res;
 }
 
 }  // namespace gx

@@ -679,7 +679,7 @@ __global__ __launch_bounds__(256) void append_kernel(AppendArgs a) {
       else
         load_slot<S>(a.keys + idx * S, key);
     }
-    const uint8_t r = find_or_put_lanes<S, B, G, U>(a.t, key, act, st);
+    const uint8_t r = find_or_put_lanes<S, B, G, U, false>(a.t, key, act, st);
     const bool is_new = act && r == kNew;
     full |= act && r == kFull;
     const uint64_t m = __ballot(is_new);

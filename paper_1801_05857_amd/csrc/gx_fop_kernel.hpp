@@ -9,6 +9,9 @@
 
 namespace gx {
 
+constexpr uint32_t kLanesPerCu = 2048;  // 8 wavefronts on each of 4 SIMDs
+constexpr uint32_t kWideBlock = 1024;   // threads per workgroup of a large launch
+
 template <int S>
 __device__ inline void load_key(const uint32_t* keys, uint32_t w, uint64_t idx,
                                 uint32_t (&k)[S]) {
@@ -38,8 +41,10 @@ __device__ inline void load_key(const uint32_t* keys, uint32_t w, uint64_t idx,
 // One key per lane: a wavefront handles 64 consecutive keys per round (one
 // coalesced read of the keys, one coalesced write of the statuses), its
 // subgroups probing them U at a time.  Grid-stride over rounds.
+// Workgroups are wide in large launches: their number, not the keys', sets
+// how many atomics meet on n_new.
 template <int S, int B, int G, int U>
-__global__ __launch_bounds__(256) void fop_kernel(TableDev t, const uint32_t* keys, uint32_t w,
+__global__ __launch_bounds__(1024) void fop_kernel(TableDev t, const uint32_t* keys, uint32_t w,
                                                   uint64_t n, uint8_t* status, uint64_t* n_new) {
   const int lane = __lane_id();
   const uint64_t wave = (static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
@@ -55,46 +60,68 @@ __global__ __launch_bounds__(256) void fop_kernel(TableDev t, const uint32_t* ke
     const uint8_t r = find_or_put_lanes<S, B, G, U>(t, key, act, st);
     if (act) status[idx] = r;
   }
-  flush_stats(t, st, n_new);
+  flush_stats_block(t, st, n_new);
 }
 
 
 template <int S, int B, int G, int U>
 hipError_t launch_fop(const FopArgs& a) {
-  // as many workgroups as can be resident at once (grid-stride over rounds)
+  // as many workgroups as can be resident at once (grid-stride over rounds);
+  // narrow ones while they are few, so that a small launch spreads out
   static int per_cu = 0;
   if (per_cu == 0) {
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, fop_kernel<S, B, G, U>, 256, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, fop_kernel<S, B, G, U>, kWideBlock, 0) !=
             hipSuccess ||
         b <= 0)
-      b = 2;
+      b = 1;
     per_cu = b;
   }
-  const uint64_t want = (a.n + 255) / 256;  // one key per thread per round
-  uint32_t grid = static_cast<uint32_t>(
-      std::min<uint64_t>(want, static_cast<uint64_t>(a.cus) * static_cast<uint32_t>(per_cu)));
+  const uint32_t block = a.n <= static_cast<uint64_t>(a.cus) * 512 ? 256 : kWideBlock;
+  // one key per thread per round.  4-lane subgroups, with every key of a
+  // round in flight, take at most eight keys a bucket at once: the keys that
+  // meet in one bucket of an empty table claim its slots one after the other,
+  // and each claims every slot that another took before it (2^19 one-word
+  // keys into 2^15 buckets of 32 words: 140 us all at once, 66 us at four a
+  // bucket; all found: 8 and 13 us).
+  const uint64_t flight = G == 4 ? std::min<uint64_t>(a.n, 8 * a.t.n_buckets) : a.n;
+  const uint64_t want = (flight + block - 1) / block;
+  uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>(
+      want, static_cast<uint64_t>(a.cus) * static_cast<uint32_t>(per_cu) * (kWideBlock / block)));
   if (grid == 0) grid = 1;
-  hipLaunchKernelGGL((fop_kernel<S, B, G, U>), dim3(grid), dim3(256), 0, a.stream, a.t, a.keys,
+  hipLaunchKernelGGL((fop_kernel<S, B, G, U>), dim3(grid), dim3(block), 0, a.stream, a.t, a.keys,
                      a.w, a.n, a.status, a.n_new);
   return hipGetLastError();
 }
 
 template <int S, int B, int G>
 hipError_t dispatch_u(uint32_t U, const FopArgs& a) {
-  switch (U) {
-    case 1: return launch_fop<S, B, G, 1>(a);
-    case 2: return launch_fop<S, B, G, 2>(a);
-    case 4: return launch_fop<S, B, G, 4>(a);
-    case 8:
-      if constexpr (G >= 8) return launch_fop<S, B, G, 8>(a);
-      break;
+  // (a 4-lane subgroup has its four keys in flight whatever U says)
+  if constexpr (G == 4) {
+    return launch_fop<S, B, 4, 1>(a);
+  } else {
+    switch (U) {
+      case 1: return launch_fop<S, B, G, 1>(a);
+      case 2: return launch_fop<S, B, G, 2>(a);
+      case 4: return launch_fop<S, B, G, 4>(a);
+      case 8: return launch_fop<S, B, G, 8>(a);
+    }
+    return hipErrorInvalidValue;
   }
-  return hipErrorInvalidValue;
 }
 
 template <int S, int B>
 hipError_t dispatch_g(uint32_t G, uint32_t U, const FopArgs& a) {
+  // A launch that fits the device with one key per lane takes 4-lane
+  // subgroups whatever the table's width: all its probes are then in flight
+  // at once, where subgroups of 8 lanes take 8 dependent rounds a wavefront.
+  // Two-word keys, 32-word buckets, load 0.25, tables of subgroup 8: 4096
+  // new keys 21.8 -> 10.0 us (found: 4.4 -> 2.5), 2^19 keys 120 -> 54 (11.1
+  // -> 10.2); at 2^20 keys the 8-lane subgroups are the faster, 58 against 71
+  // (21.0 and 20.6).  Buckets of 64 words keep their subgroups: read 64 bytes
+  // at a time, four dependent reads take longer than one wide one (found, at
+  // load 0.5: 5.2 -> 9.8 us for 4096 keys).
+  if (B <= 32 && a.n <= static_cast<uint64_t>(a.cus) * kLanesPerCu) G = 4;
   switch (G) {
     case 4:
       if constexpr (B <= 32) return dispatch_u<S, B, 4>(U, a);
