@@ -275,7 +275,7 @@ typedef struct {
   void* hip_stream;           /* stream for every launch of the call           */
   uint32_t local_dedup;       /* nonzero: before probing the table, each
                                  wavefront drops duplicates within its staged
-                                 chunk of successors (the per-block state cache
+                                 successors (the per-block state cache
                                  of the paper's tool, Sec. 3); results are
                                  unchanged, table probes fewer                 */
   uint32_t monitor_proc;      /* with monitor_bad: the process that is the
@@ -283,10 +283,9 @@ typedef struct {
   uint32_t stop_on_violation; /* nonzero: end the exploration after the first
                                  level that holds a violation (that level is
                                  counted, not expanded)                        */
-  uint32_t slice_states;      /* most frontier states one slice of a level
-                                 takes (one generation launch, then one probe
-                                 launch, whose successor buffer holds the
-                                 slice's successors); 0 -> 2^22               */
+  uint32_t slice_states;      /* most frontier states one launch takes; 0 ->
+                                 2^22 where a level is cut into slices (see
+                                 gx_explore), whole levels elsewhere          */
   const uint8_t* monitor_bad; /* host, n_states of monitor_proc bytes, nonzero
                                  = bad local state; NULL: no safety check      */
 } gx_explore_opts;
@@ -327,16 +326,18 @@ typedef struct {
  *   opts   nullable.
  *   out    filled on success; free with gx_explore_result_free.
  *
- * Device buffers (frontiers, successor buffer, deadlock list, network image)
- * are owned by the table, allocated on first use and grown on demand; later
- * explorations into the same table reuse them.  A level is expanded in
- * slices sized so that neither the next frontier nor the successor buffer
- * can overflow even if every successor were new; each slice is one
- * successor-generation launch followed by one find-or-put-and-append launch
- * on opts->hip_stream.  The network image (the transition tables of every
- * process and rule, about one word per local state and transition) is read
- * from LDS when it fits 11776 words (46 KiB), else from global memory (up to
- * 2^26 words; such networks skip the small-level path).
+ * Device buffers (frontiers, deadlock list, the log of the first levels,
+ * network image) are owned by the table, allocated on first use and grown on
+ * demand; later explorations into the same table reuse them.  Tables of up to
+ * 256 MiB get frontier and deadlock buffers of as many states as they have
+ * slots at once (within the caller's limits): no level can overflow them, and
+ * the levels are launched one after the other on opts->hip_stream, 16 between
+ * read-backs.  With larger tables a level whose successors might not fit the
+ * next frontier, if every one were new, is expanded in slices that do, the
+ * buffers growing between them.  The network image (the transition tables of
+ * every process and rule, about one word per local state and transition) is
+ * read from LDS when the tables fit 11776 words (46 KiB), else from global
+ * memory (up to 2^26 words).
  *
  * Safety check (Sec. 3: the negation of a safety property is an automaton
  * added to the network as one more process): with opts->monitor_bad set, a

@@ -36,35 +36,25 @@ gx_status compile_network_image(const gx_network* net, std::vector<uint32_t>* im
                                 uint64_t* max_succ);
 
 // instantiated in gx_batch_s1.hip, gx_batch_s2.hip, gx_batch_s4.hip
-template <int S>
-hipError_t batch_launch(uint32_t B, uint32_t G, uint32_t U, const BatchArgs& a, uint32_t grid,
-                        size_t lds, hipStream_t s);
-template <int S>
-int batch_resident(uint32_t B, uint32_t G, uint32_t U, size_t lds);
-extern template hipError_t batch_launch<1>(uint32_t, uint32_t, uint32_t, const BatchArgs&,
-                                           uint32_t, size_t, hipStream_t);
-extern template hipError_t batch_launch<2>(uint32_t, uint32_t, uint32_t, const BatchArgs&,
-                                           uint32_t, size_t, hipStream_t);
-extern template hipError_t batch_launch<4>(uint32_t, uint32_t, uint32_t, const BatchArgs&,
-                                           uint32_t, size_t, hipStream_t);
-extern template int batch_resident<1>(uint32_t, uint32_t, uint32_t, size_t);
-extern template int batch_resident<2>(uint32_t, uint32_t, uint32_t, size_t);
-extern template int batch_resident<4>(uint32_t, uint32_t, uint32_t, size_t);
-template <int S>
-hipError_t batch_init(uint32_t B, uint32_t G, uint32_t U, const BatchArgs& a, hipStream_t s);
-extern template hipError_t batch_init<1>(uint32_t, uint32_t, uint32_t, const BatchArgs&,
-                                         hipStream_t);
-extern template hipError_t batch_init<2>(uint32_t, uint32_t, uint32_t, const BatchArgs&,
-                                         hipStream_t);
-extern template hipError_t batch_init<4>(uint32_t, uint32_t, uint32_t, const BatchArgs&,
-                                         hipStream_t);
+extern template hipError_t batch_launch<1>(uint32_t, const BatchArgs&, uint32_t, size_t,
+                                           hipStream_t);
+extern template int batch_resident<1>(uint32_t, size_t);
+extern template hipError_t batch_init<1>(uint32_t, const BatchArgs&, hipStream_t);
+extern template hipError_t batch_launch<2>(uint32_t, const BatchArgs&, uint32_t, size_t,
+                                           hipStream_t);
+extern template int batch_resident<2>(uint32_t, size_t);
+extern template hipError_t batch_init<2>(uint32_t, const BatchArgs&, hipStream_t);
+extern template hipError_t batch_launch<4>(uint32_t, const BatchArgs&, uint32_t, size_t,
+                                           hipStream_t);
+extern template int batch_resident<4>(uint32_t, size_t);
+extern template hipError_t batch_init<4>(uint32_t, const BatchArgs&, hipStream_t);
 // instantiated in gx_serve_s1.hip, gx_serve_s2.hip, gx_serve_s4.hip
-extern template hipError_t serve_launch<1>(uint32_t, uint32_t, uint32_t, const ServeArgs&,
-                                           uint32_t, size_t, hipStream_t);
-extern template hipError_t serve_launch<2>(uint32_t, uint32_t, uint32_t, const ServeArgs&,
-                                           uint32_t, size_t, hipStream_t);
-extern template hipError_t serve_launch<4>(uint32_t, uint32_t, uint32_t, const ServeArgs&,
-                                           uint32_t, size_t, hipStream_t);
+extern template hipError_t serve_launch<1>(uint32_t, const ServeArgs&, uint32_t, size_t,
+                                           hipStream_t);
+extern template hipError_t serve_launch<2>(uint32_t, const ServeArgs&, uint32_t, size_t,
+                                           hipStream_t);
+extern template hipError_t serve_launch<4>(uint32_t, const ServeArgs&, uint32_t, size_t,
+                                           hipStream_t);
 
 namespace {
 
@@ -260,9 +250,9 @@ hipError_t enqueue_run(gx_batch* b, hipStream_t stream) {
       return e;
     const BatchArgs a = class_args(c);
     switch (c.S) {
-      case 1: e = batch_launch<1>(c.B, c.G, c.U, a, c.grid, c.lds, c.side); break;
-      case 2: e = batch_launch<2>(c.B, c.G, c.U, a, c.grid, c.lds, c.side); break;
-      default: e = batch_launch<4>(c.B, c.G, c.U, a, c.grid, c.lds, c.side); break;
+      case 1: e = batch_launch<1>(c.B, a, c.grid, c.lds, c.side); break;
+      case 2: e = batch_launch<2>(c.B, a, c.grid, c.lds, c.side); break;
+      default: e = batch_launch<4>(c.B, a, c.grid, c.lds, c.side); break;
     }
     if (e != hipSuccess) return e;
     if ((e = hipEventRecord(c.ev_done, c.side)) != hipSuccess) return e;
@@ -276,6 +266,7 @@ hipError_t enqueue_run(gx_batch* b, hipStream_t stream) {
 // b->step_status.
 gx_status run_stepped(gx_batch* b, hipStream_t stream) {
   const size_t nk = b->classes.size();
+  const uint32_t cus = resident_grid(b->device, 1);
   std::vector<std::vector<uint64_t>> n_in(nk);
   std::vector<std::vector<uint8_t>> cur(nk), live(nk);
   b->step_levels.assign(b->n, std::vector<uint64_t>(1, 1));
@@ -297,9 +288,9 @@ gx_status run_stepped(gx_batch* b, hipStream_t stream) {
     const BatchArgs a = class_args(c);
     hipError_t e;
     switch (c.S) {
-      case 1: e = batch_init<1>(c.B, c.G, c.U, a, stream); break;
-      case 2: e = batch_init<2>(c.B, c.G, c.U, a, stream); break;
-      default: e = batch_init<4>(c.B, c.G, c.U, a, stream); break;
+      case 1: e = batch_init<1>(c.B, a, stream); break;
+      case 2: e = batch_init<2>(c.B, a, stream); break;
+      default: e = batch_init<4>(c.B, a, stream); break;
     }
     if (e != hipSuccess) return GX_EDEVICE;
   }
@@ -312,7 +303,10 @@ gx_status run_stepped(gx_batch* b, hipStream_t stream) {
       gx_batch::Class& c = b->classes[ci];
       const uint32_t nc = static_cast<uint32_t>(c.members.size());
       uint32_t n_jobs = 0;
-      uint64_t tiles = 0;
+      uint64_t tiles = 0, states = 0;
+      for (uint32_t k = 0; k < nc; ++k)
+        if (live[ci][k]) states += n_in[ci][k];
+      const uint32_t qs = step_lanes(states, cus);
       for (uint32_t k = 0; k < nc; ++k) {
         if (!live[ci][k]) continue;
         // the descriptor from the instance's static part (BatchInst, mirrored
@@ -335,8 +329,8 @@ gx_status run_stepped(gx_batch* b, hipStream_t stream) {
                                                  offsetof(BatchGlobal, dead_used));
         x.dead_tag = c.dead_tag;
         x.tag = k;
-        x.pad = 0;
-        tiles += (n_in[ci][k] + 255) / 256;
+        x.qs = qs;
+        tiles += step_groups(n_in[ci][k], qs);
       }
       if (n_jobs == 0) continue;
       any = true;
@@ -354,9 +348,9 @@ gx_status run_stepped(gx_batch* b, hipStream_t stream) {
       if (e == hipSuccess) {
         const uint32_t grid = static_cast<uint32_t>(tiles);
         switch (c.S) {
-          case 1: e = serve_launch<1>(c.B, c.G, c.U, sa, grid, c.lds, cs); break;
-          case 2: e = serve_launch<2>(c.B, c.G, c.U, sa, grid, c.lds, cs); break;
-          default: e = serve_launch<4>(c.B, c.G, c.U, sa, grid, c.lds, cs); break;
+          case 1: e = serve_launch<1>(c.B, sa, grid, c.lds, cs); break;
+          case 2: e = serve_launch<2>(c.B, sa, grid, c.lds, cs); break;
+          default: e = serve_launch<4>(c.B, sa, grid, c.lds, cs); break;
         }
       }
       if (e == hipSuccess) {
@@ -765,12 +759,12 @@ gx_status gx_batch_create(const gx_network* nets, uint32_t n, const gx_batch_opt
       return GX_EDEVICE;
     }
     c.h_inst = std::move(hi);
-    c.lds = (c.img_stride + gx::kStageWords) * sizeof(uint32_t);
+    c.lds = gx::step_lds(S, c.img_stride);
     int per_cu = 1;
     switch (S) {
-      case 1: per_cu = gx::batch_resident<1>(c.B, c.G, c.U, c.lds); break;
-      case 2: per_cu = gx::batch_resident<2>(c.B, c.G, c.U, c.lds); break;
-      default: per_cu = gx::batch_resident<4>(c.B, c.G, c.U, c.lds); break;
+      case 1: per_cu = gx::batch_resident<1>(c.B, c.lds); break;
+      case 2: per_cu = gx::batch_resident<2>(c.B, c.lds); break;
+      default: per_cu = gx::batch_resident<4>(c.B, c.lds); break;
     }
     c.grid = static_cast<uint32_t>(per_cu) * static_cast<uint32_t>(cus);
   }

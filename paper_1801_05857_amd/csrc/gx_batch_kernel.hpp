@@ -92,7 +92,7 @@ __device__ inline uint32_t ld_rlx(const uint32_t* p) {
 
 // Put every instance's initial state into its frontier buffer 0 and insert it
 // into its table: one wavefront per instance, lane 0 holds the key.
-template <int S, int B, int G, int U>
+template <int S, int B>
 __global__ __launch_bounds__(64) void batch_init_kernel(BatchArgs a) {
   const uint32_t i = blockIdx.x;
   if (i >= a.n) return;
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(64) void batch_init_kernel(BatchArgs a) {
     for (int x = 0; x < S; ++x) in.f[0][x] = key[x];
   }
   LaneStats st;
-  const uint8_t r = find_or_put_lanes<S, B, G, U>(in.t, key, __lane_id() == 0, st);
+  const uint8_t r = find_or_put_quads<S, B>(in.t, key, __lane_id() == 0, st);
   if (__lane_id() == 0 && r != kNew) {
     // table not empty of it, or full: the instance fails before its first level
     atomicOr(ctr_at(a.state[i].ctr, kCtrFlags),
@@ -113,14 +113,13 @@ __global__ __launch_bounds__(64) void batch_init_kernel(BatchArgs a) {
   }
 }
 
-template <int S, int B, int G, int U>
+template <int S, int B>
 __global__ __launch_bounds__(256) void batch_explore_kernel(BatchArgs a) {
-  extern __shared__ uint32_t smem[];
+  extern __shared__ __align__(16) uint32_t smem[];
   __shared__ uint32_t sh_inst, sh_tile, sh_entry, sh_stop;
   uint32_t* img = smem;
-  uint32_t* stage = smem + a.img_stride + (threadIdx.x >> 6) * (kStageWords / 4);
+  uint32_t* lds = smem + a.img_stride + (threadIdx.x >> 6) * wave_words<S, false>();
   uint32_t cached = 0xFFFFFFFFu;
-  LaneStats st;
 
   while (true) {
     if (threadIdx.x == 0) {
@@ -194,7 +193,6 @@ __global__ __launch_bounds__(256) void batch_explore_kernel(BatchArgs a) {
     j.img = img;
     const uint32_t cur = uniform32(bs.cur);
     j.frontier_in = uniform_ptr(static_cast<const uint32_t*>(in.f[cur]));
-    j.first = static_cast<uint64_t>(tile) * 256 + (threadIdx.x & ~63u);
     j.n_in = uniform64(bs.n_in);
     j.frontier_out = uniform_ptr(in.f[cur ^ 1]);
     j.cap_out = uniform64(in.cap);
@@ -204,8 +202,17 @@ __global__ __launch_bounds__(256) void batch_explore_kernel(BatchArgs a) {
     j.dead_cap = a.dead_cap;
     j.dead_ctr = &a.g->dead_used;
     j.ctr = bs.ctr;
-    j.dtab = nullptr;
-    if (j.first < j.n_in) expand_wave<S, B, G, U>(j, stage, st);
+    j.tail = kCtrTail;
+    // no table statistics: they would keep six counters per lane live across
+    // the whole persistent loop
+    WaveAcc acc;
+    // a level of one tile spreads over the workgroup's lanes
+    const uint32_t qs = lanes_per_state(j.n_in, 4, 6);
+    const uint32_t per = 64u >> qs;
+    const uint64_t n_tiles = (j.n_in + per - 1) / per;
+    const uint64_t own = static_cast<uint64_t>(tile) * 4 + (threadIdx.x >> 6);
+    expand_tiles<S, B, false>(j, lds, uniform64(own), n_tiles, n_tiles, qs, acc);
+    (void)finish_block<S, false>(j, lds, acc, 0);
     __syncthreads();
     if (threadIdx.x == 0) {
       // release this tile's frontier writes (an L2 write-back; no
@@ -254,75 +261,61 @@ __global__ __launch_bounds__(256) void batch_explore_kernel(BatchArgs a) {
       }
     }
   }
-  // no table statistics: they would keep six counters per lane live across
-  // the whole persistent loop (12 more VGPRs, two fewer waves per SIMD)
-  (void)st;
 }
 
-template <int S, int B, int G, int U>
-struct BatchKernels {  // init + persistent launch of one (S, B, G, U) class
+template <int S, int B>
+struct BatchKernels {  // init + persistent launch of one (S, B) class
   static hipError_t launch(const BatchArgs& a, uint32_t grid, size_t lds, hipStream_t s) {
-    hipLaunchKernelGGL((batch_init_kernel<S, B, G, U>), dim3(a.n), dim3(64), 0, s, a);
-    hipLaunchKernelGGL((batch_explore_kernel<S, B, G, U>), dim3(grid), dim3(256), lds, s, a);
+    hipLaunchKernelGGL((batch_init_kernel<S, B>), dim3(a.n), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((batch_explore_kernel<S, B>), dim3(grid), dim3(256), lds, s, a);
     return hipGetLastError();
   }
   static hipError_t init(const BatchArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((batch_init_kernel<S, B, G, U>), dim3(a.n), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((batch_init_kernel<S, B>), dim3(a.n), dim3(64), 0, s, a);
     return hipGetLastError();
   }
+  // (asked once per class, before its first launch)
   static int resident_per_cu(size_t lds) {
+    if (lds > 65536 &&
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&batch_explore_kernel<S, B>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            static_cast<int>(lds)) != hipSuccess)
+      return 1;
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, batch_explore_kernel<S, B, G, U>, 256,
-                                                     lds) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, batch_explore_kernel<S, B>, 256, lds) !=
+        hipSuccess)
       return 1;
     return b > 0 ? b : 1;
   }
 };
 
-}  // namespace gx
-
-namespace gx {
+#define GX_BATCH_DISPATCH(call)                     \
+  switch (B) {                                      \
+    case 8: return BatchKernels<S, 8>::call;        \
+    case 16: return BatchKernels<S, 16>::call;      \
+    case 32: return BatchKernels<S, 32>::call;      \
+    case 64: return BatchKernels<S, 64>::call;      \
+  }
 
 template <int S>
-hipError_t batch_launch(uint32_t B, uint32_t G, uint32_t U, const BatchArgs& a, uint32_t grid,
-                        size_t lds, hipStream_t s) {
-#define GX_BATCH_CASE(BB, GG, UU) \
-  if (B == BB && G == GG && U == UU) return BatchKernels<S, BB, GG, UU>::launch(a, grid, lds, s);
-#define GX_BATCH_B(BB) GX_BATCH_CASE(BB, 8, 1) GX_BATCH_CASE(BB, 8, 2) GX_BATCH_CASE(BB, 16, 1) GX_BATCH_CASE(BB, 16, 2)
-#define GX_BATCH_B4(BB) GX_BATCH_B(BB) GX_BATCH_CASE(BB, 4, 1) GX_BATCH_CASE(BB, 4, 2)
-  GX_BATCH_B4(8) GX_BATCH_B4(16) GX_BATCH_B4(32) GX_BATCH_B(64)
-#undef GX_BATCH_B4
-#undef GX_BATCH_B
-#undef GX_BATCH_CASE
+hipError_t batch_launch(uint32_t B, const BatchArgs& a, uint32_t grid, size_t lds, hipStream_t s) {
+  GX_BATCH_DISPATCH(launch(a, grid, lds, s))
   return hipErrorInvalidValue;
 }
 
 // The initial states alone (the stepped schedule expands the levels with
 // the multi-job step kernel).
 template <int S>
-hipError_t batch_init(uint32_t B, uint32_t G, uint32_t U, const BatchArgs& a, hipStream_t s) {
-#define GX_BATCH_CASE(BB, GG, UU) \
-  if (B == BB && G == GG && U == UU) return BatchKernels<S, BB, GG, UU>::init(a, s);
-#define GX_BATCH_B(BB) GX_BATCH_CASE(BB, 8, 1) GX_BATCH_CASE(BB, 8, 2) GX_BATCH_CASE(BB, 16, 1) GX_BATCH_CASE(BB, 16, 2)
-#define GX_BATCH_B4(BB) GX_BATCH_B(BB) GX_BATCH_CASE(BB, 4, 1) GX_BATCH_CASE(BB, 4, 2)
-  GX_BATCH_B4(8) GX_BATCH_B4(16) GX_BATCH_B4(32) GX_BATCH_B(64)
-#undef GX_BATCH_B4
-#undef GX_BATCH_B
-#undef GX_BATCH_CASE
+hipError_t batch_init(uint32_t B, const BatchArgs& a, hipStream_t s) {
+  GX_BATCH_DISPATCH(init(a, s))
   return hipErrorInvalidValue;
 }
 
 template <int S>
-int batch_resident(uint32_t B, uint32_t G, uint32_t U, size_t lds) {
-#define GX_BATCH_CASE(BB, GG, UU) \
-  if (B == BB && G == GG && U == UU) return BatchKernels<S, BB, GG, UU>::resident_per_cu(lds);
-#define GX_BATCH_B(BB) GX_BATCH_CASE(BB, 8, 1) GX_BATCH_CASE(BB, 8, 2) GX_BATCH_CASE(BB, 16, 1) GX_BATCH_CASE(BB, 16, 2)
-#define GX_BATCH_B4(BB) GX_BATCH_B(BB) GX_BATCH_CASE(BB, 4, 1) GX_BATCH_CASE(BB, 4, 2)
-  GX_BATCH_B4(8) GX_BATCH_B4(16) GX_BATCH_B4(32) GX_BATCH_B(64)
-#undef GX_BATCH_B4
-#undef GX_BATCH_B
-#undef GX_BATCH_CASE
+int batch_resident(uint32_t B, size_t lds) {
+  GX_BATCH_DISPATCH(resident_per_cu(lds))
   return 1;
 }
+#undef GX_BATCH_DISPATCH
 
 }  // namespace gx

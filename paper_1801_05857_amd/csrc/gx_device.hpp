@@ -752,11 +752,11 @@ __device__ inline uint8_t find_or_put_quads(const TableDev& t, const uint32_t (&
 // lane shuffles; the result comes back to the owner lane.  Returns the owner's
 // status (kNew / kSeen / kFull / kInvalid).  Must be reached by the whole
 // wavefront.
-template <int S, int B, int G, int U, bool kQuads = G == 4>
+template <int S, int B, int G, int U>
 __device__ inline uint8_t find_or_put_lanes(const TableDev& t, const uint32_t (&own)[S],
                                             bool own_act, LaneStats& st) {
   static_assert(U >= 1 && U <= G && (G % U) == 0, "keys in flight per subgroup");
-  if constexpr (kQuads) {
+  if constexpr (G == 4) {
     return find_or_put_quads<S, B>(t, own, own_act, st);
   } else {
     const int lane = __lane_id();

@@ -1,29 +1,22 @@
 // Level-synchronous breadth-first exploration of the synchronous product of a
 // network of LTSs (Sec. 3 of the paper), built on the bucketed find-or-put.
 //
-// A level is expanded in slices; each slice is two kernels on the caller's
-// stream:
-//   1. gen_level_kernel: 256 frontier states per workgroup, one per lane;
-//      every lane counts its state's product successors from the
-//      LDS-resident network image (none: a deadlock, recorded at once), one
-//      atomic add per workgroup reserves their room in the successor buffer,
-//      and the wavefront writes them with coalesced stores;
-//   2. append_kernel: find-or-put of the successor buffer by subgroups of G
-//      lanes; NEW states are gathered per wavefront in LDS and moved to the
-//      next frontier with one atomic add and coalesced stores.
+// A level is one launch of level_kernel: every wavefront walks its frontier
+// states' transitions in the LDS-resident network image, puts the successors
+// into the table 64 at a time and gathers the NEW ones for the next frontier.
+// Levels whose successors fit the buffers in any case are strung together
+// with no read-back between them; a level that might not fit is expanded in
+// slices by the host, which grows the buffers.
 // The paper's tool scans the hash table for states still to explore and keeps
 // a per-block cache of new states (Sec. 3); here the next level is an explicit
 // compacted frontier, so no scan of the table is needed.  With a safety
 // monitor, every completed level is scanned once for states whose monitor
 // process is in a bad state.
 //
-// Levels of at most kSmallMaxLevel states (the first levels of every
-// exploration, the last ones of most, all of a small one) are instead
-// expanded on one workgroup, up to kSmallLevels of them per launch with no
-// host round trip in between: the first levels by lds_levels_kernel, which
-// decides NEW or SEEN from an LDS set of the states reached so far (the
-// table holds nothing else yet) and puts them into the table at the end;
-// later small levels by small_levels_kernel, which probes the table.
+// The first levels of an exploration (all of a small one) are expanded on one
+// workgroup by lds_levels_kernel, which decides NEW or SEEN from an LDS set of
+// the states reached so far (the table holds nothing else yet) and puts them
+// into the table at the end.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,18 +31,15 @@
 
 namespace gx {
 // instantiated in gx_explore_s1.hip, gx_explore_s2.hip and gx_explore_s4.hip
-extern template hipError_t launch_gen<1>(const GenArgs&, uint32_t, size_t, hipStream_t);
-extern template hipError_t launch_gen<2>(const GenArgs&, uint32_t, size_t, hipStream_t);
-extern template hipError_t launch_gen<4>(const GenArgs&, uint32_t, size_t, hipStream_t);
-extern template hipError_t append_b<1>(uint32_t, uint32_t, uint32_t, const AppendArgs&, uint32_t,
-                                       hipStream_t);
-extern template hipError_t append_b<2>(uint32_t, uint32_t, uint32_t, const AppendArgs&, uint32_t,
-                                       hipStream_t);
-extern template hipError_t append_b<4>(uint32_t, uint32_t, uint32_t, const AppendArgs&, uint32_t,
-                                       hipStream_t);
-extern template hipError_t launch_small<1>(uint32_t, const SmallArgs&, hipStream_t);
-extern template hipError_t launch_small<2>(uint32_t, const SmallArgs&, hipStream_t);
-extern template hipError_t launch_small<4>(uint32_t, const SmallArgs&, hipStream_t);
+extern template hipError_t launch_level<1>(uint32_t, const LevelArgs&, bool, uint32_t, size_t,
+                                             hipStream_t);
+extern template uint32_t level_blocks_per_cu<1>(uint32_t, size_t);
+extern template hipError_t launch_level<2>(uint32_t, const LevelArgs&, bool, uint32_t, size_t,
+                                             hipStream_t);
+extern template uint32_t level_blocks_per_cu<2>(uint32_t, size_t);
+extern template hipError_t launch_level<4>(uint32_t, const LevelArgs&, bool, uint32_t, size_t,
+                                             hipStream_t);
+extern template uint32_t level_blocks_per_cu<4>(uint32_t, size_t);
 extern template hipError_t launch_lds_levels<1>(uint32_t, SmallArgs, size_t, hipStream_t);
 extern template hipError_t launch_lds_levels<2>(uint32_t, SmallArgs, size_t, hipStream_t);
 extern template hipError_t launch_lds_levels<4>(uint32_t, SmallArgs, size_t, hipStream_t);
@@ -57,25 +47,15 @@ extern template hipError_t launch_lds_levels<4>(uint32_t, SmallArgs, size_t, hip
 
 namespace gx {
 
-// ------------------------------------------------------------ network image
-// Layout (32-bit words, indices absolute within the image):
-//   [0] P  [1] R  [2] S  [3] words per state
-//   [4 + p]         field of process p: word | shift << 8 | width << 16
-//   [4 + P + p]     index of the start of p's free-transition offsets
-//   [4 + 2P + r]    index of rule r's record
-//   rule record:    n_parts, then per participant (process q, index of the
-//                   start of its offsets for this rule)
-//   offsets arrays: n_q + 1 entries each; entry l is the index of the first
-//                   target of local state l, entry l+1 one past its last
-//   target arrays:  target local states
 constexpr uint32_t kMaxSuccPerState = 1u << 20;
-// Largest image of any kernel: one that exceeds kImgMaxWords (the LDS budget)
-// is read from global memory by the exploration's generation kernel.
+// Largest transition tables of any kernel: ones that exceed kImgMaxWords (the
+// LDS budget) are read from global memory by the level kernel.
 constexpr uint32_t kImgGlobalMaxWords = 1u << 26;
 
 struct NetImage {
   std::vector<uint32_t> img;
   uint32_t words = 0;
+  uint64_t table_words = 0;  // size of the transition tables, what the limits apply to
   std::vector<uint32_t> field;  // per process
   std::vector<uint32_t> initial;
   uint64_t max_succ = 0;
@@ -132,65 +112,87 @@ gx_status compile_network(const gx_network* net, NetImage* out,
       if (l.src[t] >= l.n_states || l.dst[t] >= l.n_states || l.label[t] >= NL) return GX_EINVAL;
   }
 
-  std::vector<uint32_t> img(4 + 2 * P + R, 0);
-  img[0] = P;
-  img[1] = R;
+  std::vector<uint32_t> img(4 + 4 * (static_cast<size_t>(P) + R), 0);
   img[2] = slot_words(words);
   img[3] = words;
-  for (uint32_t p = 0; p < P; ++p) img[4 + p] = field[p];
-  // rule records
-  for (uint32_t r = 0; r < R; ++r) {
-    img[4 + 2 * P + r] = static_cast<uint32_t>(img.size());
-    img.push_back(static_cast<uint32_t>(parts[r].size()));
-    for (uint32_t q : parts[r]) {
-      img.push_back(q);
-      img.push_back(0);  // patched below
-    }
-  }
-  auto too_big = [&]() { return img.size() > max_words; };
-  // CSR of targets selected by `keep` for process p: offsets then targets
+  // what the limits on a network's size count: a few words per process and
+  // rule, an offset per local state and a word per transition of every
+  // process and every rule participant
+  uint64_t table_words = 4 + 2ull * P + R;
+  for (uint32_t r = 0; r < R; ++r) table_words += 1 + 2ull * parts[r].size();
+  // CSR of the targets selected by `keep` for process p: offsets, then targets
+  // shifted to p's field
   auto emit_csr = [&](uint32_t p, auto keep, uint64_t* max_deg) -> uint32_t {
     const gx_lts& l = net->procs[p];
-    std::vector<std::vector<uint32_t>> by_src(l.n_states);
+    const uint32_t shift = (field[p] >> 8) & 0xFF;
+    std::vector<uint32_t> start(static_cast<size_t>(l.n_states) + 1, 0);
+    uint64_t n = 0;
     for (uint32_t t = 0; t < l.n_trans; ++t)
-      if (keep(l.label[t])) by_src[l.src[t]].push_back(l.dst[t]);
+      if (keep(l.label[t])) {
+        ++start[l.src[t] + 1];
+        ++n;
+      }
+    table_words += l.n_states + 1ull + n;
+    *max_deg = 0;
+    if (table_words > max_words || n == 0) return 0;
     const uint32_t off_at = static_cast<uint32_t>(img.size());
-    img.resize(img.size() + l.n_states + 1);
-    uint64_t md = 0;
+    const uint32_t first = off_at + l.n_states + 1;
+    img.resize(first + n);
     for (uint32_t s = 0; s < l.n_states; ++s) {
-      img[off_at + s] = static_cast<uint32_t>(img.size());
-      for (uint32_t d : by_src[s]) img.push_back(d);
-      md = std::max<uint64_t>(md, by_src[s].size());
-      if (too_big()) return 0;
+      *max_deg = std::max<uint64_t>(*max_deg, start[s + 1]);
+      start[s + 1] += start[s];
     }
-    img[off_at + l.n_states] = static_cast<uint32_t>(img.size());
-    *max_deg = md;
+    for (uint32_t s = 0; s <= l.n_states; ++s) img[off_at + s] = first + start[s];
+    for (uint32_t t = 0; t < l.n_trans; ++t)
+      if (keep(l.label[t])) img[first + start[l.src[t]]++] = l.dst[t] << shift;
     return off_at;
   };
   uint64_t max_succ = 0;
-  for (uint32_t p = 0; p < P && !too_big(); ++p) {
+  uint32_t n_items = 0;
+  auto item = [&]() { return 4 + 4 * static_cast<size_t>(n_items); };
+  for (uint32_t p = 0; p < P && table_words <= max_words; ++p) {
     uint64_t md = 0;
     const uint32_t at = emit_csr(p, [&](uint32_t a) { return !governed[p][a]; }, &md);
-    img[4 + P + p] = at;
+    if (md == 0) continue;
+    img[item() + 2] = field[p];
+    img[item() + 3] = at;
+    ++n_items;
     max_succ += md;
   }
-  for (uint32_t r = 0; r < R && !too_big(); ++r) {
-    const uint32_t rec = img[4 + 2 * P + r];
+  for (uint32_t r = 0; r < R && table_words <= max_words; ++r) {
+    const uint32_t np = static_cast<uint32_t>(parts[r].size());
     uint64_t prod = 1;
-    for (size_t i = 0; i < parts[r].size() && !too_big(); ++i) {
-      const uint32_t q = parts[r][i];
-      const uint32_t want = static_cast<uint32_t>(net->rules[size_t(r) * P + q]);
+    std::vector<uint32_t> at(np, 0);
+    for (uint32_t i = 0; i < np && table_words <= max_words; ++i) {
+      const uint32_t want = static_cast<uint32_t>(net->rules[size_t(r) * P + parts[r][i]]);
       uint64_t md = 0;
-      const uint32_t at = emit_csr(q, [&](uint32_t a) { return a == want; }, &md);
-      img[rec + 2 + 2 * i] = at;
+      at[i] = emit_csr(parts[r][i], [&](uint32_t a) { return a == want; }, &md);
       prod = std::min<uint64_t>(prod * md, uint64_t(1) << 40);
     }
+    if (prod == 0) continue;  // never enabled
+    img[item() + 2] = field[parts[r][np - 1]];
+    img[item() + 3] = at[np - 1];
+    if (np == 2) {
+      img[item()] = field[parts[r][0]];
+      img[item() + 1] = at[0];
+    } else if (np > 2) {
+      img[item()] = kItemGeneral;
+      img[item() + 1] = static_cast<uint32_t>(img.size());
+      img.push_back(np - 1);
+      for (uint32_t i = 0; i + 1 < np; ++i) {
+        img.push_back(field[parts[r][i]]);
+        img.push_back(at[i]);
+      }
+    }
+    ++n_items;
     max_succ += prod;
   }
-  if (too_big()) return GX_EINVAL;
+  if (table_words > max_words) return GX_EINVAL;
+  img[0] = n_items;
   if (max_succ > kMaxSuccPerState) return GX_EINVAL;
   out->img = std::move(img);
   out->words = words;
+  out->table_words = table_words;
   out->field = std::move(field);
   out->initial.resize(P);
   for (uint32_t p = 0; p < P; ++p) out->initial[p] = net->procs[p].initial;
@@ -285,22 +287,31 @@ hipError_t launch_monitor_scan(uint32_t S, const uint32_t* states, uint64_t n, u
   return hipGetLastError();
 }
 
-// One slice of a level: successor generation, then find-or-put-and-append.
-hipError_t launch_slice(const gx_table* t, const GenArgs& g, uint32_t grid, size_t lds,
-                        const AppendArgs& ap, uint32_t cus, hipStream_t s) {
-  hipError_t e = hipSuccess;
+hipError_t launch_level_of(const gx_table* t, const LevelArgs& a, bool filter, uint32_t grid,
+                           size_t lds, hipStream_t s) {
   switch (t->S) {
-    case 1:
-      if ((e = launch_gen<1>(g, grid, lds, s)) != hipSuccess) return e;
-      return append_b<1>(t->B, t->G, t->U, ap, cus, s);
-    case 2:
-      if ((e = launch_gen<2>(g, grid, lds, s)) != hipSuccess) return e;
-      return append_b<2>(t->B, t->G, t->U, ap, cus, s);
-    case 4:
-      if ((e = launch_gen<4>(g, grid, lds, s)) != hipSuccess) return e;
-      return append_b<4>(t->B, t->G, t->U, ap, cus, s);
+    case 1: return launch_level<1>(t->B, a, filter, grid, lds, s);
+    case 2: return launch_level<2>(t->B, a, filter, grid, lds, s);
+    case 4: return launch_level<4>(t->B, a, filter, grid, lds, s);
   }
   return hipErrorInvalidValue;
+}
+
+// Level-kernel workgroups the table's device holds at once, and the LDS of
+// each.
+uint32_t level_grid(const gx_table* t, uint32_t img_stride, bool filter, uint32_t cus,
+                    size_t* lds) {
+  switch (t->S) {
+    case 1:
+      *lds = level_lds<1>(img_stride, filter);
+      return cus * level_blocks_per_cu<1>(t->B, *lds);
+    case 2:
+      *lds = level_lds<2>(img_stride, filter);
+      return cus * level_blocks_per_cu<2>(t->B, *lds);
+    default:
+      *lds = level_lds<4>(img_stride, filter);
+      return cus * level_blocks_per_cu<4>(t->B, *lds);
+  }
 }
 
 // Grow a device buffer of `cap` elements of `elem` bytes to at least `need`
@@ -341,9 +352,9 @@ namespace gx {
 // cache line each), what a small-level launch reports, the initial state's
 // slot and the network image.
 constexpr size_t kCtrWords = kCtrCount * kCtrSpread;
-constexpr size_t kBlockWords = kCtrWords + sizeof(SmallOut) / sizeof(uint64_t);
+constexpr size_t kBlockWords = kCtrWords + sizeof(LevelCtl) / sizeof(uint64_t);
 constexpr size_t kControlBytes =
-    kBlockWords * sizeof(uint64_t) + 4 * sizeof(uint32_t) + kImgMaxWords * sizeof(uint32_t);
+    kBlockWords * sizeof(uint64_t) + 4 * sizeof(uint32_t) + kImgStoreWords * sizeof(uint32_t);
 
 // Where gx_explore_noalloc puts its results.
 struct FixedOut {
@@ -499,9 +510,10 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   // resident buffers of the table (allocated on first use, grow-only)
   const uint32_t img_words = static_cast<uint32_t>(ni.img.size());
   // an image beyond the LDS budget stays in global memory (a buffer of its
-  // own), read there by the generation kernel; such networks take no
-  // small-level path (its kernels keep the image in LDS)
-  const bool global_img = img_words > gx::kImgMaxWords;
+  // own), read there by the level kernel; such networks' first levels are
+  // not expanded in LDS (that kernel keeps the image there)
+  const bool global_img =
+      ni.table_words > gx::kImgMaxWords || img_words > gx::kImgStoreWords;
   const uint32_t img_stride = global_img ? 0u : (img_words + 3) & ~3u;
   // the control block: the level's counters, what a small-level launch
   // reports (read back together), the initial state's slot, the image
@@ -532,14 +544,29 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   }
   eb.key = reinterpret_cast<uint32_t*>(eb.ctr + kBlockWords);
   eb.img = eb.key + 4;
-  eb.img_cap = gx::kImgMaxWords;
+  eb.img_cap = gx::kImgStoreWords;
+  // A level's NEW states are in the table, so a frontier buffer as large as
+  // the table takes any level; likewise the deadlocks.  Tables of up to
+  // kRoomyBytes get such buffers at once (the caller's limits aside), others
+  // ones that grow with the levels.
+  constexpr uint64_t kRoomyBytes = 256ull << 20;
+  const uint64_t n_slots = t->n_buckets * (t->B / S);
+  const bool roomy = !fixed && n_slots * state_bytes <= kRoomyBytes;
+  auto first_buf = [&](uint32_t** p, uint64_t* cap, uint64_t limit) -> gx_status {
+    const uint64_t want = roomy ? std::min<uint64_t>(n_slots, limit) : 1;
+    gx_status r = grow_buf(p, cap, want, 0, limit);
+    if (r == GX_ENOMEM && want > 1) r = grow_buf(p, cap, 1, 0, limit);
+    return r;
+  };
   for (int k = 0; k < 2; ++k)
-    if ((s = grow_buf(&eb.f[k], &eb.f_cap[k], 1, 0, max_cap)) != GX_OK) return s;
-  if ((s = grow_buf(&eb.dead, &eb.dead_cap, 1, 0, max_dead)) != GX_OK) return s;
-  // Small levels run on one workgroup (small_levels_kernel) when a level of
-  // `small_limit` states has room for all its successors in the frontier and
-  // successor buffers as they are; not with a safety monitor or the local
-  // duplicate filter, whose per-level work stays on the host path.
+    if ((s = first_buf(&eb.f[k], &eb.f_cap[k], max_cap)) != GX_OK) return s;
+  if ((s = first_buf(&eb.dead, &eb.dead_cap, max_dead)) != GX_OK) return s;
+  // a state's successors never exceed a preallocated buffer
+  if (fixed && max_succ > eb.succ_cap) return GX_ENOMEM;
+  // The first levels run on one workgroup (lds_levels_kernel) while a level
+  // of `small_limit` states has room for all its successors in the frontier
+  // buffer and the log; not with a safety monitor or the local duplicate
+  // filter, whose per-level work that kernel does not do.
   const bool dedup = opts && opts->local_dedup;
   uint64_t small_limit = 0;
   if (!monitor && !dedup && !global_img) {
@@ -556,7 +583,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   // the level's counters, spread over cache lines on the device, read back
   // into pinned host memory
   uint64_t* ctr_raw = eb.ctr_host;
-  const gx::SmallOut* small_out = reinterpret_cast<const gx::SmallOut*>(ctr_raw + kCtrWords);
+  const gx::LevelCtl* ctl = reinterpret_cast<const gx::LevelCtl*>(ctr_raw + kCtrWords);
   auto ctr = [&](uint32_t k) { return ctr_raw[k * gx::kCtrSpread]; };
   t->holds_states = true;  // from here on the exploration writes the table
   {
@@ -571,13 +598,13 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     if (hipMemcpyAsync(eb.ctr, ctr_raw, up, hipMemcpyHostToDevice, stream) != hipSuccess)
       return GX_EDEVICE;
   }
-  // the first level for the table-probing kernels (the small-level kernels
-  // take the initial state from eb.key)
+  // the first level for the level kernel (lds_levels_kernel takes the initial
+  // state from eb.key)
   if (small_limit == 0 &&
       hipMemcpyAsync(eb.f[0], eb.key, state_bytes, hipMemcpyDeviceToDevice, stream) != hipSuccess)
     return GX_EDEVICE;
-  // the initial state must be new, i.e. the table must not hold it yet (with
-  // small levels, the first small launch inserts it)
+  // the initial state must be new, i.e. the table must not hold it yet
+  // (lds_levels_kernel puts it there itself)
   if (small_limit == 0) {
     if (gx::launch_find_or_put(t, eb.key, 1, eb.status, nullptr, stream) != hipSuccess)
       return GX_EDEVICE;
@@ -630,31 +657,6 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     }
   }
 
-  gx::GenArgs g;
-  g.img = global_img ? eb.img_global : eb.img;
-  g.img_words = img_words;
-  g.img_stride = img_stride;  // LDS words of the image (0: read from global memory)
-  g.global_img = global_img ? 1u : 0u;
-  g.ctr = eb.ctr;
-  g.dedup = opts && opts->local_dedup ? 1u : 0u;
-  gx::AppendArgs ap;
-  ap.t = t->dev();
-  ap.keys = nullptr;
-  ap.n_keys = nullptr;  // per slice: the successor counter its generation uses
-  ap.ctr = eb.ctr;
-  ap.count_trans = g.dedup ? 0u : 1u;  // the filtered generation counts its own
-  // a three-word state's successors go through the successor buffer as three
-  // words, not as their four-word slots (a quarter less written and read;
-  // the filtered generation stages whole slots)
-  g.succ_words = S == 4 && t->w == 3 && !g.dedup ? 3u : S;
-  g.pad = 0;
-  ap.key_words = g.succ_words;
-  const uint32_t dedup_words =
-      g.dedup ? 4u * (S == 1 ? gx::dedup_entries<1>() : S == 2 ? gx::dedup_entries<2>()
-                                                               : gx::dedup_entries<4>())
-              : 0u;
-  const size_t lds =
-      (img_stride + (g.dedup ? gx::kStageWords + dedup_words : 0u) + 8) * sizeof(uint32_t);
   int cus = 256;
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device);
   auto read_ctr = [&]() -> gx_status {
@@ -669,91 +671,107 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     return GX_OK;
   };
 
-  // Levels are expanded in slices small enough that even if every successor
-  // were new the next frontier could not overflow: slice * max_succ <= free
-  // frontier room (and slice <= free deadlock room, one record per state at
-  // most).  The room is tracked from these worst-case bounds; only when it is
-  // short of a full slice is the exact fill read back (one synchronisation),
-  // and the buffers grow, keeping their contents, to hold a full slice.
+  size_t lds = 0;
+  const uint32_t grid_max = gx::level_grid(t, img_stride, dedup, static_cast<uint32_t>(cus), &lds);
+  uint32_t max_qs = 0;
+  while (max_qs < 6 && (2u << max_qs) <= ni.img[0]) ++max_qs;
+  gx::LevelArgs la{};
+  la.t = t->dev();
+  la.img = global_img ? eb.img_global : eb.img;
+  la.img_words = img_words;
+  la.img_stride = img_stride;
+  la.ctr = eb.ctr;
+  la.tail = gx::kCtrTail;
+  la.waves = grid_max * (gx::kLevelBlock / 64);
+  la.max_qs = max_qs;
+
   gx::LevelList levels(fixed);
   levels.push(1);
   uint64_t n_in = 1;
   int cur = 0;
   uint64_t dead_known = 0;
-  // 16384 workgroups per launch unless the caller asks for less
-  const uint64_t kTargetSlice = opts && opts->slice_states ? opts->slice_states : 1u << 22;
-  constexpr uint64_t kMaxRoom = 1ull << 28;    // states of frontier room one slice may claim
-  uint64_t slice_no = 0;  // successor counters alternate from slice to slice
-  bool init_inserted = small_limit == 0;
-  while (n_in > 0 && !stop) {
-    bool small = n_in <= small_limit;
-    if (small && std::min<uint64_t>(eb.dead_cap, max_dead) - dead_known < n_in) {
-      // every state of a small level may be a deadlock: room for a level
-      s = grow_buf(&eb.dead, &eb.dead_cap, std::min<uint64_t>(dead_known + n_in, max_dead),
-                   dead_known, max_dead);
-      if (s != GX_OK && s != GX_ENOMEM) return s;
-      small = std::min<uint64_t>(eb.dead_cap, max_dead) - dead_known >= n_in;
+  // (the caller's limits on the buffers keep the plain bound of a level's
+  // successors)
+  const bool any_fits = !(opts && opts->frontier_capacity);
+  const uint64_t slice_states = opts ? opts->slice_states : 0;
+  if (small_limit > 0) {
+    // the first levels, LDS-resident while the table holds nothing else
+    gx::SmallArgs sa{};
+    sa.t = t->dev();
+    sa.img = eb.img;
+    sa.img_words = img_words;
+    sa.img_stride = img_stride;
+    sa.f = eb.f[0];
+    sa.log = eb.succ;
+    sa.log_cap = eb.succ_cap;
+    sa.dead = eb.dead;
+    sa.dead_cap = std::min<uint64_t>(eb.dead_cap, max_dead);
+    sa.ctr = eb.ctr;
+    sa.out = reinterpret_cast<gx::LevelCtl*>(eb.ctr + kCtrWords);
+    sa.limit = small_limit;
+    sa.init_key = eb.key;
+    sa.max_succ = static_cast<uint32_t>(max_succ);
+    sa.max_qs = max_qs;
+    const size_t lds_limit = gx::lds_per_workgroup(t->device);
+    hipError_t e = hipErrorInvalidValue;
+    switch (S) {
+      case 1: e = gx::launch_lds_levels<1>(t->B, sa, lds_limit, stream); break;
+      case 2: e = gx::launch_lds_levels<2>(t->B, sa, lds_limit, stream); break;
+      case 4: e = gx::launch_lds_levels<4>(t->B, sa, lds_limit, stream); break;
     }
-    if (small) {
-      // small levels on one workgroup, as many as stay small (up to
-      // kSmallLevels per launch), then one read-back
-      gx::SmallArgs sa;
-      sa.t = t->dev();
-      sa.img = eb.img;
-      sa.img_words = img_words;
-      sa.img_stride = img_stride;
-      sa.f[0] = eb.f[0];
-      sa.f[1] = eb.f[1];
-      sa.f_cap = std::min<uint64_t>(std::min<uint64_t>(eb.f_cap[0], eb.f_cap[1]), max_cap);
-      sa.cur = static_cast<uint32_t>(cur);
-      sa.n_in = n_in;
-      sa.succ = eb.succ;
-      sa.succ_cap = eb.succ_cap;
-      sa.dead = eb.dead;
-      sa.dead_cap = std::min<uint64_t>(eb.dead_cap, max_dead);
-      sa.ctr = eb.ctr;
-      sa.out = reinterpret_cast<gx::SmallOut*>(eb.ctr + kCtrWords);
-      sa.limit = small_limit;
-      sa.init_key = init_inserted ? nullptr : eb.key;
-      sa.set_mask = 0;
-      sa.max_succ = static_cast<uint32_t>(max_succ);
-      hipError_t e = hipErrorInvalidValue;
-      bool lds_mode = false;
-      if (!init_inserted) {
-        // the first levels: LDS-resident while the table holds nothing else
-        const size_t lds_limit = gx::lds_per_workgroup(t->device);
-        switch (S) {
-          case 1: e = gx::launch_lds_levels<1>(t->B, sa, lds_limit, stream); break;
-          case 2: e = gx::launch_lds_levels<2>(t->B, sa, lds_limit, stream); break;
-          case 4: e = gx::launch_lds_levels<4>(t->B, sa, lds_limit, stream); break;
-        }
-        lds_mode = e == hipSuccess;
-        if (!lds_mode) (void)hipGetLastError();
-      }
-      if (!lds_mode) {
-        switch (S) {
-          case 1: e = gx::launch_small<1>(t->B, sa, stream); break;
-          case 2: e = gx::launch_small<2>(t->B, sa, stream); break;
-          case 4: e = gx::launch_small<4>(t->B, sa, stream); break;
-        }
-      }
-      if (e != hipSuccess) return GX_EDEVICE;
+    if (e != hipSuccess) return GX_EDEVICE;
+    if ((s = read_ctr()) != GX_OK) return s;
+    if (ctl->init_status == gx::kFull) return GX_ETABLEFULL;
+    if (ctl->init_status != gx::kNew) return GX_EINVAL;
+    for (uint64_t k = 0; k < ctl->n_levels; ++k) levels.push(ctl->levels[k]);
+    dead_known = ctr(gx::kCtrDead);
+    if (dead_known > std::min<uint64_t>(eb.dead_cap, max_dead)) return GX_ENOMEM;
+    n_in = ctl->n_in;
+    cur = static_cast<int>(ctl->cur);
+  }
+
+  // 16384 workgroups' worth of states per launch unless the caller asks for
+  // less
+  const uint64_t kTargetSlice = slice_states ? slice_states : 1u << 22;
+  constexpr uint64_t kMaxRoom = 1ull << 28;  // states of frontier room one slice may claim
+  constexpr uint32_t kString = 16;           // launches between read-backs
+  while (n_in > 0 && !stop) {
+    // Levels whose successors fit whatever they are: a string of launches,
+    // each taking the level the one before left.
+    const uint64_t f_both = std::min<uint64_t>(std::min<uint64_t>(eb.f_cap[0], eb.f_cap[1]), max_cap);
+    const uint64_t d_cap_now = std::min<uint64_t>(eb.dead_cap, max_dead);
+    uint64_t limit = any_fits && f_both >= n_slots ? ~0ull : f_both / max_succ;
+    if (slice_states) limit = std::min<uint64_t>(limit, slice_states);
+    if (!monitor && n_in <= limit && d_cap_now - std::min(dead_known, d_cap_now) >= n_in) {
+      la.f[0] = eb.f[0];
+      la.f[1] = eb.f[1];
+      la.cap_out = f_both;
+      la.dead = eb.dead;
+      la.dead_cap = d_cap_now;
+      la.cur = static_cast<uint32_t>(cur);
+      la.first = 0;
+      la.n_in = n_in;
+      la.ctl = reinterpret_cast<gx::LevelCtl*>(eb.ctr + kCtrWords);
+      la.limit = limit;
+      for (la.link = 0; la.link < kString; ++la.link)
+        if (gx::launch_level_of(t, la, dedup, grid_max, lds, stream) != hipSuccess)
+          return GX_EDEVICE;
       if ((s = read_ctr()) != GX_OK) return s;
-      if (!init_inserted) {
-        init_inserted = true;
-        if (small_out->init_status == gx::kFull) return GX_ETABLEFULL;
-        if (small_out->init_status != gx::kNew) return GX_EINVAL;
-      }
-      for (uint64_t k = 0; k < small_out->n_levels; ++k) levels.push(small_out->levels[k]);
+      const gx::LevelCtl::Entry& e = ctl->entry[kString & 1u];
+      for (uint64_t k = 0; k < e.n_levels; ++k) levels.push(ctl->levels[k]);
       dead_known = ctr(gx::kCtrDead);
-      if (dead_known > std::min<uint64_t>(eb.dead_cap, max_dead)) return GX_ENOMEM;
-      n_in = small_out->n_in;
-      cur = static_cast<int>(small_out->cur);
-      // (an LDS-resident launch may hand its first level straight to the
-      // table-probing kernels)
-      if (!lds_mode && small_out->n_levels == 0 && n_in > 0) return GX_EDEVICE;  // no progress
+      if (dead_known > d_cap_now) return GX_ENOMEM;
+      n_in = e.n_in;
+      cur = static_cast<int>(e.cur);
       continue;
     }
+    // Otherwise the level is expanded in slices small enough that even if
+    // every successor were new the next frontier could not overflow: slice *
+    // max_succ <= free frontier room (and slice <= free deadlock room, one
+    // record per state at most).  The room is tracked from these worst-case
+    // bounds; only when it is short of a full slice is the exact fill read
+    // back (one synchronisation), and the buffers grow, keeping their
+    // contents, to hold a full slice.
     const int nxt = cur ^ 1;
     uint64_t tail_known = 0, bound = 0, dead_bound = dead_known, pos = 0;
     while (pos < n_in) {
@@ -764,18 +782,22 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
       // honours this call's limits
       auto f_cap = [&]() { return std::min<uint64_t>(eb.f_cap[nxt], max_cap); };
       auto d_cap = [&]() { return std::min<uint64_t>(eb.dead_cap, max_dead); };
-      auto f_room = [&]() { return (f_cap() - bound) / max_succ; };
+      auto f_room = [&]() {
+        return any_fits && f_cap() >= n_slots ? ~0ull : (f_cap() - bound) / max_succ;
+      };
       // a deadlock buffer at its limit no longer bounds the slice: records
       // past it are counted, not stored, and the call ends with GX_ENOMEM
       auto d_room = [&]() { return d_cap() >= max_dead ? ~0ull : d_cap() - dead_bound; };
       if (std::min<uint64_t>(f_room(), d_room()) < want) {
         if (bound != tail_known || dead_bound != dead_known) {
           if ((s = read_ctr()) != GX_OK) return s;
-          tail_known = bound = ctr(gx::kCtrTail);
+          tail_known = bound = ctr(la.tail);
           dead_known = dead_bound = ctr(gx::kCtrDead);
         }
         if (f_room() < want) {
-          s = grow_buf(&eb.f[nxt], &eb.f_cap[nxt], bound + want * max_succ, tail_known, max_cap);
+          const uint64_t need = bound + want * max_succ;
+          s = grow_buf(&eb.f[nxt], &eb.f_cap[nxt],
+                       any_fits ? std::min<uint64_t>(need, n_slots) : need, tail_known, max_cap);
           if (s == GX_ENOMEM)  // no room for a full slice: settle for one state
             s = grow_buf(&eb.f[nxt], &eb.f_cap[nxt], bound + max_succ, tail_known,
                          std::min<uint64_t>(max_cap, bound + max_succ));
@@ -787,44 +809,31 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
           if (s != GX_OK) return s;
         }
       }
-      const uint64_t slice = std::min<uint64_t>(want, std::min<uint64_t>(f_room(), d_room()));
-      if (slice == 0) return GX_ENOMEM;
-      // the slice's successors (all of them, in the worst case) fit the
-      // successor buffer
-      const uint64_t slice_keys = slice * max_succ;
-      if (eb.succ_cap < slice_keys) {
-        s = grow_buf(&eb.succ, &eb.succ_cap, slice_keys, 0, ~0ull);
-        if (s == GX_ENOMEM)  // settle for what fits, at least one state
-          s = grow_buf(&eb.succ, &eb.succ_cap, max_succ, 0, ~0ull);
-        if (s != GX_OK) return s;
-      }
-      const uint64_t run = std::min<uint64_t>(slice, eb.succ_cap / max_succ);
-      g.frontier_in = eb.f[cur] + pos * S;
-      g.n_in = run;
-      g.succ = eb.succ;
-      g.succ_cap = eb.succ_cap;
-      g.dead = eb.dead;
-      g.dead_cap = d_cap();
-      ap.keys = eb.succ;
-      ap.keys_cap = eb.succ_cap;
-      ap.frontier_out = eb.f[nxt];
-      ap.cap_out = f_cap();
-      // the first slice's generation clears the next-frontier tail; each
-      // slice's clears the other successor counter for the next slice
-      g.reset_tail = pos == 0 ? 1u : 0u;
-      g.succ_ctr = (slice_no++ & 1) ? gx::kCtrSuccAlt : gx::kCtrSucc;
-      ap.n_keys = eb.ctr + g.succ_ctr * gx::kCtrSpread;
-      const uint64_t grid = (run + 255) / 256;
-      if (gx::launch_slice(t, g, static_cast<uint32_t>(grid), lds, ap, static_cast<uint32_t>(cus),
-                           stream) != hipSuccess)
-        return GX_EDEVICE;
+      const uint64_t run = std::min<uint64_t>(want, std::min<uint64_t>(f_room(), d_room()));
+      if (run == 0) return GX_ENOMEM;
+      la.f[cur] = eb.f[cur];
+      la.f[nxt] = eb.f[nxt];
+      la.cap_out = f_cap();
+      la.dead = eb.dead;
+      la.dead_cap = d_cap();
+      la.cur = static_cast<uint32_t>(cur);
+      la.first = pos;
+      la.n_in = run;
+      la.ctl = nullptr;
+      const uint32_t qs = gx::lanes_per_state(run, la.waves, max_qs);
+      const uint64_t per_group = (64u >> qs) * (gx::kLevelBlock / 64);
+      const uint32_t grid = static_cast<uint32_t>(
+          std::min<uint64_t>(grid_max, (run + per_group - 1) / per_group));
+      if (gx::launch_level_of(t, la, dedup, grid, lds, stream) != hipSuccess) return GX_EDEVICE;
       pos += run;
-      bound += run * max_succ;
+      bound += std::min<uint64_t>(run * max_succ, n_slots);
       dead_bound += run;
     }
     if ((s = read_ctr()) != GX_OK) return s;
     dead_known = ctr(gx::kCtrDead);
-    n_in = ctr(gx::kCtrTail);
+    n_in = ctr(la.tail);
+    // (the level's launches have cleared the other tail for the next one)
+    la.tail = la.tail == gx::kCtrTail ? gx::kCtrTailAlt : gx::kCtrTail;
     if (n_in) levels.push(n_in);
     if (monitor && n_in) {
       // scan the level just completed; if the record buffer was short, grow

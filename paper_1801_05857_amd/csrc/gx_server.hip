@@ -34,12 +34,12 @@ gx_status compile_network_image(const gx_network* net, std::vector<uint32_t>* im
                                 uint64_t* max_succ);
 
 // instantiated in gx_serve_s1.hip, gx_serve_s2.hip and gx_serve_s4.hip
-extern template hipError_t serve_launch<1>(uint32_t, uint32_t, uint32_t, const ServeArgs&,
-                                           uint32_t, size_t, hipStream_t);
-extern template hipError_t serve_launch<2>(uint32_t, uint32_t, uint32_t, const ServeArgs&,
-                                           uint32_t, size_t, hipStream_t);
-extern template hipError_t serve_launch<4>(uint32_t, uint32_t, uint32_t, const ServeArgs&,
-                                           uint32_t, size_t, hipStream_t);
+extern template hipError_t serve_launch<1>(uint32_t, const ServeArgs&, uint32_t, size_t,
+                                           hipStream_t);
+extern template hipError_t serve_launch<2>(uint32_t, const ServeArgs&, uint32_t, size_t,
+                                           hipStream_t);
+extern template hipError_t serve_launch<4>(uint32_t, const ServeArgs&, uint32_t, size_t,
+                                           hipStream_t);
 
 namespace {
 
@@ -224,7 +224,7 @@ void admit(gx_server* s) {
                              s->stream) ==
                   hipSuccess &&
               launch_find_or_put(t, t->eb.key, 1, t->eb.status, nullptr, s->stream) == hipSuccess &&
-              hipMemcpyAsync(s->d_img + static_cast<uint64_t>(j.slot) * kImgMaxWords,
+              hipMemcpyAsync(s->d_img + static_cast<uint64_t>(j.slot) * kImgStoreWords,
                              r->img.data(), r->img.size() * sizeof(uint32_t),
                              hipMemcpyHostToDevice, s->stream) == hipSuccess &&
               hipStreamSynchronize(s->stream) == hipSuccess;
@@ -312,6 +312,7 @@ void finish_job(gx_server* s, size_t k, gx_status st, uint64_t transitions, uint
 
 void step_loop(gx_server* s) {
   std::vector<ServeJob> hjs[3];  // per slot-width class
+  const uint32_t cus = resident_grid(s->device, 1);
   while (true) {
     {
       std::unique_lock<std::mutex> lock(s->mu);
@@ -329,13 +330,16 @@ void step_loop(gx_server* s) {
     for (uint32_t S : {1u, 2u, 4u}) {
       std::vector<ServeJob>& hj = hjs[S == 1 ? 0 : S == 2 ? 1 : 2];
       hj.clear();
-      uint64_t tiles = 0;
+      uint64_t tiles = 0, states = 0;
       uint32_t img_max = 0;
+      for (auto& j : s->active)
+        if (j.t->S == S) states += j.n_in;
+      const uint32_t qs = step_lanes(states, cus);
       for (auto& j : s->active) {
         if (j.t->S != S) continue;
         ServeJob x;
         x.t = j.t->dev();
-        x.img_off = j.slot * kImgMaxWords;
+        x.img_off = j.slot * kImgStoreWords;
         x.img_words = static_cast<uint32_t>(j.r->img.size());
         x.frontier_in = j.t->eb.f[j.cur];
         x.n_in = j.n_in;
@@ -348,8 +352,8 @@ void step_loop(gx_server* s) {
         x.dead_ctr = nullptr;
         x.dead_tag = nullptr;
         x.tag = 0;
-        x.pad = 0;
-        tiles += (j.n_in + 255) / 256;
+        x.qs = qs;
+        tiles += step_groups(j.n_in, qs);
         img_max = std::max<uint32_t>(img_max, x.img_words);
         hj.push_back(x);
       }
@@ -360,7 +364,7 @@ void step_loop(gx_server* s) {
       a.n_jobs = static_cast<uint32_t>(hj.size());
       a.img = s->d_img;
       a.img_stride = (img_max + 3) & ~3u;
-      const size_t lds = (a.img_stride + kStageWords) * sizeof(uint32_t);
+      const size_t lds = step_lds(S, a.img_stride);
       // staged in pinned memory (one region per class, reused only after the
       // step's synchronisation) so the upload is a plain asynchronous copy
       ServeJob* staged = s->h_jobs + (S == 1 ? 0 : S == 2 ? 1 : 2) * s->max_active;
@@ -369,9 +373,9 @@ void step_loop(gx_server* s) {
                                     hj.size() * sizeof(ServeJob), hipMemcpyHostToDevice, s->stream);
       if (e == hipSuccess) {
         switch (S) {
-          case 1: e = serve_launch<1>(c[0], c[1], c[2], a, static_cast<uint32_t>(tiles), lds, s->stream); break;
-          case 2: e = serve_launch<2>(c[0], c[1], c[2], a, static_cast<uint32_t>(tiles), lds, s->stream); break;
-          default: e = serve_launch<4>(c[0], c[1], c[2], a, static_cast<uint32_t>(tiles), lds, s->stream); break;
+          case 1: e = serve_launch<1>(c[0], a, static_cast<uint32_t>(tiles), lds, s->stream); break;
+          case 2: e = serve_launch<2>(c[0], a, static_cast<uint32_t>(tiles), lds, s->stream); break;
+          default: e = serve_launch<4>(c[0], a, static_cast<uint32_t>(tiles), lds, s->stream); break;
         }
       }
       if (e != hipSuccess) ok = false;
@@ -504,7 +508,7 @@ gx_status gx_server_create(const gx_server_opts* opts, gx_server** out) {
   s->cfg[3][2] = s->cfg[4][2];
   if (hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess ||
       hipMalloc(&s->d_jobs, 3ull * s->max_active * sizeof(gx::ServeJob)) != hipSuccess ||
-      hipMalloc(&s->d_img, static_cast<uint64_t>(s->max_active) * gx::kImgMaxWords *
+      hipMalloc(&s->d_img, static_cast<uint64_t>(s->max_active) * gx::kImgStoreWords *
                                sizeof(uint32_t)) != hipSuccess ||
       hipMalloc(&s->d_ctr, gx::kSlotCtrWords * s->max_active * sizeof(uint64_t)) != hipSuccess ||
       hipHostMalloc(&s->h_ctr, gx::kSlotCtrWords * s->max_active * sizeof(uint64_t)) !=
