@@ -161,6 +161,7 @@ struct gx_batch {
   std::vector<uint32_t> Bi, Gi, Ui;
   std::vector<uint64_t> tab_off, tab_words;  // per instance: its table partition in its class
   bool keep_states = false;
+  gx::SortSpace sort;
   std::vector<Class> classes;
   hipEvent_t ev_fork = nullptr;
   bool use_graph = false;
@@ -922,8 +923,11 @@ gx_status gx_batch_results(gx_batch* b, gx_explore_result* outs, gx_status* inst
       outs[i].n_deadlocks = dl.size();
       outs[i].deadlocks = D;
       if (b->keep_states) {
-        const gx_status ks = gx::sorted_keys_malloc(c.tables + b->tab_off[i], b->tab_words[i], S,
-                                                    w, &outs[i].states);
+        // (the instance's frontier buffers, free once the run is over)
+        const gx::BatchInst& in = c.h_inst[k];
+        const gx_status ks =
+            gx::sorted_keys_malloc(c.tables + b->tab_off[i], b->tab_words[i], S, w, in.f[0],
+                                   in.f[1], in.cap, b->sort, nullptr, &outs[i].states);
         if (ks != GX_OK) {
           gx_explore_result_free(&outs[i]);
           inst_status[i] = ks;

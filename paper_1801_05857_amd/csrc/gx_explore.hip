@@ -865,31 +865,42 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   const uint64_t n_dead = ctr(gx::kCtrDead);
   if (n_dead > std::min<uint64_t>(eb.dead_cap, max_dead)) return GX_ENOMEM;
   if (fixed) return gx::finish_fixed(*fixed, levels, n_dead, ctr(gx::kCtrTrans), eb.dead, S, t->w);
-  std::vector<uint32_t> raw(n_dead * S);
-  if (n_dead && hipMemcpy(raw.data(), eb.dead, raw.size() * sizeof(uint32_t),
-                          hipMemcpyDeviceToHost) != hipSuccess)
-    return GX_EDEVICE;
-  std::vector<std::array<uint32_t, 4>> dl(n_dead);
-  for (uint64_t i = 0; i < n_dead; ++i) {
-    dl[i] = {0, 0, 0, 0};
-    for (uint32_t k = 0; k < t->w; ++k) dl[i][k] = raw[i * S + k];
-  }
-  std::sort(dl.begin(), dl.end());
+  // n records of S words at src, sorted, w words each, to dst
+  auto sorted_out = [&](uint32_t* src, uint64_t n, uint32_t* dst) -> gx_status {
+    if (n == 0) return GX_OK;
+    if (n >= gx::kSortMin && n < (uint64_t(1) << 32) &&
+        grow_buf(&eb.f[0], &eb.f_cap[0], n, 0, ~0ull) == GX_OK) {
+      const gx_status r = gx::sort_records(S, t->w, src, eb.f[0], n, eb.sort, dst, stream);
+      if (r != GX_ENOMEM) return r;
+    }
+    std::vector<uint32_t> raw(n * S);
+    if (hipMemcpy(raw.data(), src, raw.size() * sizeof(uint32_t), hipMemcpyDeviceToHost) !=
+        hipSuccess)
+      return GX_EDEVICE;
+    std::vector<std::array<uint32_t, 4>> v(n);
+    for (uint64_t i = 0; i < n; ++i) {
+      v[i] = {0, 0, 0, 0};
+      for (uint32_t k = 0; k < t->w; ++k) v[i][k] = raw[i * S + k];
+    }
+    std::sort(v.begin(), v.end());
+    for (uint64_t i = 0; i < n; ++i)
+      for (uint32_t k = 0; k < t->w; ++k) dst[i * t->w + k] = v[i][k];
+    return GX_OK;
+  };
 
   uint64_t* lv = static_cast<uint64_t*>(std::malloc(sizeof(uint64_t) * levels.size()));
   uint32_t* dd = static_cast<uint32_t*>(std::malloc(sizeof(uint32_t) * (n_dead * t->w + 1)));
-  if (!lv || !dd) {
+  s = lv && dd ? sorted_out(eb.dead, n_dead, dd) : GX_ENOMEM;
+  if (s != GX_OK) {
     std::free(lv);
     std::free(dd);
-    return GX_ENOMEM;
+    return s;
   }
   uint64_t n_states = 0;
   for (uint64_t k = 0; k < levels.size(); ++k) {
     lv[k] = levels.at(k);
     n_states += levels.at(k);
   }
-  for (uint64_t i = 0; i < n_dead; ++i)
-    for (uint32_t k = 0; k < t->w; ++k) dd[i * t->w + k] = dl[i][k];
   out->n_states = n_states;
   out->n_transitions = ctr(gx::kCtrTrans);
   out->words_per_state = t->w;
@@ -904,27 +915,30 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   out->reserved = 0;
   out->states = nullptr;
   if (monitor) {
-    std::vector<uint32_t> vraw(viol_total * S);
-    if (viol_total && hipMemcpy(vraw.data(), eb.viol, vraw.size() * sizeof(uint32_t),
-                                hipMemcpyDeviceToHost) != hipSuccess) {
+    const uint64_t n_viol = viol_total + (init_violates ? 1 : 0);
+    uint32_t* vv = static_cast<uint32_t*>(std::malloc(sizeof(uint32_t) * (n_viol * t->w + 1)));
+    s = vv ? sorted_out(eb.viol, viol_total, vv) : GX_ENOMEM;
+    if (s != GX_OK) {
+      std::free(vv);
       gx_explore_result_free(out);
-      return GX_EDEVICE;
+      return s;
     }
-    std::vector<std::array<uint32_t, 4>> vl(viol_total);
-    for (uint64_t i = 0; i < viol_total; ++i) {
-      vl[i] = {0, 0, 0, 0};
-      for (uint32_t k = 0; k < t->w; ++k) vl[i][k] = vraw[i * S + k];
+    if (init_violates) {
+      // the initial state to its place among the others
+      uint64_t lo = 0, hi = viol_total;
+      while (lo < hi) {
+        const uint64_t mid = (lo + hi) / 2;
+        if (std::lexicographical_compare(vv + mid * t->w, vv + (mid + 1) * t->w, init,
+                                         init + t->w))
+          lo = mid + 1;
+        else
+          hi = mid;
+      }
+      std::memmove(vv + (lo + 1) * t->w, vv + lo * t->w,
+                   (viol_total - lo) * t->w * sizeof(uint32_t));
+      std::copy(init, init + t->w, vv + lo * t->w);
     }
-    if (init_violates) vl.push_back({init[0], init[1], init[2], init[3]});
-    std::sort(vl.begin(), vl.end());
-    uint32_t* vv = static_cast<uint32_t*>(std::malloc(sizeof(uint32_t) * (vl.size() * t->w + 1)));
-    if (!vv) {
-      gx_explore_result_free(out);
-      return GX_ENOMEM;
-    }
-    for (size_t i = 0; i < vl.size(); ++i)
-      for (uint32_t k = 0; k < t->w; ++k) vv[i * t->w + k] = vl[i][k];
-    out->n_violations = vl.size();
+    out->n_violations = n_viol;
     out->violations = vv;
   }
   return GX_OK;

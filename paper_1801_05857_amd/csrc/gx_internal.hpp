@@ -9,9 +9,26 @@
 #include "../../include/gx.h"
 #include "gx_device.hpp"
 
+namespace gx {
+
+// Device workspace of the sorted lists (see gx_sort.hip); grow-only, freed
+// with its owner.
+struct SortSpace {
+  uint32_t* words = nullptr;
+  uint64_t cap = 0;
+  SortSpace() = default;
+  SortSpace(const SortSpace&) = delete;
+  SortSpace& operator=(const SortSpace&) = delete;
+  ~SortSpace();
+  bool reserve(uint64_t n);  // room for lists of n records
+};
+
+}  // namespace gx
+
 // Device buffers of the exploration driver, owned by a table and reused by
 // every exploration into it (grow-only).
 struct gx_explore_buffers {
+  gx::SortSpace sort;
   uint32_t* img = nullptr;  // network image (in the control block, see ctr)
   uint64_t img_cap = 0;     // words
   uint32_t* img_global = nullptr;  // an image too large for LDS (own allocation)
@@ -116,14 +133,36 @@ hipError_t launch_find_or_put(const gx_table* t, const uint32_t* keys, uint64_t 
 hipError_t fill_words(uint32_t* p, uint64_t n_words, uint32_t value, int device,
                       hipStream_t stream);
 
+// Lists of fewer records, and storage of fewer words, are sorted on the host:
+// a few kernels and a read-back take longer.
+constexpr uint64_t kSortMin = 2048;
+constexpr uint64_t kGatherMin = 32768;
+
+// The keys stored in n_slots slots of S words on the device: their number to
+// *n, and the first `cap` of them, in any order, to out (nullable).
+// Synchronous.
+gx_status gather_keys(uint32_t S, const uint32_t* words, uint64_t n_slots, uint32_t* out,
+                      uint64_t cap, SortSpace& ws, uint64_t* n, hipStream_t stream);
+// The n (< 2^32) keys that gather_keys has just put into a, sorted
+// lexicographically, w words each, to host memory.  b: as large as a; both
+// are overwritten.  Synchronous.
+gx_status sort_gathered(uint32_t S, uint32_t w, uint32_t* a, uint32_t* b, uint64_t n,
+                        SortSpace& ws, uint32_t* host, hipStream_t stream);
+// The same for n records of S words in a.
+gx_status sort_records(uint32_t S, uint32_t w, uint32_t* a, uint32_t* b, uint64_t n, SortSpace& ws,
+                       uint32_t* host, hipStream_t stream);
+
 // The keys stored in total_words words of bucket storage (slots of S words,
-// keys of w words) on the device, sorted lexicographically, w words each.
-// Waits for all device work.  *n_out receives the number of keys.
+// keys of w words) on the device, sorted lexicographically, w words each, by
+// the host.  Waits for all device work.  *n_out receives the number of keys.
 gx_status sorted_keys(const uint32_t* dev_words, uint64_t total_words, uint32_t S, uint32_t w,
                       std::vector<uint32_t>* out, uint64_t* n_out);
-// The same into a malloc'd array (for gx_explore_result.states).
+// The same into a malloc'd array (for gx_explore_result.states), sorted on
+// the device in a and b (buffers of `room` records each) where they hold the
+// keys, else by the host.
 gx_status sorted_keys_malloc(const uint32_t* dev_words, uint64_t total_words, uint32_t S,
-                             uint32_t w, uint32_t** out);
+                             uint32_t w, uint32_t* a, uint32_t* b, uint64_t room, SortSpace& ws,
+                             hipStream_t stream, uint32_t** out);
 
 // LDS bytes one workgroup may use on the device (queried once per device).
 size_t lds_per_workgroup(int device);

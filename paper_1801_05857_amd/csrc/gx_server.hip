@@ -113,6 +113,7 @@ struct gx_server {
   char* d_small = nullptr;
   gx_server_stats stats{};
   // owned by the step thread
+  gx::SortSpace sort;
   std::vector<Job> active;
   std::vector<uint32_t> free_slots;
   gx::ServeJob* d_jobs = nullptr;
@@ -277,7 +278,9 @@ void finish_job(gx_server* s, size_t k, gx_status st, uint64_t transitions, uint
     uint32_t* V = nullptr;  // the table's contents, read before its block is released
     if (!L || !D) rs = GX_ENOMEM;
     if (rs == GX_OK && s->keep_states)
-      rs = sorted_keys_malloc(j.t->words, j.t->n_buckets * j.t->B, S, w, &V);
+      // (the job's frontier buffers, free once it is over)
+      rs = sorted_keys_malloc(j.t->words, j.t->n_buckets * j.t->B, S, w, j.t->eb.f[0],
+                              j.t->eb.f[1], j.t->eb.f_cap[0], s->sort, s->stream, &V);
     if (rs == GX_OK) {
       uint64_t total = 0;
       for (size_t l = 0; l < j.levels.size(); ++l) {

@@ -251,7 +251,22 @@ size_t lds_per_workgroup(int device) {
 }
 
 gx_status sorted_keys_malloc(const uint32_t* dev_words, uint64_t total_words, uint32_t S,
-                             uint32_t w, uint32_t** out) {
+                             uint32_t w, uint32_t* a, uint32_t* b, uint64_t room, SortSpace& ws,
+                             hipStream_t stream, uint32_t** out) {
+  if (total_words >= kGatherMin && room < (uint64_t(1) << 32)) {
+    uint64_t n = 0;
+    if (gather_keys(S, dev_words, total_words / S, a, room, ws, &n, stream) == GX_OK && n <= room) {
+      uint32_t* p = static_cast<uint32_t*>(std::malloc(sizeof(uint32_t) * (n * w + 1)));
+      if (!p) return GX_ENOMEM;
+      const gx_status st = sort_gathered(S, w, a, b, n, ws, p, stream);
+      if (st != GX_OK) {
+        std::free(p);
+        return st;
+      }
+      *out = p;
+      return GX_OK;
+    }
+  }
   std::vector<uint32_t> keys;
   uint64_t n = 0;
   const gx_status st = sorted_keys(dev_words, total_words, S, w, &keys, &n);
@@ -423,8 +438,42 @@ gx_status gx_table_copy_raw(gx_table* t, uint32_t* dev_words, uint64_t first, ui
 
 gx_status gx_table_dump(gx_table* t, uint32_t* host_keys, uint64_t cap, uint64_t* n_out) {
   if (!t || !n_out) return GX_EINVAL;
-  std::vector<uint32_t> keys;
   uint64_t count = 0;
+  const uint64_t n_slots = t->n_buckets * (t->B / t->S);
+  if (n_slots * t->S >= gx::kGatherMin) {
+    if (hipDeviceSynchronize() != hipSuccess) return GX_EDEVICE;
+    gx_explore_buffers& e = t->eb;
+    gx_status s = gx::gather_keys(t->S, t->words, n_slots, nullptr, 0, e.sort, &count, nullptr);
+    if (s == GX_EDEVICE) return s;
+    if (s == GX_OK) {
+      if (!host_keys || cap < count) {
+        *n_out = count;
+        return GX_ENOMEM;
+      }
+      // (the frontier buffers, which no exploration is using)
+      bool room = count < (uint64_t(1) << 32);
+      for (int k = 0; k < 2 && room; ++k) {
+        if (e.f_cap[k] >= count && e.f[k]) continue;
+        if (e.f[k]) (void)hipFree(e.f[k]);
+        e.f[k] = nullptr;
+        e.f_cap[k] = 0;
+        room = hipMalloc(&e.f[k], std::max<uint64_t>(count, 1) * t->S * sizeof(uint32_t)) ==
+               hipSuccess;
+        if (room) e.f_cap[k] = std::max<uint64_t>(count, 1);
+        else (void)hipGetLastError();
+      }
+      if (room) s = gx::gather_keys(t->S, t->words, n_slots, e.f[0], count, e.sort, &count, nullptr);
+      if (room && s == GX_OK)
+        s = gx::sort_gathered(t->S, t->w, e.f[0], e.f[1], count, e.sort, host_keys, nullptr);
+      if (room && s == GX_OK) {
+        *n_out = count;
+        return GX_OK;
+      }
+      if (s == GX_EDEVICE) return s;
+    }
+  }
+  // a small table, or no memory for the lists: sorted by the host
+  std::vector<uint32_t> keys;
   const gx_status s = gx::sorted_keys(t->words, t->n_buckets * t->B, t->S, t->w, &keys, &count);
   if (s != GX_OK) return s;
   *n_out = count;
