@@ -211,8 +211,11 @@ __global__ __launch_bounds__(256) void batch_explore_kernel(BatchArgs a) {
     const uint32_t per = 64u >> qs;
     const uint64_t n_tiles = (j.n_in + per - 1) / per;
     const uint64_t own = static_cast<uint64_t>(tile) * 4 + (threadIdx.x >> 6);
-    expand_tiles<S, B, false>(j, lds, uniform64(own), n_tiles, n_tiles, qs, acc);
-    (void)finish_block<S, false>(j, lds, acc, 0);
+    uint32_t sw[S];
+    load_tile<S>(j, uniform64(own), qs, sw);
+    expand_tiles<S, B, false>(j, lds, uniform64(own), n_tiles, n_tiles, qs, sw, acc);
+    uint64_t n_new;
+    (void)finish_block<S, false, false>(j, lds, acc, 0, &n_new);
     __syncthreads();
     if (threadIdx.x == 0) {
       // release this tile's frontier writes (an L2 write-back; no

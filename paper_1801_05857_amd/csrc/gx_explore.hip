@@ -674,7 +674,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   size_t lds = 0;
   const uint32_t grid_max = gx::level_grid(t, img_stride, dedup, static_cast<uint32_t>(cus), &lds);
   uint32_t max_qs = 0;
-  while (max_qs < 6 && (2u << max_qs) <= ni.img[0]) ++max_qs;
+  while (max_qs < 6 && (1u << max_qs) < ni.img[0]) ++max_qs;
   gx::LevelArgs la{};
   la.t = t->dev();
   la.img = global_img ? eb.img_global : eb.img;

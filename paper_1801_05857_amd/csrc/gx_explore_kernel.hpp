@@ -36,25 +36,34 @@ enum : uint32_t { kFlagFrontierOverflow = 1, kFlagTableFull = 2 };
 
 // Field access with mask arithmetic only: a select chain over the words is
 // folded by the compiler into an indexed load from a private array, which
-// would live in scratch memory.
+// would live in scratch memory.  (Bit-field instructions use the low five bits
+// of a shift and a width.)
 template <int S>
 __device__ __forceinline__ uint32_t get_field(const uint32_t (&sw)[S], uint32_t f) {
-  const uint32_t word = f & 0xFF, shift = (f >> 8) & 0xFF, width = f >> 16;
-  uint32_t x = 0;
-#pragma unroll
-  for (int t = 0; t < S; ++t) x |= sw[t] & (0u - static_cast<uint32_t>(word == static_cast<uint32_t>(t)));
-  return (x >> shift) & ((1u << width) - 1u);
+  uint32_t x = sw[0];
+  if constexpr (S == 2) {
+    x ^= (sw[0] ^ sw[1]) & (0u - (f & 1u));
+  } else if constexpr (S == 4) {
+    const uint32_t lo = 0u - (f & 1u), hi = 0u - ((f >> 1) & 1u);
+    const uint32_t a = sw[0] ^ ((sw[0] ^ sw[1]) & lo), b = sw[2] ^ ((sw[2] ^ sw[3]) & lo);
+    x = a ^ ((a ^ b) & hi);
+  }
+  return __builtin_amdgcn_ubfe(x, f >> 8, f >> 16);
 }
 
 // Field f of the state set to v, which is shifted to the field's position.
 template <int S>
 __device__ __forceinline__ void put_field(uint32_t (&sw)[S], uint32_t f, uint32_t v) {
-  const uint32_t word = f & 0xFF;
-  const uint32_t m = ((1u << (f >> 16)) - 1u) << ((f >> 8) & 0xFF);
+  const uint32_t m = ((1u << (f >> 16)) - 1u) << ((f >> 8) & 31u);
+  if constexpr (S == 1) {
+    sw[0] = (sw[0] & ~m) | v;
+  } else {
+    const uint32_t word = f & 0xFF;
 #pragma unroll
-  for (int t = 0; t < S; ++t) {
-    const uint32_t sel = 0u - static_cast<uint32_t>(word == static_cast<uint32_t>(t));
-    sw[t] = (sw[t] & ~(m & sel)) | (v & sel);
+    for (int t = 0; t < S; ++t) {
+      const uint32_t sel = 0u - static_cast<uint32_t>(word == static_cast<uint32_t>(t));
+      sw[t] = (sw[t] & ~(m & sel)) | (v & sel);
+    }
   }
 }
 
@@ -299,6 +308,16 @@ __device__ inline uint32_t dedup_stage(uint32_t* dtab, const uint32_t* stage, ui
   return mask;
 }
 
+// This lane's state of a tile (zero where there is none).
+template <int S>
+__device__ __forceinline__ void load_tile(const WaveJob& j, uint64_t tile, uint32_t qs,
+                                          uint32_t (&sw)[S]) {
+  const uint64_t i = tile * (64u >> qs) + (static_cast<uint32_t>(__lane_id()) >> qs);
+#pragma unroll
+  for (int x = 0; x < S; ++x) sw[x] = 0;
+  if (i < j.n_in) load_slot<S>(j.frontier_in + i * S, sw);
+}
+
 // Expands tiles tile0, tile0 + stride, ... below n_tiles of a level: 64 >>
 // qs frontier states each, 2^qs lanes a state (see walk_items).  Generation
 // and probes share the wavefront: the successors pass through its LDS only
@@ -308,11 +327,12 @@ __device__ inline uint32_t dedup_stage(uint32_t* dtab, const uint32_t* stage, ui
 // find_or_put_quads; the wavefronts of a SIMD overlap one's walk with the
 // others' reads.  NEW states leave the LDS 64 at a time, with one atomic add
 // and one coalesced store; what is left goes out with the workgroup's
-// (finish_block).  Must be reached by the whole wavefront.
+// (finish_block).  sw: tile0's states (load_tile), read before the caller
+// waited for the image.  Must be reached by the whole wavefront.
 template <int S, int B, bool kFilter>
 __device__ __forceinline__ void expand_tiles(const WaveJob& j, uint32_t* lds, uint64_t tile0,
                                              uint64_t n_tiles, uint64_t stride, uint32_t qs,
-                                             WaveAcc& acc) {
+                                             uint32_t (&sw)[S], WaveAcc& acc) {
   constexpr uint32_t kStageKeys = kFilter ? filter_keys<S>() : kWaveKeys;
   constexpr uint32_t kTop = kFilter ? filter_keys<S>() + 128u : kWaveKeys;  // end of the NEW keys
   const uint32_t lane = __lane_id();
@@ -371,10 +391,6 @@ __device__ __forceinline__ void expand_tiles(const WaveJob& j, uint32_t* lds, ui
   for (uint64_t tile = tile0; tile < n_tiles; tile += stride) {
     const uint64_t i = tile * per + (lane >> qs);
     const bool has = i < j.n_in;
-    uint32_t sw[S];
-#pragma unroll
-    for (int x = 0; x < S; ++x) sw[x] = 0;
-    if (has) load_slot<S>(j.frontier_in + i * S, sw);
     const uint32_t own = walk_items<S>(j.img, sw, has, sub, q, stage, cnt,
                                        kFilter ? kStageKeys - 64u : 63u, take);
     acc.trans += own;
@@ -393,6 +409,7 @@ __device__ __forceinline__ void expand_tiles(const WaveJob& j, uint32_t* lds, ui
         if (j.dead_tag) j.dead_tag[d] = j.tag;
       }
     }
+    if (tile + stride < n_tiles) load_tile<S>(j, tile + stride, qs, sw);
   }
   if (cnt) take();
 }
@@ -406,26 +423,42 @@ __device__ inline uint64_t wave_sum64(uint64_t x) {
 }
 
 // The workgroup's wavefronts hand over what they hold: NEW states, transition
-// and duplicate counts, flags.  One atomic of each kind per workgroup.
+// and duplicate counts, flags and (kStats) the table's statistics.  One atomic
+// of each kind per workgroup, all issued together: each takes about half a
+// microsecond, which a small level would otherwise spend several times.
 // `arrive` (0 or 1 << kArriveShift) is added to the tail with the NEW states;
-// returns (to thread 0) the tail before.  Every thread of the workgroup must
-// come here, its wavefront's expand_tiles done; lds: this wavefront's region.
-template <int S, bool kFilter>
+// returns (to thread 0) the tail before and, in *n_new, what was added to it.
+// Every thread of the workgroup must come here, its wavefront's expand_tiles
+// done; lds: this wavefront's region.
+template <int S, bool kFilter, bool kStats>
 __device__ __forceinline__ uint64_t finish_block(const WaveJob& j, const uint32_t* lds,
-                                                 WaveAcc& acc, uint64_t arrive) {
+                                                 WaveAcc& acc, uint64_t arrive, uint64_t* n_new) {
   constexpr uint32_t kTop = kFilter ? filter_keys<S>() + 128u : kWaveKeys;
-  __shared__ uint32_t sh_new[16], sh_flags[16], sh_dups[16];
+  enum : uint32_t { kNewStates, kFlags, kDups, kProbes, kMaxJ, kStored, kLookups, kFulls, kRows };
+  __shared__ uint32_t sh[kRows][16];
   __shared__ uint64_t sh_trans[16];
   __shared__ unsigned long long sh_base;
   const uint32_t wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
   const uint32_t lane = __lane_id();
   const uint64_t trans = wave_sum64(acc.trans);
   const uint32_t dups = kFilter ? wave_sum(acc.dups) : 0u;
+  uint32_t probes = 0, max_j = 0;
+  if constexpr (kStats) {
+    probes = wave_sum(acc.st.probes);
+    max_j = wave_max(acc.st.max_j);
+  }
   if (lane == 0) {
-    sh_new[wave] = acc.n_new;
-    sh_flags[wave] = acc.flags;
+    sh[kNewStates][wave] = acc.n_new;
+    sh[kFlags][wave] = acc.flags;
     sh_trans[wave] = trans;
-    if (kFilter) sh_dups[wave] = dups;
+    if (kFilter) sh[kDups][wave] = dups;
+    if constexpr (kStats) {
+      sh[kProbes][wave] = probes;
+      sh[kMaxJ][wave] = max_j;
+      sh[kStored][wave] = acc.st.stored;
+      sh[kLookups][wave] = acc.st.lookups;
+      sh[kFulls][wave] = acc.st.full;
+    }
   }
   __syncthreads();
   uint64_t before = 0;
@@ -433,10 +466,10 @@ __device__ __forceinline__ uint64_t finish_block(const WaveJob& j, const uint32_
     uint64_t t = 0, n = 0, d = 0;
     uint32_t f = 0;
     for (uint32_t w = 0; w < waves; ++w) {
-      n += sh_new[w];
-      f |= sh_flags[w];
+      n += sh[kNewStates][w];
+      f |= sh[kFlags][w];
       t += sh_trans[w];
-      if (kFilter) d += sh_dups[w];
+      if (kFilter) d += sh[kDups][w];
     }
     if (f) {
       // before the arrival: the last workgroup to arrive reads the flags
@@ -447,12 +480,33 @@ __device__ __forceinline__ uint64_t finish_block(const WaveJob& j, const uint32_
     if (d) atomicAdd(ctr_at(j.ctr, kCtrDups), static_cast<unsigned long long>(d));
     if (n + arrive) before = atomicAdd(ctr_at(j.ctr, j.tail), n + arrive);
     sh_base = before & kTailMask;
+    *n_new = n;
     if ((before & kTailMask) + n > j.cap_out)
       atomicOr(ctr_at(j.ctr, kCtrFlags), static_cast<unsigned long long>(kFlagFrontierOverflow));
   }
+  if constexpr (kStats) {
+    // (threads of the second wavefront, beside the first one's)
+    const uint32_t k = threadIdx.x - 64u;
+    if (k < 5 && j.t.counters != nullptr) {
+      const uint32_t row = k == 0 ? kStored : k == 1 ? kLookups : k == 2 ? kProbes
+                           : k == 3 ? kFulls : kMaxJ;
+      const uint32_t to = k == 4 ? kCntMaxJ : k;
+      uint64_t x = 0;
+      for (uint32_t w = 0; w < waves; ++w) {
+        const uint64_t y = sh[row][w];
+        x = k == 4 ? (y > x ? y : x) : x + y;
+      }
+      auto* c = reinterpret_cast<unsigned long long*>(
+          j.t.counters + static_cast<uint64_t>(blockIdx.x % j.t.ctr_slots) * kNumCounters + to);
+      if (x) {
+        if (k == 4) atomicMax(c, static_cast<unsigned long long>(x));
+        else atomicAdd(c, static_cast<unsigned long long>(x));
+      }
+    }
+  }
   __syncthreads();
   uint64_t base = sh_base;
-  for (uint32_t w = 0; w < wave; ++w) base += sh_new[w];
+  for (uint32_t w = 0; w < wave; ++w) base += sh[kNewStates][w];
   for (uint32_t k = lane; k < acc.n_new; k += 64) {
     if (base + k < j.cap_out) {
       uint32_t key[S];
@@ -463,6 +517,9 @@ __device__ __forceinline__ uint64_t finish_block(const WaveJob& j, const uint32_
   acc.n_new = 0;
   return before;
 }
+static_assert(kCntStored == 0 && kCntLookups == 1 && kCntProbes == 2 && kCntFull == 3 &&
+                  kCntMaxJ == 5,
+              "counter order");
 
 // ------------------------------------------------------- a level's kernel
 constexpr uint32_t kLevelBlock = 512;  // threads per workgroup
@@ -530,6 +587,11 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
   extern __shared__ __align__(16) uint32_t smem[];
   uint64_t n_in = a.n_in, first = a.first;
   uint32_t cur = a.cur;
+  // (the image's first words are on their way while the level's entry is read)
+  uint32_t head = 0;
+  if constexpr (!kGlobalImg) {
+    if (threadIdx.x < a.img_words) head = a.img[threadIdx.x];
+  }
   if (a.ctl != nullptr) {
     if (a.link > 0) {
       const LevelCtl::Entry& e = a.ctl->entry[a.link & 1u];
@@ -549,19 +611,11 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
   const uint64_t n_tiles = (n_in + per - 1) / per;
   const uint64_t groups = min(static_cast<uint64_t>(gridDim.x), (n_tiles + kWaves - 1) / kWaves);
   if (blockIdx.x >= groups) return;
-  const uint32_t* img;
-  if constexpr (kGlobalImg) {
-    img = a.img;
-  } else {
-    for (uint32_t k = threadIdx.x; k < a.img_words; k += kLevelBlock) smem[k] = a.img[k];
-    img = smem;
-  }
-  __syncthreads();
   const uint32_t wave = threadIdx.x >> 6;
   uint32_t* lds = smem + a.img_stride + wave * wave_words<S, kFilter>();
   WaveJob j;
   j.t = a.t;
-  j.img = img;
+  j.img = kGlobalImg ? a.img : smem;
   j.frontier_in = a.f[cur] + first * S;
   j.n_in = n_in;
   j.frontier_out = a.f[cur ^ 1u];
@@ -575,15 +629,23 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
   j.tail = a.tail;
   WaveAcc acc;
   // neighbouring workgroups take neighbouring tiles at the same time
-  expand_tiles<S, B, kFilter>(j, lds, static_cast<uint64_t>(blockIdx.x) + wave * groups, n_tiles,
-                              groups * kWaves, qs, acc);
-  const uint64_t before =
-      finish_block<S, kFilter>(j, lds, acc, a.ctl != nullptr ? uint64_t(1) << kArriveShift : 0);
+  const uint64_t tile0 = static_cast<uint64_t>(blockIdx.x) + wave * groups;
+  uint32_t sw[S];
+  load_tile<S>(j, tile0, qs, sw);
+  if constexpr (!kGlobalImg) {
+    if (threadIdx.x < a.img_words) smem[threadIdx.x] = head;
+    for (uint32_t k = threadIdx.x + kLevelBlock; k < a.img_words; k += kLevelBlock)
+      smem[k] = a.img[k];
+  }
+  __syncthreads();
+  expand_tiles<S, B, kFilter>(j, lds, tile0, n_tiles, groups * kWaves, qs, sw, acc);
+  uint64_t n_new = 0;
+  const uint64_t before = finish_block<S, kFilter, true>(
+      j, lds, acc, a.ctl != nullptr ? uint64_t(1) << kArriveShift : 0, &n_new);
   if (a.ctl != nullptr && threadIdx.x == 0 && (before >> kArriveShift) + 1 == groups) {
     // every workgroup has arrived: the level's NEW states are all counted
     auto* tail = ctr_at(a.ctr, a.tail);
-    const uint64_t n_next =
-        __hip_atomic_load(tail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kTailMask;
+    const uint64_t n_next = (before & kTailMask) + n_new;
     __hip_atomic_store(tail, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint64_t flags = __hip_atomic_load(ctr_at(a.ctr, kCtrFlags), __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
@@ -604,7 +666,6 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
                ? 1u
                : 0u;
   }
-  flush_stats_block(a.t, acc.st, nullptr);
 }
 
 template <int S, int B, bool kFilter, bool kGlobalImg>

@@ -73,8 +73,6 @@ __global__ __launch_bounds__(kStepBlock) void serve_step_kernel(ServeArgs a) {
     else hi = mid;
   }
   const ServeJob& jb = a.jobs[lo];
-  for (uint32_t k = threadIdx.x; k < jb.img_words; k += kStepBlock) img[k] = a.img[jb.img_off + k];
-  __syncthreads();
   WaveJob j;
   j.t = uniform_table(jb.t);
   j.img = img;
@@ -93,9 +91,15 @@ __global__ __launch_bounds__(kStepBlock) void serve_step_kernel(ServeArgs a) {
   const uint32_t qs = uniform32(jb.qs);
   const uint32_t per = 64u >> qs;
   const uint64_t n_tiles = (j.n_in + per - 1) / per;
-  const uint64_t tile = (group - jb.tile_begin) * (kStepBlock / 64) + (threadIdx.x >> 6);
-  expand_tiles<S, B, false>(j, lds, uniform64(tile), n_tiles, n_tiles, qs, acc);
-  (void)finish_block<S, false>(j, lds, acc, 0);
+  const uint64_t tile =
+      uniform64((group - jb.tile_begin) * (kStepBlock / 64) + (threadIdx.x >> 6));
+  uint32_t sw[S];
+  load_tile<S>(j, tile, qs, sw);
+  for (uint32_t k = threadIdx.x; k < jb.img_words; k += kStepBlock) img[k] = a.img[jb.img_off + k];
+  __syncthreads();
+  expand_tiles<S, B, false>(j, lds, tile, n_tiles, n_tiles, qs, sw, acc);
+  uint64_t n_new;
+  (void)finish_block<S, false, false>(j, lds, acc, 0, &n_new);
 }
 
 // (The probes are those of 4-lane subgroups whatever the jobs' own width.)

@@ -60,6 +60,20 @@ __device__ inline bool lds_set_insert(uint32_t* set, uint32_t mask, const uint32
                                       bool act) {
   bool done = !act, fresh = false;
   uint32_t h = dedup_hash<S>(key) & mask;
+  if constexpr (S == 1) {
+    // one-word entries: the compare-and-swap is the look too
+    while (__ballot(!done)) {
+      if (!done) {
+        uint32_t old = kEmpty;
+        fresh = __hip_atomic_compare_exchange_strong(set + h, &old, key[0], __ATOMIC_RELAXED,
+                                                     __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+        done = fresh || old == key[0];
+        h = (h + 1) & mask;
+      }
+    }
+    return fresh;
+  }
   while (__ballot(!done)) {
     if (!done) {
       uint32_t* e = set + h * S;
