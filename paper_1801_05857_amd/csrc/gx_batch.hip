@@ -1,13 +1,12 @@
 // Batched exploration (many networks explored together, each in its own table
 // partition) and the find-or-put autotuner.
 //
-// Two schedules.  Stepped (the default): every unfinished instance advances
-// one BFS level per step; a step is one multi-instance launch per kernel
-// class (the server's step kernel over the concatenated tiles of the class's
-// current levels), a summary kernel per class that copies each instance's
-// next-level size and flags into a compact array and clears its tail, and
-// one read-back of those arrays; gx_batch_run returns when every instance has
-// finished.  Persistent (with use_graph or persistent): one persistent launch
+// Two schedules.  Stepped (the default): every unfinished instance of a kernel
+// class advances one BFS level per step; a step is one multi-instance launch
+// (the server's step kernel over the concatenated levels) and an update
+// kernel that prepares the next one; classes run side by side, each with
+// strings of steps between read-backs; gx_batch_run returns when every
+// instance has finished.  Persistent (with use_graph or persistent): one persistent launch
 // per class pulls (instance, level, tile) work from a device queue with no
 // host involvement, so a whole run can be captured in a hipGraph.
 #include <hip/hip_runtime.h>
@@ -51,10 +50,13 @@ extern template hipError_t batch_init<4>(uint32_t, const BatchArgs&, hipStream_t
 // instantiated in gx_serve_s1.hip, gx_serve_s2.hip, gx_serve_s4.hip
 extern template hipError_t serve_launch<1>(uint32_t, const ServeArgs&, uint32_t, size_t,
                                            hipStream_t);
+extern template uint32_t step_blocks_per_cu<1>(uint32_t, size_t);
 extern template hipError_t serve_launch<2>(uint32_t, const ServeArgs&, uint32_t, size_t,
                                            hipStream_t);
+extern template uint32_t step_blocks_per_cu<2>(uint32_t, size_t);
 extern template hipError_t serve_launch<4>(uint32_t, const ServeArgs&, uint32_t, size_t,
                                            hipStream_t);
+extern template uint32_t step_blocks_per_cu<4>(uint32_t, size_t);
 
 namespace {
 
@@ -62,6 +64,11 @@ constexpr uint32_t kDefaultMaxLevels = 4096;
 constexpr uint64_t kSpinLimit = 1ull << 23;  // polls of one to two microseconds each
 
 uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
+
+// Bytes of a class's header, job descriptors and first groups.
+size_t step_bytes(uint32_t n_jobs) {
+  return sizeof(StepHdr) + n_jobs * (sizeof(ServeJob) + sizeof(uint32_t));
+}
 
 // ---------------------------------------------------------------- autotuner
 // Tables are tuned per size class: a table's size decides where most of its
@@ -100,17 +107,7 @@ __global__ void tune_keys_kernel(uint32_t* keys, uint32_t S, uint64_t n, uint64_
     keys[i * S + k] = static_cast<uint32_t>((k & 1) ? (x >> 33) : (x & 0x7FFFFFFFu)) ^ k;
 }
 
-// After a step of the stepped schedule: instance k's next-level size and
-// flags to sum[2k], sum[2k + 1]; its next-level tail cleared for the step
-// after.
-__global__ void batch_step_summary_kernel(BatchState* state, uint32_t n, uint64_t* sum) {
-  const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  uint64_t* c = state[k].ctr;
-  sum[2 * k] = c[kCtrTail * kCtrSpread];
-  sum[2 * k + 1] = c[kCtrFlags * kCtrSpread];
-  c[kCtrTail * kCtrSpread] = 0;
-}
+constexpr uint32_t kSteps = 16;  // steps of a class between read-backs
 
 }  // namespace
 }  // namespace gx
@@ -144,12 +141,14 @@ struct gx_batch {
     size_t lds = 0;
     hipStream_t side = nullptr;
     hipEvent_t ev_done = nullptr;
-    // stepped schedule: job descriptors (device, pinned staging) and the
-    // per-step summary (device, pinned read-back), nc entries each
-    gx::ServeJob* d_jobs = nullptr;
-    gx::ServeJob* h_jobs = nullptr;
-    uint64_t* d_sum = nullptr;
-    uint64_t* h_sum = nullptr;
+    // stepped schedule: header, job descriptors and first groups (device,
+    // pinned staging) and what every step of a string leaves per instance
+    // (device, pinned read-back)
+    char* d_step = nullptr;
+    char* h_step = nullptr;
+    gx::StepOut* d_out = nullptr;
+    gx::StepOut* h_out = nullptr;
+    uint32_t resident = 0;  // step workgroups the device holds at once
   };
   int device = 0;
   uint32_t n = 0;
@@ -194,10 +193,10 @@ void free_batch(gx_batch* b) {
       if (p) (void)hipFree(p);
     if (c.side) (void)hipStreamDestroy(c.side);
     if (c.ev_done) (void)hipEventDestroy(c.ev_done);
-    if (c.d_jobs) (void)hipFree(c.d_jobs);
-    if (c.d_sum) (void)hipFree(c.d_sum);
-    if (c.h_jobs) (void)hipHostFree(c.h_jobs);
-    if (c.h_sum) (void)hipHostFree(c.h_sum);
+    if (c.d_step) (void)hipFree(c.d_step);
+    if (c.d_out) (void)hipFree(c.d_out);
+    if (c.h_step) (void)hipHostFree(c.h_step);
+    if (c.h_out) (void)hipHostFree(c.h_out);
   }
   if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
   if (b->hc) (void)hipFree(b->hc);
@@ -295,106 +294,135 @@ gx_status run_stepped(gx_batch* b, hipStream_t stream) {
     }
     if (e != hipSuccess) return GX_EDEVICE;
   }
-  while (true) {
-    bool any = false;
-    // the classes' launches of a step run side by side, each on its own
-    // stream, forked from and joined to `stream`
-    if (hipEventRecord(b->ev_fork, stream) != hipSuccess) return GX_EDEVICE;
-    for (size_t ci = 0; ci < nk; ++ci) {
-      gx_batch::Class& c = b->classes[ci];
-      const uint32_t nc = static_cast<uint32_t>(c.members.size());
-      uint32_t n_jobs = 0;
-      uint64_t tiles = 0, states = 0;
-      for (uint32_t k = 0; k < nc; ++k)
-        if (live[ci][k]) states += n_in[ci][k];
-      const uint32_t qs = step_lanes(states, cus);
-      for (uint32_t k = 0; k < nc; ++k) {
-        if (!live[ci][k]) continue;
-        // the descriptor from the instance's static part (BatchInst, mirrored
-        // on the host at creation) and its current level
-        ServeJob& x = c.h_jobs[n_jobs++];
-        const BatchInst& in = c.h_inst[k];
-        x.t = in.t;
-        x.img_off = in.img_off;
-        x.img_words = in.img_words;
-        x.frontier_in = in.f[cur[ci][k]];
-        x.n_in = n_in[ci][k];
-        x.frontier_out = in.f[cur[ci][k] ^ 1];
-        x.cap_out = in.cap;
-        x.dead = c.dead;
-        x.dead_cap = c.dead_cap;
-        x.ctr = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(c.state) +
-                                            k * sizeof(BatchState) + offsetof(BatchState, ctr));
-        x.tile_begin = tiles;
-        x.dead_ctr = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(c.g) +
-                                                 offsetof(BatchGlobal, dead_used));
-        x.dead_tag = c.dead_tag;
-        x.tag = k;
-        x.qs = qs;
-        tiles += step_groups(n_in[ci][k], qs);
-      }
-      if (n_jobs == 0) continue;
-      any = true;
-      if (tiles > 0x7FFFFFFFull) return GX_EINVAL;
-      ServeArgs sa;
-      sa.jobs = c.d_jobs;
-      sa.n_jobs = n_jobs;
-      sa.img = c.img;
-      sa.img_stride = c.img_stride;
-      const hipStream_t cs = c.side;
-      hipError_t e = hipStreamWaitEvent(cs, b->ev_fork, 0);
-      if (e == hipSuccess)
-        e = hipMemcpyAsync(c.d_jobs, c.h_jobs, n_jobs * sizeof(ServeJob), hipMemcpyHostToDevice,
-                           cs);
-      if (e == hipSuccess) {
-        const uint32_t grid = static_cast<uint32_t>(tiles);
-        switch (c.S) {
-          case 1: e = serve_launch<1>(c.B, sa, grid, c.lds, cs); break;
-          case 2: e = serve_launch<2>(c.B, sa, grid, c.lds, cs); break;
-          default: e = serve_launch<4>(c.B, sa, grid, c.lds, cs); break;
-        }
-      }
-      if (e == hipSuccess) {
-        hipLaunchKernelGGL(batch_step_summary_kernel, dim3((nc + 255) / 256), dim3(256), 0, cs,
-                           c.state, nc, c.d_sum);
-        e = hipGetLastError();
-      }
-      if (e == hipSuccess)
-        e = hipMemcpyAsync(c.h_sum, c.d_sum, 2ull * nc * sizeof(uint64_t), hipMemcpyDeviceToHost,
-                           cs);
-      if (e == hipSuccess) e = hipEventRecord(c.ev_done, cs);
-      if (e == hipSuccess) e = hipStreamWaitEvent(stream, c.ev_done, 0);
-      if (e != hipSuccess) return GX_EDEVICE;
+  // every class on its own stream, after the work queued on `stream`
+  if (hipEventRecord(b->ev_fork, stream) != hipSuccess) return GX_EDEVICE;
+  std::vector<uint64_t> states(nk, 0);
+  for (size_t ci = 0; ci < nk; ++ci) {
+    if (hipStreamWaitEvent(b->classes[ci].side, b->ev_fork, 0) != hipSuccess) return GX_EDEVICE;
+    states[ci] = b->classes[ci].members.size();
+  }
+  // Uploads the class's jobs and enqueues a string of steps and its read-back.
+  auto enqueue = [&](size_t ci) -> hipError_t {
+    gx_batch::Class& c = b->classes[ci];
+    const uint32_t nc = static_cast<uint32_t>(c.members.size());
+    StepHdr* hdr = reinterpret_cast<StepHdr*>(c.h_step);
+    ServeJob* jobs = reinterpret_cast<ServeJob*>(c.h_step + sizeof(StepHdr));
+    uint32_t* begin = reinterpret_cast<uint32_t*>(jobs + nc);
+    const uint32_t qs = step_lanes(states[ci], cus);
+    uint64_t total = 0;
+    for (uint32_t k = 0; k < nc; ++k) {
+      // the descriptor from the instance's static part (BatchInst, mirrored
+      // on the host at creation) and its current level
+      ServeJob& x = jobs[k];
+      const BatchInst& in = c.h_inst[k];
+      x.t = in.t;
+      x.img_off = in.img_off;
+      x.img_words = in.img_words;
+      x.f[0] = in.f[0];
+      x.f[1] = in.f[1];
+      x.n_in = live[ci][k] ? n_in[ci][k] : 0;
+      x.cap_out = in.cap;
+      x.dead = c.dead;
+      x.dead_cap = c.dead_cap;
+      x.ctr = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(c.state) +
+                                          k * sizeof(BatchState) + offsetof(BatchState, ctr));
+      x.dead_ctr = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(c.g) +
+                                               offsetof(BatchGlobal, dead_used));
+      x.dead_tag = c.dead_tag;
+      x.tag = k;
+      x.cur = cur[ci][k];
+      const uint64_t found = b->step_levels[c.members[k]].size();
+      x.levels_left = static_cast<uint32_t>(b->max_levels - std::min<uint64_t>(found, b->max_levels));
+      x.pad = 0;
+      begin[k] = static_cast<uint32_t>(total);
+      total += step_groups(x.n_in, qs);
     }
-    if (!any) break;
-    // one synchronisation per step (every class joined `stream`): the staged
-    // descriptors of this step are reused only after it
-    if (hipStreamSynchronize(stream) != hipSuccess) return GX_EDEVICE;
-    for (size_t ci = 0; ci < nk; ++ci) {
+    if (total > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    hdr->total = static_cast<uint32_t>(total);
+    hdr->qs = qs;
+    hdr->steps = 0;
+    hdr->halt = 0;
+    ServeArgs sa;
+    ServeJob* d_jobs = reinterpret_cast<ServeJob*>(c.d_step + sizeof(StepHdr));
+    uint32_t* d_begin = reinterpret_cast<uint32_t*>(d_jobs + nc);
+    StepHdr* d_hdr = reinterpret_cast<StepHdr*>(c.d_step);
+    sa.jobs = d_jobs;
+    sa.begin = d_begin;
+    sa.n_jobs = nc;
+    sa.hdr = d_hdr;
+    sa.img = c.img;
+    sa.img_stride = c.img_stride;
+    // the class's share of the device, a little more than its states' of all:
+    // workgroups that hold the whole device would keep the others out for a
+    // step
+    uint64_t all = 0;
+    for (uint64_t x : states) all += x;
+    const double share = all ? static_cast<double>(states[ci]) / static_cast<double>(all) : 1.0;
+    const uint32_t grid = std::min<uint32_t>(
+        c.resident, std::max<uint32_t>(cus, static_cast<uint32_t>(c.resident * (share * 1.2))));
+    hipError_t e = hipMemcpyAsync(c.d_step, c.h_step, step_bytes(nc), hipMemcpyHostToDevice, c.side);
+    for (uint32_t k = 0; k < kSteps && e == hipSuccess; ++k) {
+      switch (c.S) {
+        case 1: e = serve_launch<1>(c.B, sa, grid, c.lds, c.side); break;
+        case 2: e = serve_launch<2>(c.B, sa, grid, c.lds, c.side); break;
+        default: e = serve_launch<4>(c.B, sa, grid, c.lds, c.side); break;
+      }
+      if (e != hipSuccess) break;
+      hipLaunchKernelGGL(step_update_kernel, dim3(1), dim3(1024), 0, c.side, d_jobs, d_begin, nc,
+                         d_hdr, c.d_out + static_cast<uint64_t>(k) * nc, cus, ~uint64_t(0));
+      e = hipGetLastError();
+    }
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(c.h_out, c.d_out, sizeof(StepOut) * kSteps * nc, hipMemcpyDeviceToHost,
+                         c.side);
+    if (e == hipSuccess) e = hipEventRecord(c.ev_done, c.side);
+    return e;
+  };
+  bool ok = true;
+  for (size_t ci = 0; ci < nk; ++ci) ok = ok && enqueue(ci) == hipSuccess;
+  bool any = true;
+  while (any && ok) {
+    any = false;
+    for (size_t ci = 0; ci < nk && ok; ++ci) {
       gx_batch::Class& c = b->classes[ci];
       const uint32_t nc = static_cast<uint32_t>(c.members.size());
+      if (states[ci] == 0) continue;
+      if (hipEventSynchronize(c.ev_done) != hipSuccess) {
+        ok = false;
+        break;
+      }
+      states[ci] = 0;
       for (uint32_t k = 0; k < nc; ++k) {
-        if (!live[ci][k]) continue;
         const uint32_t i = c.members[k];
-        const uint64_t n_next = c.h_sum[2 * k], flags = c.h_sum[2 * k + 1];
         std::vector<uint64_t>& L = b->step_levels[i];
-        gx_status st = GX_OK;
-        bool done = true;
-        if (flags & kFlagTableFull) st = GX_ETABLEFULL;
-        else if (flags) st = GX_ENOMEM;
-        else if (n_next == 0) st = GX_OK;
-        else if (L.size() >= b->max_levels) st = GX_ENOMEM;  // deeper than max_levels
-        else done = false;
-        if (done) {
-          live[ci][k] = 0;
-          b->step_status[i] = st;
-        } else {
-          L.push_back(n_next);
-          n_in[ci][k] = n_next;
-          cur[ci][k] ^= 1;
+        for (uint32_t step = 0; step < kSteps && live[ci][k]; ++step) {
+          const StepOut& o = c.h_out[static_cast<uint64_t>(step) * nc + k];
+          gx_status st = GX_OK;
+          bool done = true;
+          if (o.flags & kFlagTableFull) st = GX_ETABLEFULL;
+          else if (o.flags) st = GX_ENOMEM;
+          else if (o.n_next == 0) st = GX_OK;
+          else if (L.size() >= b->max_levels) st = GX_ENOMEM;  // deeper than max_levels
+          else done = false;
+          if (done) {
+            live[ci][k] = 0;
+            b->step_status[i] = st;
+          } else {
+            L.push_back(o.n_next);
+            n_in[ci][k] = o.n_next;
+            cur[ci][k] ^= 1;
+          }
         }
+        if (live[ci][k]) states[ci] += n_in[ci][k];
       }
+      if (states[ci] == 0) continue;
+      any = true;
+      ok = enqueue(ci) == hipSuccess;
     }
+  }
+  if (!ok) {
+    for (auto& c : b->classes) (void)hipStreamSynchronize(c.side);
+    return GX_EDEVICE;
   }
   return GX_OK;
 }
@@ -691,10 +719,11 @@ gx_status gx_batch_create(const gx_network* nets, uint32_t n, const gx_batch_opt
         gx::dmalloc(&c.state_init, nc) != hipSuccess ||
         (!b->stepped && (gx::dmalloc(&c.queue, c.queue_cap) != hipSuccess ||
                          gx::dmalloc(&c.queue_init, nc) != hipSuccess)) ||
-        (b->stepped && (gx::dmalloc(&c.d_jobs, nc) != hipSuccess ||
-                        gx::dmalloc(&c.d_sum, 2ull * nc) != hipSuccess ||
-                        hipHostMalloc(&c.h_jobs, nc * sizeof(gx::ServeJob)) != hipSuccess ||
-                        hipHostMalloc(&c.h_sum, 2ull * nc * sizeof(uint64_t)) != hipSuccess)) ||
+        (b->stepped &&
+         (gx::dmalloc(&c.d_step, gx::step_bytes(nc)) != hipSuccess ||
+          gx::dmalloc(&c.d_out, static_cast<uint64_t>(gx::kSteps) * nc) != hipSuccess ||
+          hipHostMalloc(&c.h_step, gx::step_bytes(nc)) != hipSuccess ||
+          hipHostMalloc(&c.h_out, sizeof(gx::StepOut) * gx::kSteps * nc) != hipSuccess)) ||
         gx::dmalloc(&c.g, 1) != hipSuccess ||
         gx::dmalloc(&c.g_init, 1) != hipSuccess || gx::dmalloc(&c.img, imgw) != hipSuccess ||
         gx::dmalloc(&c.init_states, static_cast<uint64_t>(nc) * S) != hipSuccess ||
@@ -761,6 +790,12 @@ gx_status gx_batch_create(const gx_network* nets, uint32_t n, const gx_batch_opt
     }
     c.h_inst = std::move(hi);
     c.lds = gx::step_lds(S, c.img_stride);
+    switch (S) {
+      case 1: c.resident = gx::step_blocks_per_cu<1>(c.B, c.lds); break;
+      case 2: c.resident = gx::step_blocks_per_cu<2>(c.B, c.lds); break;
+      default: c.resident = gx::step_blocks_per_cu<4>(c.B, c.lds); break;
+    }
+    c.resident *= static_cast<uint32_t>(cus);
     int per_cu = 1;
     switch (S) {
       case 1: per_cu = gx::batch_resident<1>(c.B, c.lds); break;

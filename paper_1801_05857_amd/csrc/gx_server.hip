@@ -36,10 +36,19 @@ gx_status compile_network_image(const gx_network* net, std::vector<uint32_t>* im
 // instantiated in gx_serve_s1.hip, gx_serve_s2.hip and gx_serve_s4.hip
 extern template hipError_t serve_launch<1>(uint32_t, const ServeArgs&, uint32_t, size_t,
                                            hipStream_t);
+extern template hipError_t admit_launch<1>(uint32_t, const TableDev&, const uint32_t*, uint32_t*,
+                                            uint64_t*, uint32_t, hipStream_t);
+extern template uint32_t step_blocks_per_cu<1>(uint32_t, size_t);
 extern template hipError_t serve_launch<2>(uint32_t, const ServeArgs&, uint32_t, size_t,
                                            hipStream_t);
+extern template hipError_t admit_launch<2>(uint32_t, const TableDev&, const uint32_t*, uint32_t*,
+                                            uint64_t*, uint32_t, hipStream_t);
+extern template uint32_t step_blocks_per_cu<2>(uint32_t, size_t);
 extern template hipError_t serve_launch<4>(uint32_t, const ServeArgs&, uint32_t, size_t,
                                            hipStream_t);
+extern template hipError_t admit_launch<4>(uint32_t, const TableDev&, const uint32_t*, uint32_t*,
+                                            uint64_t*, uint32_t, hipStream_t);
+extern template uint32_t step_blocks_per_cu<4>(uint32_t, size_t);
 
 namespace {
 
@@ -68,9 +77,20 @@ uint64_t pow2_at_least(uint64_t x) {
 }
 
 
-// Device words a job's small state takes: table counters, the initial key
-// and its status byte.
-constexpr uint64_t kSlotSmallBytes = 128;
+// What goes up when a job is admitted, one copy: its initial state's slot and
+// its network image (a region per job slot on the device).  Pinned staging has
+// kStageSlots regions, used in turn: the copies of one round of admissions are
+// done before the next (its steps' read-back follows them), and a round that
+// admits more waits for them.
+constexpr uint64_t kSlotWords = 4 + kImgStoreWords;
+constexpr uint32_t kStageSlots = 64;
+
+// Steps between read-backs: while the jobs' levels are small a read-back costs
+// as much as a step, and a request that arrives meanwhile waits for a few
+// short steps; once they hold kLargeLevels states in all, steps are long and
+// every one is followed by a read-back.
+constexpr uint32_t kSteps = 8;
+constexpr uint64_t kLargeLevels = 1u << 20;
 
 }  // namespace
 }  // namespace gx
@@ -110,17 +130,29 @@ struct gx_server {
   gx::Buddy buddy;
   uint64_t a0 = 0, c0 = 0;  // first hash constant pair (host copy)
   uint64_t* d_hc = nullptr;
-  char* d_small = nullptr;
   gx_server_stats stats{};
   // owned by the step thread
   gx::SortSpace sort;
   std::vector<Job> active;
   std::vector<uint32_t> free_slots;
-  gx::ServeJob* d_jobs = nullptr;
-  uint32_t* d_img = nullptr;
+  // per job slot: initial state and image (device, pinned staging), counters
+  uint32_t* d_slot = nullptr;
+  uint32_t* h_slot = nullptr;
   uint64_t* d_ctr = nullptr;
-  uint64_t* h_ctr = nullptr;   // pinned host copy of d_ctr (per-step read-back)
-  gx::ServeJob* h_jobs = nullptr;  // pinned staging of the step's job descriptors
+  uint64_t* h_ctr = nullptr;   // pinned host copy of d_ctr
+  // per slot width: its steps' stream, descriptors and what they leave, as
+  // the batch's classes
+  struct Lane {
+    hipStream_t stream = nullptr;
+    hipEvent_t done = nullptr;
+    char* d_step = nullptr;
+    char* h_step = nullptr;
+    gx::StepOut* d_out = nullptr;
+    gx::StepOut* h_out = nullptr;
+    std::vector<size_t> jobs;  // the string's, by their place in `active`
+    uint32_t lds_for = 0, resident = 0;  // image stride the grid was sized for
+  } lanes[3];
+  hipEvent_t admitted = nullptr;
   std::thread th;
 };
 
@@ -145,10 +177,9 @@ void complete(gx_server* s, Request* r, gx_status st) {
 
 // A table over the arena block at `off` for w words and `slots` slots (a
 // power of two): the table, then the two frontiers and the deadlock buffer,
-// slots states each; counters, initial key and status in the job slot's
-// small state; the server's shared hash constants.  Nothing is allocated on
-// the device.  mu held.
-gx_table* job_table(gx_server* s, uint32_t w, uint64_t slots, uint64_t off, uint32_t slot) {
+// slots states each; the server's shared hash constants.  Nothing is
+// allocated on the device.  mu held.
+gx_table* job_table(gx_server* s, uint32_t w, uint64_t slots, uint64_t off) {
   const uint32_t S = slot_words(w);
   const uint32_t* c = s->cfg[S];
   gx_table* t = new (std::nothrow) gx_table;
@@ -166,13 +197,10 @@ gx_table* job_table(gx_server* s, uint32_t w, uint64_t slots, uint64_t off, uint
   t->c0 = s->c0;
   const uint64_t T = slots * S * sizeof(uint32_t);
   char* base = s->arena + off;
-  char* small = s->d_small + static_cast<uint64_t>(slot) * kSlotSmallBytes;
   t->words = reinterpret_cast<uint32_t*>(base);
   t->hc = s->d_hc;
   t->counters = nullptr;  // job tables keep no statistics
   t->ctr_slots = 1;
-  t->eb.key = reinterpret_cast<uint32_t*>(small + 64);
-  t->eb.status = reinterpret_cast<uint8_t*>(small + 96);
   for (int k = 0; k < 2; ++k) {
     t->eb.f[k] = reinterpret_cast<uint32_t*>(base + (k + 1) * T);
     t->eb.f_cap[k] = slots;
@@ -184,6 +212,7 @@ gx_table* job_table(gx_server* s, uint32_t w, uint64_t slots, uint64_t off, uint
 
 // Admit waiting requests while their reservations fit.  mu held.
 void admit(gx_server* s) {
+  uint32_t staged = 0;
   while (!s->waiting.empty() && !s->free_slots.empty()) {
     Request* r = s->waiting.front();
     const uint64_t slots = pow2_at_least(
@@ -198,7 +227,7 @@ void admit(gx_server* s) {
     const uint64_t off = s->buddy.alloc(need);
     if (off == ~0ull) break;  // wait for running jobs to finish
     const uint32_t slot = s->free_slots.back();
-    gx_table* t = job_table(s, r->w, slots, off, slot);
+    gx_table* t = job_table(s, r->w, slots, off);
     if (!t) {
       s->buddy.release(off, need);
       break;
@@ -213,22 +242,31 @@ void admit(gx_server* s) {
     s->free_slots.pop_back();
     s->reserved += need;
     s->stats.reserved_peak = std::max(s->stats.reserved_peak, s->reserved);
-    // reset the table, place the initial state, insert it
-    uint32_t init[4] = {0, 0, 0, 0};
-    for (uint32_t x = 0; x < r->w; ++x) init[x] = r->init[x];
-    bool ok = gx_table_clear(t, s->stream) == GX_OK &&
-              hipMemcpyAsync(t->eb.f[0], init, t->S * sizeof(uint32_t), hipMemcpyHostToDevice,
-                             s->stream) == hipSuccess &&
-              hipMemcpyAsync(t->eb.key, init, r->w * sizeof(uint32_t), hipMemcpyHostToDevice,
-                             s->stream) == hipSuccess &&
-              hipMemsetAsync(s->d_ctr + kSlotCtrWords * j.slot, 0, kSlotCtrWords * sizeof(uint64_t),
-                             s->stream) ==
-                  hipSuccess &&
-              launch_find_or_put(t, t->eb.key, 1, t->eb.status, nullptr, s->stream) == hipSuccess &&
-              hipMemcpyAsync(s->d_img + static_cast<uint64_t>(j.slot) * kImgStoreWords,
-                             r->img.data(), r->img.size() * sizeof(uint32_t),
-                             hipMemcpyHostToDevice, s->stream) == hipSuccess &&
-              hipStreamSynchronize(s->stream) == hipSuccess;
+    // reset the table, place the initial state, insert it: only enqueued (the
+    // job's first step comes after it on the device)
+    const uint64_t at = static_cast<uint64_t>(j.slot) * kSlotWords;
+    bool ok = true;
+    if (staged == kStageSlots) {
+      ok = hipStreamSynchronize(s->stream) == hipSuccess;
+      staged = 0;
+    }
+    uint32_t* up = s->h_slot + staged++ * kSlotWords;
+    for (uint32_t x = 0; x < 4; ++x) up[x] = x < r->w ? r->init[x] : 0u;
+    std::copy(r->img.begin(), r->img.end(), up + 4);
+    uint64_t* ctr = s->d_ctr + kSlotCtrWords * j.slot;
+    ok = ok && gx_table_clear(t, s->stream) == GX_OK &&
+         hipMemcpyAsync(s->d_slot + at, up, (4 + r->img.size()) * sizeof(uint32_t),
+                        hipMemcpyHostToDevice, s->stream) == hipSuccess;
+    if (ok) {
+      const uint32_t* key = s->d_slot + at;
+      hipError_t e;
+      switch (t->S) {
+        case 1: e = admit_launch<1>(t->B, t->dev(), key, t->eb.f[0], ctr, kSlotCtrWords, s->stream); break;
+        case 2: e = admit_launch<2>(t->B, t->dev(), key, t->eb.f[0], ctr, kSlotCtrWords, s->stream); break;
+        default: e = admit_launch<4>(t->B, t->dev(), key, t->eb.f[0], ctr, kSlotCtrWords, s->stream); break;
+      }
+      ok = e == hipSuccess;
+    }
     if (!ok) {
       s->reserved -= need;
       s->free_slots.push_back(j.slot);
@@ -313,8 +351,113 @@ void finish_job(gx_server* s, size_t k, gx_status st, uint64_t transitions, uint
   s->active.erase(s->active.begin() + k);
 }
 
+// Bytes of a class's header, job descriptors and first groups.
+size_t step_bytes(uint32_t n_jobs) {
+  return sizeof(StepHdr) + n_jobs * (sizeof(ServeJob) + sizeof(uint32_t));
+}
+
+// Enqueues a string of steps of the active jobs of slot width S on the
+// class's stream, after the admissions; *steps receives its length.
+hipError_t enqueue_steps(gx_server* s, uint32_t S, uint32_t cus, uint64_t all_states,
+                         uint32_t n_steps, bool* any) {
+  gx_server::Lane& ln = s->lanes[S == 1 ? 0 : S == 2 ? 1 : 2];
+  ln.jobs.clear();
+  uint64_t states = 0;
+  uint32_t img_max = 0;
+  for (size_t k = 0; k < s->active.size(); ++k) {
+    const gx_server::Job& j = s->active[k];
+    if (j.t->S != S) continue;
+    ln.jobs.push_back(k);
+    states += j.n_in;
+    img_max = std::max<uint32_t>(img_max, static_cast<uint32_t>(j.r->img.size()));
+  }
+  *any = !ln.jobs.empty();
+  if (!*any) return hipSuccess;
+  const uint32_t n = static_cast<uint32_t>(ln.jobs.size());
+  const uint32_t qs = step_lanes(states, cus);
+  StepHdr* hdr = reinterpret_cast<StepHdr*>(ln.h_step);
+  ServeJob* jobs = reinterpret_cast<ServeJob*>(ln.h_step + sizeof(StepHdr));
+  uint32_t* begin = reinterpret_cast<uint32_t*>(jobs + n);
+  uint64_t total = 0;
+  for (uint32_t k = 0; k < n; ++k) {
+    const gx_server::Job& j = s->active[ln.jobs[k]];
+    ServeJob& x = jobs[k];
+    x.t = j.t->dev();
+    x.img_off = static_cast<uint32_t>(j.slot * kSlotWords + 4);
+    x.img_words = static_cast<uint32_t>(j.r->img.size());
+    x.f[0] = j.t->eb.f[0];
+    x.f[1] = j.t->eb.f[1];
+    x.n_in = j.n_in;
+    x.cap_out = j.t->eb.f_cap[0];
+    x.dead = j.t->eb.dead;
+    x.dead_cap = j.t->eb.dead_cap;
+    x.ctr = s->d_ctr + kSlotCtrWords * j.slot;
+    x.dead_ctr = nullptr;
+    x.dead_tag = nullptr;
+    x.tag = 0;
+    x.cur = static_cast<uint32_t>(j.cur);
+    x.levels_left = 0xFFFFFFFFu;
+    x.pad = 0;
+    begin[k] = static_cast<uint32_t>(total);
+    total += step_groups(j.n_in, qs);
+  }
+  if (total > 0x7FFFFFFFull) return hipErrorInvalidValue;
+  hdr->total = static_cast<uint32_t>(total);
+  hdr->qs = qs;
+  hdr->steps = 0;
+  hdr->halt = 0;
+  ServeJob* d_jobs = reinterpret_cast<ServeJob*>(ln.d_step + sizeof(StepHdr));
+  uint32_t* d_begin = reinterpret_cast<uint32_t*>(d_jobs + n);
+  StepHdr* d_hdr = reinterpret_cast<StepHdr*>(ln.d_step);
+  ServeArgs a;
+  a.jobs = d_jobs;
+  a.begin = d_begin;
+  a.n_jobs = n;
+  a.hdr = d_hdr;
+  a.img = s->d_slot;
+  a.img_stride = (img_max + 3) & ~3u;
+  const size_t lds = step_lds(S, a.img_stride);
+  const uint32_t* c = s->cfg[S];
+  if (ln.resident == 0 || ln.lds_for != a.img_stride) {
+    switch (S) {
+      case 1: ln.resident = cus * step_blocks_per_cu<1>(c[0], lds); break;
+      case 2: ln.resident = cus * step_blocks_per_cu<2>(c[0], lds); break;
+      default: ln.resident = cus * step_blocks_per_cu<4>(c[0], lds); break;
+    }
+    ln.lds_for = a.img_stride;
+  }
+  // the class's share of the device, a little more than its states' of all:
+  // workgroups that hold the whole device would keep the others out for a step
+  const double share =
+      all_states ? static_cast<double>(states) / static_cast<double>(all_states) : 1.0;
+  const uint32_t grid = std::min<uint32_t>(
+      ln.resident, std::max<uint32_t>(cus, static_cast<uint32_t>(ln.resident * (share * 1.2))));
+  hipError_t e = hipStreamWaitEvent(ln.stream, s->admitted, 0);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(ln.d_step, ln.h_step, step_bytes(n), hipMemcpyHostToDevice, ln.stream);
+  for (uint32_t k = 0; k < n_steps && e == hipSuccess; ++k) {
+    switch (S) {
+      case 1: e = serve_launch<1>(c[0], a, grid, lds, ln.stream); break;
+      case 2: e = serve_launch<2>(c[0], a, grid, lds, ln.stream); break;
+      default: e = serve_launch<4>(c[0], a, grid, lds, ln.stream); break;
+    }
+    if (e != hipSuccess) break;
+    hipLaunchKernelGGL(step_update_kernel, dim3(1), dim3(1024), 0, ln.stream, d_jobs, d_begin, n,
+                       d_hdr, ln.d_out + static_cast<uint64_t>(k) * n, cus,
+                       n_steps > 1 ? kLargeLevels : ~uint64_t(0));
+    e = hipGetLastError();
+  }
+  // the header tells how many steps were done
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(ln.h_step, ln.d_step, sizeof(StepHdr), hipMemcpyDeviceToHost, ln.stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(ln.h_out, ln.d_out, sizeof(StepOut) * n_steps * n, hipMemcpyDeviceToHost,
+                       ln.stream);
+  if (e == hipSuccess) e = hipEventRecord(ln.done, ln.stream);
+  return e;
+}
+
 void step_loop(gx_server* s) {
-  std::vector<ServeJob> hjs[3];  // per slot-width class
   const uint32_t cus = resident_grid(s->device, 1);
   while (true) {
     {
@@ -328,100 +471,73 @@ void step_loop(gx_server* s) {
         continue;
       }
     }
-    // one step over every active job, per slot-width class
-    bool ok = true;
-    for (uint32_t S : {1u, 2u, 4u}) {
-      std::vector<ServeJob>& hj = hjs[S == 1 ? 0 : S == 2 ? 1 : 2];
-      hj.clear();
-      uint64_t tiles = 0, states = 0;
-      uint32_t img_max = 0;
-      for (auto& j : s->active)
-        if (j.t->S == S) states += j.n_in;
-      const uint32_t qs = step_lanes(states, cus);
-      for (auto& j : s->active) {
-        if (j.t->S != S) continue;
-        ServeJob x;
-        x.t = j.t->dev();
-        x.img_off = j.slot * kImgStoreWords;
-        x.img_words = static_cast<uint32_t>(j.r->img.size());
-        x.frontier_in = j.t->eb.f[j.cur];
-        x.n_in = j.n_in;
-        x.frontier_out = j.t->eb.f[j.cur ^ 1];
-        x.cap_out = j.t->eb.f_cap[j.cur ^ 1];
-        x.dead = j.t->eb.dead;
-        x.dead_cap = j.t->eb.dead_cap;
-        x.ctr = s->d_ctr + kSlotCtrWords * j.slot;
-        x.tile_begin = tiles;
-        x.dead_ctr = nullptr;
-        x.dead_tag = nullptr;
-        x.tag = 0;
-        x.qs = qs;
-        tiles += step_groups(j.n_in, qs);
-        img_max = std::max<uint32_t>(img_max, x.img_words);
-        hj.push_back(x);
-      }
-      if (hj.empty()) continue;
-      const uint32_t* c = s->cfg[S];
-      ServeArgs a;
-      a.jobs = s->d_jobs + (S == 1 ? 0 : S == 2 ? 1 : 2) * s->max_active;
-      a.n_jobs = static_cast<uint32_t>(hj.size());
-      a.img = s->d_img;
-      a.img_stride = (img_max + 3) & ~3u;
-      const size_t lds = step_lds(S, a.img_stride);
-      // staged in pinned memory (one region per class, reused only after the
-      // step's synchronisation) so the upload is a plain asynchronous copy
-      ServeJob* staged = s->h_jobs + (S == 1 ? 0 : S == 2 ? 1 : 2) * s->max_active;
-      std::copy(hj.begin(), hj.end(), staged);
-      hipError_t e = hipMemcpyAsync(const_cast<ServeJob*>(a.jobs), staged,
-                                    hj.size() * sizeof(ServeJob), hipMemcpyHostToDevice, s->stream);
-      if (e == hipSuccess) {
-        switch (S) {
-          case 1: e = serve_launch<1>(c[0], a, static_cast<uint32_t>(tiles), lds, s->stream); break;
-          case 2: e = serve_launch<2>(c[0], a, static_cast<uint32_t>(tiles), lds, s->stream); break;
-          default: e = serve_launch<4>(c[0], a, static_cast<uint32_t>(tiles), lds, s->stream); break;
+    // a string of steps over every active job, the slot widths side by side
+    uint64_t all = 0;
+    for (const auto& j : s->active) all += j.n_in;
+    const uint32_t n_steps = all >= kLargeLevels ? 1 : kSteps;
+    bool ok = hipEventRecord(s->admitted, s->stream) == hipSuccess;
+    bool any[3] = {false, false, false};
+    for (int i = 0; i < 3 && ok; ++i)
+      ok = enqueue_steps(s, i == 0 ? 1u : i == 1 ? 2u : 4u, cus, all, n_steps, &any[i]) ==
+           hipSuccess;
+    for (int i = 0; i < 3; ++i) {
+      if (!any[i]) continue;
+      if (ok) ok = hipEventSynchronize(s->lanes[i].done) == hipSuccess;
+      if (!ok) (void)hipStreamSynchronize(s->lanes[i].stream);
+    }
+    // what became of each job: its levels, and its end
+    struct End {
+      size_t k;
+      gx_status st;
+    };
+    std::vector<End> ends;
+    uint64_t most = 0;
+    if (ok) {
+      for (int i = 0; i < 3; ++i) {
+        if (!any[i]) continue;
+        gx_server::Lane& ln = s->lanes[i];
+        const uint32_t n = static_cast<uint32_t>(ln.jobs.size());
+        const uint32_t steps = reinterpret_cast<const StepHdr*>(ln.h_step)->steps;
+        most = std::max<uint64_t>(most, steps);
+        for (uint32_t k = 0; k < n; ++k) {
+          gx_server::Job& j = s->active[ln.jobs[k]];
+          for (uint32_t st = 0; st < steps; ++st) {
+            const StepOut& o = ln.h_out[static_cast<uint64_t>(st) * n + k];
+            if (o.flags == 0 && o.n_next != 0) {
+              j.levels.push_back(o.n_next);
+              j.n_in = o.n_next;
+              j.cur ^= 1;
+              continue;
+            }
+            ends.push_back({ln.jobs[k], o.flags & kFlagTableFull ? GX_ETABLEFULL
+                                        : o.flags                ? GX_ENOMEM
+                                                                 : GX_OK});
+            break;
+          }
         }
       }
-      if (e != hipSuccess) ok = false;
+      // the counters of the jobs that have ended
+      uint32_t n_slots = 0;
+      for (const End& x : ends) n_slots = std::max(n_slots, s->active[x.k].slot + 1);
+      if (n_slots &&
+          (hipMemcpyAsync(s->h_ctr, s->d_ctr, kSlotCtrWords * n_slots * sizeof(uint64_t),
+                          hipMemcpyDeviceToHost, s->stream) != hipSuccess ||
+           hipStreamSynchronize(s->stream) != hipSuccess))
+        ok = false;
     }
-    // one synchronisation per step: the classes' launches and the read-back
-    // of the counters of slots 0 .. the highest active one follow each other
-    // on the stream without host round trips
-    uint32_t n_slots = 0;
-    for (const auto& j : s->active) n_slots = std::max(n_slots, j.slot + 1);
-    if (hipMemcpyAsync(s->h_ctr, s->d_ctr, kSlotCtrWords * n_slots * sizeof(uint64_t),
-                       hipMemcpyDeviceToHost, s->stream) != hipSuccess ||
-        hipStreamSynchronize(s->stream) != hipSuccess)
-      ok = false;
-    const uint64_t* ctr = s->h_ctr;
     std::lock_guard<std::mutex> lock(s->mu);
-    ++s->stats.steps;
-    for (size_t k = s->active.size(); k-- > 0;) {
-      gx_server::Job& j = s->active[k];
-      if (!ok) {
-        finish_job(s, k, GX_EDEVICE, 0, 0);
-        continue;
-      }
-      const uint64_t* c = &ctr[kSlotCtrWords * j.slot];
-      const uint64_t flags = c[kCtrFlags * kCtrSpread], n_next = c[kCtrTail * kCtrSpread];
-      if (flags & kFlagTableFull) {
-        finish_job(s, k, GX_ETABLEFULL, 0, 0);
-      } else if (flags) {
-        finish_job(s, k, GX_ENOMEM, 0, 0);
-      } else if (n_next == 0) {
-        finish_job(s, k, GX_OK, c[kCtrTrans * kCtrSpread], c[kCtrDead * kCtrSpread]);
-      } else {
-        j.levels.push_back(n_next);
-        j.n_in = n_next;
-        j.cur ^= 1;
-      }
-    }
-    // clear the next-frontier tails of slots 0 .. n_slots - 1 in one strided
-    // fill (finished or idle slots included: admission clears a slot's
-    // counters anyway)
-    if (ok && n_slots &&
-        hipMemset2DAsync(s->d_ctr + kCtrTail * kCtrSpread, kSlotCtrWords * sizeof(uint64_t), 0,
-                         sizeof(uint64_t), n_slots, s->stream) != hipSuccess) {
+    s->stats.steps += std::max<uint64_t>(most, 1);
+    if (!ok) {
       for (size_t k = s->active.size(); k-- > 0;) finish_job(s, k, GX_EDEVICE, 0, 0);
+    } else {
+      std::sort(ends.begin(), ends.end(), [](const End& x, const End& y) { return x.k > y.k; });
+      for (const End& x : ends) {
+        const uint64_t* c = &s->h_ctr[kSlotCtrWords * s->active[x.k].slot];
+        if (x.st == GX_OK)
+          finish_job(s, x.k, GX_OK, c[kCtrTrans * kCtrSpread], c[kCtrDead * kCtrSpread]);
+        else
+          finish_job(s, x.k, x.st, 0, 0);
+      }
     }
     s->cv_done.notify_all();
   }
@@ -440,14 +556,21 @@ void destroy_server(gx_server* s) {
   (void)hipDeviceSynchronize();
   for (auto& j : s->active) delete j.t;
   for (auto& kv : s->reqs) gx_explore_result_free(&kv.second->result);
-  if (s->d_jobs) (void)hipFree(s->d_jobs);
-  if (s->d_img) (void)hipFree(s->d_img);
+  for (auto& ln : s->lanes) {
+    if (ln.d_step) (void)hipFree(ln.d_step);
+    if (ln.d_out) (void)hipFree(ln.d_out);
+    if (ln.h_step) (void)hipHostFree(ln.h_step);
+    if (ln.h_out) (void)hipHostFree(ln.h_out);
+    if (ln.done) (void)hipEventDestroy(ln.done);
+    if (ln.stream) (void)hipStreamDestroy(ln.stream);
+  }
+  if (s->admitted) (void)hipEventDestroy(s->admitted);
+  if (s->d_slot) (void)hipFree(s->d_slot);
+  if (s->h_slot) (void)hipHostFree(s->h_slot);
   if (s->d_ctr) (void)hipFree(s->d_ctr);
   if (s->h_ctr) (void)hipHostFree(s->h_ctr);
-  if (s->h_jobs) (void)hipHostFree(s->h_jobs);
   if (s->arena) (void)hipFree(s->arena);
   if (s->d_hc) (void)hipFree(s->d_hc);
-  if (s->d_small) (void)hipFree(s->d_small);
   if (s->stream) (void)hipStreamDestroy(s->stream);
   s->cv_done.notify_all();
   delete s;
@@ -509,20 +632,27 @@ gx_status gx_server_create(const gx_server_opts* opts, gx_server** out) {
   s->cfg[3][0] = s->cfg[4][0];
   s->cfg[3][1] = s->cfg[4][1];
   s->cfg[3][2] = s->cfg[4][2];
-  if (hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess ||
-      hipMalloc(&s->d_jobs, 3ull * s->max_active * sizeof(gx::ServeJob)) != hipSuccess ||
-      hipMalloc(&s->d_img, static_cast<uint64_t>(s->max_active) * gx::kImgStoreWords *
-                               sizeof(uint32_t)) != hipSuccess ||
-      hipMalloc(&s->d_ctr, gx::kSlotCtrWords * s->max_active * sizeof(uint64_t)) != hipSuccess ||
-      hipHostMalloc(&s->h_ctr, gx::kSlotCtrWords * s->max_active * sizeof(uint64_t)) !=
-          hipSuccess ||
-      hipHostMalloc(&s->h_jobs, 3ull * s->max_active * sizeof(gx::ServeJob)) != hipSuccess) {
+  bool made =
+      hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) == hipSuccess &&
+      hipEventCreateWithFlags(&s->admitted, hipEventDisableTiming) == hipSuccess &&
+      hipMalloc(&s->d_slot, s->max_active * gx::kSlotWords * sizeof(uint32_t)) == hipSuccess &&
+      hipHostMalloc(&s->h_slot, gx::kStageSlots * gx::kSlotWords * sizeof(uint32_t)) == hipSuccess &&
+      hipMalloc(&s->d_ctr, gx::kSlotCtrWords * s->max_active * sizeof(uint64_t)) == hipSuccess &&
+      hipHostMalloc(&s->h_ctr, gx::kSlotCtrWords * s->max_active * sizeof(uint64_t)) == hipSuccess;
+  for (auto& ln : s->lanes)
+    made = made && hipStreamCreateWithFlags(&ln.stream, hipStreamNonBlocking) == hipSuccess &&
+           hipEventCreateWithFlags(&ln.done, hipEventDisableTiming) == hipSuccess &&
+           hipMalloc(&ln.d_step, gx::step_bytes(s->max_active)) == hipSuccess &&
+           hipHostMalloc(&ln.h_step, gx::step_bytes(s->max_active)) == hipSuccess &&
+           hipMalloc(&ln.d_out, sizeof(gx::StepOut) * gx::kSteps * s->max_active) == hipSuccess &&
+           hipHostMalloc(&ln.h_out, sizeof(gx::StepOut) * gx::kSteps * s->max_active) == hipSuccess;
+  if (!made) {
     (void)hipGetLastError();
     gx::destroy_server(s);
     return GX_ENOMEM;
   }
-  // the arena (allocated once: admission allocates nothing), the hash
-  // constants every job table shares, and each job slot's small state
+  // the arena (allocated once: admission allocates nothing) and the hash
+  // constants every job table shares
   {
     const uint64_t arena_bytes = s->budget & ~((uint64_t(1) << gx::Buddy::kMinShift) - 1);
     std::vector<uint64_t> hc(2 * s->H);
@@ -530,8 +660,7 @@ gx_status gx_server_create(const gx_server_opts* opts, gx_server** out) {
     s->a0 = hc[0];
     s->c0 = hc[1];
     if (arena_bytes == 0 || hipMalloc(&s->arena, arena_bytes) != hipSuccess ||
-        hipMalloc(&s->d_hc, hc.size() * sizeof(uint64_t)) != hipSuccess ||
-        hipMalloc(&s->d_small, gx::kSlotSmallBytes * s->max_active) != hipSuccess) {
+        hipMalloc(&s->d_hc, hc.size() * sizeof(uint64_t)) != hipSuccess) {
       (void)hipGetLastError();
       gx::destroy_server(s);
       return GX_ENOMEM;
