@@ -58,7 +58,8 @@ struct NetImage {
   uint64_t table_words = 0;  // size of the transition tables, what the limits apply to
   std::vector<uint32_t> field;  // per process
   std::vector<uint32_t> initial;
-  uint64_t max_succ = 0;
+  uint64_t max_succ = 0;  // transitions a state can have at most
+  uint64_t max_out = 0;   // distinct successors formed for a state at most
 };
 
 namespace {
@@ -120,9 +121,12 @@ gx_status compile_network(const gx_network* net, NetImage* out,
   // process and every rule participant
   uint64_t table_words = 4 + 2ull * P + R;
   for (uint32_t r = 0; r < R; ++r) table_words += 1 + 2ull * parts[r].size();
-  // CSR of the targets selected by `keep` for process p: offsets, then targets
-  // shifted to p's field
-  auto emit_csr = [&](uint32_t p, auto keep, uint64_t* max_deg) -> uint32_t {
+  // Lists of the targets selected by `keep` for process p (see the image's
+  // layout): *max_deg receives the most transitions of a local state, *max_out
+  // the most targets listed.  drop_self: targets equal to the source are only
+  // counted.
+  auto emit_csr = [&](uint32_t p, auto keep, bool drop_self, uint64_t* max_deg,
+                      uint64_t* max_out) -> uint32_t {
     const gx_lts& l = net->procs[p];
     const uint32_t shift = (field[p] >> 8) & 0xFF;
     std::vector<uint32_t> start(static_cast<size_t>(l.n_states) + 1, 0);
@@ -133,41 +137,54 @@ gx_status compile_network(const gx_network* net, NetImage* out,
         ++n;
       }
     table_words += l.n_states + 1ull + n;
-    *max_deg = 0;
+    *max_deg = *max_out = 0;
     if (table_words > max_words || n == 0) return 0;
-    const uint32_t off_at = static_cast<uint32_t>(img.size());
-    const uint32_t first = off_at + l.n_states + 1;
-    img.resize(first + n);
     for (uint32_t s = 0; s < l.n_states; ++s) {
       *max_deg = std::max<uint64_t>(*max_deg, start[s + 1]);
       start[s + 1] += start[s];
     }
-    for (uint32_t s = 0; s <= l.n_states; ++s) img[off_at + s] = first + start[s];
+    std::vector<uint32_t> dst(n), at(start.begin(), start.end() - 1);
     for (uint32_t t = 0; t < l.n_trans; ++t)
-      if (keep(l.label[t])) img[first + start[l.src[t]]++] = l.dst[t] << shift;
+      if (keep(l.label[t])) dst[at[l.src[t]]++] = l.dst[t];
+    const uint32_t off_at = static_cast<uint32_t>(img.size());
+    img.resize(img.size() + l.n_states + 1);
+    for (uint32_t s = 0; s < l.n_states; ++s) {
+      const auto b = dst.begin() + start[s], e = dst.begin() + start[s + 1];
+      std::sort(b, e);
+      auto u = std::unique(b, e);
+      if (drop_self) u = std::remove(b, u, s);
+      const uint32_t listed = static_cast<uint32_t>(u - b), total = start[s + 1] - start[s];
+      img[off_at + s] = static_cast<uint32_t>(img.size()) | (listed != total ? kListCounted : 0u);
+      if (listed != total) img.push_back(total);
+      for (auto d = b; d != u; ++d) img.push_back(*d << shift);
+      *max_out = std::max<uint64_t>(*max_out, listed);
+    }
+    img[off_at + l.n_states] = static_cast<uint32_t>(img.size());
     return off_at;
   };
-  uint64_t max_succ = 0;
+  uint64_t max_succ = 0, max_out = 0;
   uint32_t n_items = 0;
   auto item = [&]() { return 4 + 4 * static_cast<size_t>(n_items); };
   for (uint32_t p = 0; p < P && table_words <= max_words; ++p) {
-    uint64_t md = 0;
-    const uint32_t at = emit_csr(p, [&](uint32_t a) { return !governed[p][a]; }, &md);
+    uint64_t md = 0, mo = 0;
+    const uint32_t at = emit_csr(p, [&](uint32_t a) { return !governed[p][a]; }, true, &md, &mo);
     if (md == 0) continue;
     img[item() + 2] = field[p];
     img[item() + 3] = at;
     ++n_items;
     max_succ += md;
+    max_out += mo;
   }
   for (uint32_t r = 0; r < R && table_words <= max_words; ++r) {
     const uint32_t np = static_cast<uint32_t>(parts[r].size());
-    uint64_t prod = 1;
+    uint64_t prod = 1, prod_out = 1;
     std::vector<uint32_t> at(np, 0);
     for (uint32_t i = 0; i < np && table_words <= max_words; ++i) {
       const uint32_t want = static_cast<uint32_t>(net->rules[size_t(r) * P + parts[r][i]]);
-      uint64_t md = 0;
-      at[i] = emit_csr(parts[r][i], [&](uint32_t a) { return a == want; }, &md);
+      uint64_t md = 0, mo = 0;
+      at[i] = emit_csr(parts[r][i], [&](uint32_t a) { return a == want; }, false, &md, &mo);
       prod = std::min<uint64_t>(prod * md, uint64_t(1) << 40);
+      prod_out = std::min<uint64_t>(prod_out * mo, uint64_t(1) << 40);
     }
     if (prod == 0) continue;  // never enabled
     img[item() + 2] = field[parts[r][np - 1]];
@@ -186,6 +203,7 @@ gx_status compile_network(const gx_network* net, NetImage* out,
     }
     ++n_items;
     max_succ += prod;
+    max_out += prod_out;
   }
   if (table_words > max_words) return GX_EINVAL;
   img[0] = n_items;
@@ -197,6 +215,7 @@ gx_status compile_network(const gx_network* net, NetImage* out,
   out->initial.resize(P);
   for (uint32_t p = 0; p < P; ++p) out->initial[p] = net->procs[p].initial;
   out->max_succ = max_succ;
+  out->max_out = max_out;
   return GX_OK;
 }
 
@@ -495,6 +514,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   const uint64_t max_dead = opts && opts->deadlock_capacity ? opts->deadlock_capacity : ~0ull;
   hipStream_t stream = opts ? static_cast<hipStream_t>(opts->hip_stream) : nullptr;
   const uint64_t max_succ = std::max<uint64_t>(1, ni.max_succ);
+  const uint64_t max_out = std::max<uint64_t>(1, ni.max_out);
 
   auto grow_buf = [&](uint32_t** p, uint64_t* cap, uint64_t need, uint64_t keep,
                       uint64_t limit) -> gx_status {
@@ -575,7 +595,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
         std::min<uint64_t>(eb.f_cap[0], eb.f_cap[1]),
         std::min<uint64_t>(eb.succ_cap, max_cap));
     small_limit = std::min<uint64_t>(
-        gx::kSmallMaxLevel, std::min<uint64_t>(room, gx::kSmallSuccBudget) / max_succ);
+        gx::kSmallMaxLevel, std::min<uint64_t>(room, gx::kSmallSuccBudget) / max_out);
   }
 
   uint32_t init[4] = {0, 0, 0, 0};
@@ -710,7 +730,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     sa.out = reinterpret_cast<gx::LevelCtl*>(eb.ctr + kCtrWords);
     sa.limit = small_limit;
     sa.init_key = eb.key;
-    sa.max_succ = static_cast<uint32_t>(max_succ);
+    sa.max_succ = static_cast<uint32_t>(max_out);
     sa.max_qs = max_qs;
     const size_t lds_limit = gx::lds_per_workgroup(t->device);
     hipError_t e = hipErrorInvalidValue;

@@ -21,11 +21,17 @@ namespace gx {
 //       participant of a two-party rule and the index of its offsets, or
 //       kItemGeneral and the index of a record (participants before the last,
 //       then per participant field, index of its offsets)
-//   offsets arrays: n_q + 1 entries each; entry l is the index of the first
-//                   target of local state l, entry l+1 one past its last
-//   target arrays:  target local states, shifted to their field's position
+//   offsets arrays: n_q + 1 entries each; entry l is the index of local state
+//                   l's list, entry l+1 one past its end
+//   lists:          distinct target local states, shifted to their field's
+//                   position; where that leaves out transitions (several to
+//                   one target; a process's own steps that change nothing,
+//                   whose successor is the state itself) the entry has
+//                   kListCounted set and the list begins with the number of
+//                   transitions it stands for
 // Items that no local state offers anything for are left out.
 constexpr uint32_t kItemGeneral = 0xFFFFFFFFu;
+constexpr uint32_t kListCounted = 0x80000000u;
 // A network whose transition tables take more than kImgMaxWords words (46
 // KiB) is read from global memory; an image that stays in LDS takes at most
 // kImgStoreWords (its items take up to that many words more).
@@ -109,6 +115,22 @@ __device__ __forceinline__ uint32_t lane_rank(uint64_t m) {
                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
 }
 
+// Local state l's list: its first target's index, its targets, the
+// transitions they stand for.
+struct TargetList {
+  uint32_t first, n, total;
+};
+__device__ __forceinline__ TargetList target_list(const uint32_t* img, uint32_t offsets,
+                                                  uint32_t l) {
+  const uint32_t e0 = img[offsets + l], e1 = img[offsets + l + 1];
+  TargetList t;
+  t.first = (e0 & ~kListCounted) + (e0 >> 31);
+  t.n = (e1 & ~kListCounted) - t.first;
+  t.total = t.n;
+  if (e0 >> 31) t.total = img[t.first - 1];
+  return t;
+}
+
 // The outer participants of an item's combination c written into mid.
 template <int S>
 __device__ __forceinline__ void put_outer(const uint32_t* img, const uint4& it,
@@ -122,10 +144,9 @@ __device__ __forceinline__ void put_outer(const uint32_t* img, const uint4& it,
   uint32_t rem = c;
   for (uint32_t i = 0; i < np; ++i) {
     const uint32_t f = img[it.y + 1 + 2 * i], ob = img[it.y + 2 + 2 * i];
-    const uint32_t l = get_field<S>(sw, f);
-    const uint32_t x0 = img[ob + l], n = img[ob + l + 1] - x0;
-    put_field<S>(mid, f, img[x0 + rem % n]);
-    rem /= n;
+    const TargetList t = target_list(img, ob, get_field<S>(sw, f));
+    put_field<S>(mid, f, img[t.first + rem % t.n]);
+    rem /= t.n;
   }
 }
 
@@ -139,8 +160,11 @@ __device__ __forceinline__ void put_outer(const uint32_t* img, const uint4& it,
 // ballot, so the wavefront never splits), and at each step the lanes that
 // form a successor take consecutive places.  Nothing is counted beforehand:
 // the walk stops at any point to have the staged successors taken and goes
-// on.  Must be reached by the whole wavefront; a lane without a state passes
-// has = false.  Returns this lane's successors.
+// on.  Several transitions to one successor form it once, and a step that
+// changes nothing forms none: at random targets among 6 local states, 3
+// transitions a state, that leaves 2.1 of 3 successors to look up.  Must be
+// reached by the whole wavefront; a lane without a state passes has = false.
+// Returns the number of this lane's transitions.
 template <int S, typename Sink>
 __device__ __forceinline__ uint32_t walk_items(const uint32_t* img, const uint32_t (&sw)[S],
                                                bool has, uint32_t sub, uint32_t q,
@@ -152,24 +176,26 @@ __device__ __forceinline__ uint32_t walk_items(const uint32_t* img, const uint32
     const uint32_t i = i0 + sub;
     const bool valid = has && i < n_items;
     const uint4 it = *reinterpret_cast<const uint4*>(img + 4 + 4 * (i < n_items ? i : 0));
-    const uint32_t l = get_field<S>(sw, it.z);
-    const uint32_t b0 = img[it.w + l];
-    uint32_t bend = img[it.w + l + 1];
-    uint32_t outer = 1, a0 = 0;
+    const TargetList in = target_list(img, it.w, get_field<S>(sw, it.z));
+    const uint32_t b0 = in.first;
+    uint32_t bend = in.first + in.n;
+    uint32_t outer = 1, a0 = 0, total = in.total;
     if (it.x == kItemGeneral) {
       const uint32_t np = img[it.y];
       for (uint32_t k = 0; k < np; ++k) {
         const uint32_t f = img[it.y + 1 + 2 * k], ob = img[it.y + 2 + 2 * k];
-        const uint32_t lk = get_field<S>(sw, f);
-        outer *= img[ob + lk + 1] - img[ob + lk];
+        const TargetList t = target_list(img, ob, get_field<S>(sw, f));
+        outer *= t.n;
+        total *= t.total;
       }
     } else if (it.x) {
-      const uint32_t la = get_field<S>(sw, it.x);
-      a0 = img[it.y + la];
-      outer = img[it.y + la + 1] - a0;
+      const TargetList t = target_list(img, it.y, get_field<S>(sw, it.x));
+      a0 = t.first;
+      outer = t.n;
+      total *= t.total;
     }
-    const uint32_t n = valid ? (bend - b0) * outer : 0u;
-    own += n;
+    const uint32_t n = valid ? in.n * outer : 0u;
+    own += valid ? total : 0u;
     if (n == 0) bend = b0;
     uint32_t mid[S];
 #pragma unroll
@@ -434,7 +460,7 @@ template <int S, bool kFilter, bool kStats>
 __device__ __forceinline__ uint64_t finish_block(const WaveJob& j, const uint32_t* lds,
                                                  WaveAcc& acc, uint64_t arrive, uint64_t* n_new) {
   constexpr uint32_t kTop = kFilter ? filter_keys<S>() + 128u : kWaveKeys;
-  enum : uint32_t { kNewStates, kFlags, kDups, kProbes, kMaxJ, kStored, kLookups, kFulls, kRows };
+  enum : uint32_t { kNewStates, kFlags, kDups, kProbes, kMaxJ, kStored, kFulls, kRows };
   __shared__ uint32_t sh[kRows][16];
   __shared__ uint64_t sh_trans[16];
   __shared__ unsigned long long sh_base;
@@ -456,7 +482,6 @@ __device__ __forceinline__ uint64_t finish_block(const WaveJob& j, const uint32_
       sh[kProbes][wave] = probes;
       sh[kMaxJ][wave] = max_j;
       sh[kStored][wave] = acc.st.stored;
-      sh[kLookups][wave] = acc.st.lookups;
       sh[kFulls][wave] = acc.st.full;
     }
   }
@@ -488,12 +513,13 @@ __device__ __forceinline__ uint64_t finish_block(const WaveJob& j, const uint32_
     // (threads of the second wavefront, beside the first one's)
     const uint32_t k = threadIdx.x - 64u;
     if (k < 5 && j.t.counters != nullptr) {
-      const uint32_t row = k == 0 ? kStored : k == 1 ? kLookups : k == 2 ? kProbes
-                           : k == 3 ? kFulls : kMaxJ;
+      // (every transition counts as a lookup, the ones known to find their
+      // state among them, but for what the filter dropped)
+      const uint32_t row = k == 0 ? kStored : k == 2 ? kProbes : k == 3 ? kFulls : kMaxJ;
       const uint32_t to = k == 4 ? kCntMaxJ : k;
       uint64_t x = 0;
       for (uint32_t w = 0; w < waves; ++w) {
-        const uint64_t y = sh[row][w];
+        const uint64_t y = k == 1 ? sh_trans[w] - (kFilter ? sh[kDups][w] : 0u) : sh[row][w];
         x = k == 4 ? (y > x ? y : x) : x + y;
       }
       auto* c = reinterpret_cast<unsigned long long*>(

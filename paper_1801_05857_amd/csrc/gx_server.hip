@@ -85,12 +85,15 @@ uint64_t pow2_at_least(uint64_t x) {
 constexpr uint64_t kSlotWords = 4 + kImgStoreWords;
 constexpr uint32_t kStageSlots = 64;
 
-// Steps between read-backs: while the jobs' levels are small a read-back costs
-// as much as a step, and a request that arrives meanwhile waits for a few
-// short steps; once they hold kLargeLevels states in all, steps are long and
-// every one is followed by a read-back.
+// Steps between read-backs, by the states of all jobs' levels: while levels
+// are small a read-back (about 85 us) costs as much as a step, and a request
+// that arrives meanwhile waits for a few short steps; from kLargeLevels on a
+// step takes milliseconds, and every one is followed by a read-back.
 constexpr uint32_t kSteps = 8;
-constexpr uint64_t kLargeLevels = 1u << 20;
+constexpr uint64_t kSmallLevels = 1u << 20, kLargeLevels = 1u << 23;
+uint32_t steps_for(uint64_t states) {
+  return states < kSmallLevels ? kSteps : states < kLargeLevels ? kSteps / 2 : 1;
+}
 
 }  // namespace
 }  // namespace gx
@@ -444,7 +447,9 @@ hipError_t enqueue_steps(gx_server* s, uint32_t S, uint32_t cus, uint64_t all_st
     if (e != hipSuccess) break;
     hipLaunchKernelGGL(step_update_kernel, dim3(1), dim3(1024), 0, ln.stream, d_jobs, d_begin, n,
                        d_hdr, ln.d_out + static_cast<uint64_t>(k) * n, cus,
-                       n_steps > 1 ? kLargeLevels : ~uint64_t(0));
+                       n_steps == 1      ? ~uint64_t(0)
+                       : n_steps == kSteps ? 2 * kSmallLevels
+                                           : 2 * kLargeLevels);
     e = hipGetLastError();
   }
   // the header tells how many steps were done
@@ -474,7 +479,7 @@ void step_loop(gx_server* s) {
     // a string of steps over every active job, the slot widths side by side
     uint64_t all = 0;
     for (const auto& j : s->active) all += j.n_in;
-    const uint32_t n_steps = all >= kLargeLevels ? 1 : kSteps;
+    const uint32_t n_steps = steps_for(all);
     bool ok = hipEventRecord(s->admitted, s->stream) == hipSuccess;
     bool any[3] = {false, false, false};
     for (int i = 0; i < 3 && ok; ++i)

@@ -36,7 +36,7 @@ struct SmallArgs {
   uint64_t limit;       // largest level this launch expands
   const uint32_t* init_key;  // the level-0 state
   uint32_t set_mask;    // entries of the LDS visited set, minus one (a power of two)
-  uint32_t max_succ;    // successors a state can have at most
+  uint32_t max_succ;    // distinct successors a state can form at most
   uint32_t max_qs;      // log2 of the most lanes a state is worth
 };
 
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(small_threads<S>()) void lds_levels_kernel(SmallArg
                   : 0u;
     }
   }
-  uint32_t trans = 0;  // this lane's
+  uint64_t trans = 0;  // this lane's
   while (true) {
     __syncthreads();
     if (!sh_go) break;
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(small_threads<S>()) void lds_levels_kernel(SmallArg
                   : 0u;
     }
   }
-  trans = wave_sum(trans);  // (a level's transitions fit the set: 64 levels' fit 32 bits)
+  trans = wave_sum64(trans);
   if (lane == 0 && trans) atomicAdd(&sh_trans, static_cast<unsigned long long>(trans));
   __syncthreads();
   // the current level becomes frontier buffer 0 (when the levels go on)

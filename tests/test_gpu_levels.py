@@ -141,3 +141,42 @@ def test_batches_of_uneven_levels(n):
                 assert st == gx.GX_OK
                 _same(got, w)
                 assert np.array_equal(got.states, w.visited)
+
+
+def _shared_targets(P, n, copies, rules):
+    """Cycles of n states whose steps are offered `copies` times, beside
+    self-loops; with rules, neighbours meet on labels offered several times,
+    to the same target, to the source and to another one."""
+    trans, rows = [], []
+    for p in range(P):
+        t = [(s, 0, (s + 1) % n) for s in range(n) for _ in range(copies)]
+        t += [(s, 0, s) for s in range(0, n, 2) for _ in range(copies + 1)]
+        if rules:
+            t += [(s, 1, d) for s in range(n) for d in (s, s, (s + 2) % n)]
+        trans.append(t)
+    if rules:
+        rows = [[1 if x in (p, (p + 1) % P) else -1 for x in range(P)] for p in range(P - 1)]
+        rows.append([1] * P)
+    return W._net([n] * P, [0] * P, trans, 2, np.asarray(rows or np.zeros((0, P)), np.int32),
+                  "shared_targets")
+
+
+@pytest.mark.parametrize("P,n,copies,rules", [(1, 2, 1, False), (1, 7, 40, False), (3, 9, 1, True),
+                                              (3, 9, 3, True), (4, 8, 2, True), (5, 6, 2, False),
+                                              (4, 17, 2, False)])
+@pytest.mark.parametrize("dedup", [False, True])
+def test_transitions_that_share_a_successor(P, n, copies, rules, dedup):
+    """Every transition counts, each successor is formed once; a state whose
+    steps all lead to itself is no deadlock."""
+    net = _shared_targets(P, n, copies, rules)
+    want = oracle.explore(net, want_visited=True)
+    with gx.Table(want.words, 16, max(64, 2 * want.n_states), max_hashes=64) as t:
+        got = gx.explore(net, t, local_dedup=dedup)
+        _same(got, want, t)
+        if dedup:
+            assert t.stats().lookups + got.local_duplicates == want.n_transitions + 1
+    with gx.Batch([net], [2 * want.n_states], bucket_words=16, subgroup=4, max_hashes=64) as b:
+        b.run()
+        (st, got), = b.results()
+        assert st == gx.GX_OK
+        _same(got, want)
