@@ -296,19 +296,32 @@ struct LaneStats {
   uint32_t probes = 0, max_j = 0;                            // per lane
 };
 
+// Sum and maximum over the wavefront, in every lane, by row shifts and
+// broadcasts (a butterfly of lane shuffles takes an LDS round trip a step).
+// Every lane of the wavefront must be active.
+template <int Ctrl, int Rows>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t x) {
+  return static_cast<uint32_t>(
+      __builtin_amdgcn_update_dpp(0, static_cast<int>(x), Ctrl, Rows, 0xf, false));
+}
 __device__ inline uint32_t wave_sum(uint32_t x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
-  return x;
+  x += dpp_or_zero<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8: a row's sum in its last lane
+  x += dpp_or_zero<0x112, 0xf>(x);
+  x += dpp_or_zero<0x114, 0xf>(x);
+  x += dpp_or_zero<0x118, 0xf>(x);
+  x += dpp_or_zero<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+  x += dpp_or_zero<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), 63));
 }
 
 __device__ inline uint32_t wave_max(uint32_t x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    uint32_t y = __shfl_xor(x, d, 64);
-    x = y > x ? y : x;
-  }
-  return x;
+  x = max(x, dpp_or_zero<0x111, 0xf>(x));
+  x = max(x, dpp_or_zero<0x112, 0xf>(x));
+  x = max(x, dpp_or_zero<0x114, 0xf>(x));
+  x = max(x, dpp_or_zero<0x118, 0xf>(x));
+  x = max(x, dpp_or_zero<0x142, 0xa>(x));
+  x = max(x, dpp_or_zero<0x143, 0xc>(x));
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), 63));
 }
 
 __device__ inline void flush_stats(const TableDev& t, const LaneStats& st, uint64_t* n_new) {

@@ -440,12 +440,10 @@ __device__ __forceinline__ void expand_tiles(const WaveJob& j, uint32_t* lds, ui
   if (cnt) take();
 }
 
+// (values below 2^50)
 __device__ inline uint64_t wave_sum64(uint64_t x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1)
-    x += (static_cast<uint64_t>(__shfl_xor(static_cast<uint32_t>(x >> 32), d, 64)) << 32) |
-         __shfl_xor(static_cast<uint32_t>(x), d, 64);
-  return x;
+  return wave_sum(static_cast<uint32_t>(x) & 0xFFFFFFu) +
+         (static_cast<uint64_t>(wave_sum(static_cast<uint32_t>(x >> 24))) << 24);
 }
 
 // The workgroup's wavefronts hand over what they hold: NEW states, transition
