@@ -252,56 +252,83 @@ void pack_host(const NetImage& ni, const uint32_t* local, uint32_t* out) {
 
 namespace {
 
-// Safety monitor: the states among states[0, n) whose monitor field f (word
-// | shift << 8 | width << 16) holds a local state marked in the bitmask
-// `bad` are counted in *ctr and, below cap, copied to out (S words each).
-// One atomic add per wavefront that finds any.
+// Safety monitor: the level just completed, states[0, n) of f[cur], searched
+// for states whose monitor field (word | shift << 8 | width << 16) holds a
+// local state marked in the bitmask `bad`.  They are counted in the kCtrViol
+// counter and, below cap, copied to out (S words each); the first one ever
+// leaves its level, plus one, in kCtrViolLevel.  With ctl (a string of levels,
+// see LevelCtl) the level is the one that launch `link` has left, if it left
+// one; `stop` then ends the string at a violation.  One atomic add per
+// workgroup and round that finds any.
+struct ScanArgs {
+  const uint32_t* f[2];
+  uint64_t n;
+  uint32_t cur;
+  uint32_t field;
+  const uint32_t* bad;
+  uint32_t* out;
+  uint64_t cap;
+  uint64_t* ctr;
+  uint64_t level;  // the level's number; in a string, its first level's
+  LevelCtl* ctl;
+  uint32_t link;
+  uint32_t stop;
+};
+
 template <int S>
-__global__ __launch_bounds__(256) void monitor_scan_kernel(const uint32_t* states, uint64_t n,
-                                                           uint32_t f, const uint32_t* bad,
-                                                           uint32_t* out, uint64_t cap,
-                                                           unsigned long long* ctr) {
-  const uint64_t stride = static_cast<uint64_t>(gridDim.x) * 256;
-  const uint64_t first = static_cast<uint64_t>(blockIdx.x) * 256 + (threadIdx.x & ~63u);
-  const int lane = __lane_id();
-  for (uint64_t base = first; base < n; base += stride) {  // wavefront-uniform
-    const uint64_t i = base + lane;
+__global__ __launch_bounds__(256) void monitor_scan_kernel(ScanArgs a) {
+  __shared__ uint32_t hits[4];
+  __shared__ unsigned long long sh_base;
+  uint64_t n = a.n, level = a.level;
+  uint32_t cur = a.cur;
+  LevelCtl::Entry* e = nullptr;
+  if (a.ctl != nullptr) {
+    e = &a.ctl->entry[(a.link & 1u) ^ 1u];
+    if (!e->fresh) return;
+    n = uniform64(e->n_in);
+    cur = uniform32(static_cast<uint32_t>(e->cur));
+    level = a.level + e->n_levels - 1;
+  }
+  const uint32_t wave = threadIdx.x >> 6, lane = __lane_id();
+  const uint32_t* states = a.f[cur];
+  for (uint64_t base = static_cast<uint64_t>(blockIdx.x) * 256; base < n;
+       base += static_cast<uint64_t>(gridDim.x) * 256) {
+    const uint64_t i = base + threadIdx.x;
     uint32_t sw[S] = {};
     bool hit = false;
     if (i < n) {
       load_slot<S>(states + i * S, sw);
-      const uint32_t l = get_field<S>(sw, f);
-      hit = (bad[l >> 5] >> (l & 31)) & 1u;
+      const uint32_t l = get_field<S>(sw, a.field);
+      hit = (a.bad[l >> 5] >> (l & 31)) & 1u;
     }
     const uint64_t m = __ballot(hit);
-    if (m == 0) continue;
-    unsigned long long k = 0;
-    if (lane == 0) k = atomicAdd(ctr, static_cast<unsigned long long>(__popcll(m)));
-    k = __shfl(k, 0, 64) + __popcll(m & ((1ull << lane) - 1ull));
-    if (hit && k < cap) store_slot<S>(out + k * S, sw);
+    if (lane == 0) hits[wave] = static_cast<uint32_t>(__popcll(m));
+    __syncthreads();
+    const uint32_t all = hits[0] + hits[1] + hits[2] + hits[3];
+    if (threadIdx.x == 0 && all) {
+      sh_base = atomicAdd(ctr_at(a.ctr, kCtrViol), static_cast<unsigned long long>(all));
+      if (sh_base == 0) a.ctr[kCtrViolLevel * kCtrSpread] = level + 1;
+      if (e != nullptr && a.stop) e->go = 0;
+    }
+    __syncthreads();
+    if (hit) {
+      uint64_t k = sh_base + lane_rank(m);
+      for (uint32_t w = 0; w < wave; ++w) k += hits[w];
+      if (k < a.cap) store_slot<S>(a.out + k * S, sw);
+    }
+    __syncthreads();  // hits and sh_base are rewritten by the next round
   }
 }
 
-hipError_t launch_monitor_scan(uint32_t S, const uint32_t* states, uint64_t n, uint32_t f,
-                               const uint32_t* bad, uint32_t* out, uint64_t cap, uint64_t* ctr,
-                               uint32_t cus, hipStream_t s) {
-  if (n == 0) return hipSuccess;
+hipError_t launch_monitor_scan(uint32_t S, const ScanArgs& a, uint32_t cus, hipStream_t s) {
+  if (a.ctl == nullptr && a.n == 0) return hipSuccess;
+  const uint64_t most = static_cast<uint64_t>(cus) * 4;
   const uint32_t grid =
-      static_cast<uint32_t>(std::min<uint64_t>((n + 255) / 256, static_cast<uint64_t>(cus) * 8));
-  auto* c = reinterpret_cast<unsigned long long*>(ctr);
+      static_cast<uint32_t>(a.ctl ? most : std::min<uint64_t>((a.n + 255) / 256, most));
   switch (S) {
-    case 1:
-      hipLaunchKernelGGL((monitor_scan_kernel<1>), dim3(grid), dim3(256), 0, s, states, n, f, bad,
-                         out, cap, c);
-      break;
-    case 2:
-      hipLaunchKernelGGL((monitor_scan_kernel<2>), dim3(grid), dim3(256), 0, s, states, n, f, bad,
-                         out, cap, c);
-      break;
-    default:
-      hipLaunchKernelGGL((monitor_scan_kernel<4>), dim3(grid), dim3(256), 0, s, states, n, f, bad,
-                         out, cap, c);
-      break;
+    case 1: hipLaunchKernelGGL(monitor_scan_kernel<1>, dim3(grid), dim3(256), 0, s, a); break;
+    case 2: hipLaunchKernelGGL(monitor_scan_kernel<2>, dim3(grid), dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL(monitor_scan_kernel<4>, dim3(grid), dim3(256), 0, s, a); break;
   }
   return hipGetLastError();
 }
@@ -661,13 +688,11 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
       }
       eb.mon_cap = mon_mask.size();
     }
-    if (!eb.viol_ctr && hipMalloc(&eb.viol_ctr, sizeof(uint64_t)) != hipSuccess) {
-      (void)hipGetLastError();
-      return GX_ENOMEM;
-    }
     if (hipMemcpy(eb.mon, mon_mask.data(), mon_mask.size() * sizeof(uint32_t),
-                  hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemsetAsync(eb.viol_ctr, 0, sizeof(uint64_t), stream) != hipSuccess)
+                  hipMemcpyHostToDevice) != hipSuccess)
+      return GX_EDEVICE;
+    // (room for every state of a table that has buffers of its own size)
+    if (roomy && grow_buf(&eb.viol, &eb.viol_cap, n_slots, 0, ~0ull) == GX_EDEVICE)
       return GX_EDEVICE;
     mon_field = ni.field[mp];
     if (opts->monitor_bad[ni.initial[mp]]) {
@@ -704,6 +729,12 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   la.tail = gx::kCtrTail;
   la.waves = grid_max * (gx::kLevelBlock / 64);
   la.max_qs = max_qs;
+
+  gx::ScanArgs scan{};
+  scan.field = mon_field;
+  scan.bad = eb.mon;
+  scan.ctr = eb.ctr;
+  scan.stop = opts && opts->stop_on_violation ? 1u : 0u;
 
   gx::LevelList levels(fixed);
   levels.push(1);
@@ -762,7 +793,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     const uint64_t d_cap_now = std::min<uint64_t>(eb.dead_cap, max_dead);
     uint64_t limit = any_fits && f_both >= n_slots ? ~0ull : f_both / max_succ;
     if (slice_states) limit = std::min<uint64_t>(limit, slice_states);
-    if (!monitor && n_in <= limit && d_cap_now - std::min(dead_known, d_cap_now) >= n_in) {
+    if ((!monitor || eb.viol_cap >= n_slots) && n_in <= limit && d_cap_now - std::min(dead_known, d_cap_now) >= n_in) {
       la.f[0] = eb.f[0];
       la.f[1] = eb.f[1];
       la.cap_out = f_both;
@@ -773,10 +804,23 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
       la.n_in = n_in;
       la.ctl = reinterpret_cast<gx::LevelCtl*>(eb.ctr + kCtrWords);
       la.limit = limit;
-      for (la.link = 0; la.link < kString; ++la.link)
+      for (la.link = 0; la.link < kString; ++la.link) {
         if (gx::launch_level_of(t, la, dedup, grid_max, lds, stream) != hipSuccess)
           return GX_EDEVICE;
+        if (!monitor) continue;
+        scan.f[0] = eb.f[0];
+        scan.f[1] = eb.f[1];
+        scan.out = eb.viol;
+        scan.cap = eb.viol_cap;
+        scan.level = levels.size();
+        scan.ctl = la.ctl;
+        scan.link = la.link;
+        if (gx::launch_monitor_scan(S, scan, static_cast<uint32_t>(cus), stream) != hipSuccess)
+          return GX_EDEVICE;
+      }
       if ((s = read_ctr()) != GX_OK) return s;
+      viol_total = ctr(gx::kCtrViol);
+      if (viol_total && opts->stop_on_violation) stop = true;
       const gx::LevelCtl::Entry& e = ctl->entry[kString & 1u];
       for (uint64_t k = 0; k < e.n_levels; ++k) levels.push(ctl->levels[k]);
       dead_known = ctr(gx::kCtrDead);
@@ -860,28 +904,29 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
       // it (keeping earlier levels' records) and scan the level again
       const uint64_t prev = viol_total;
       for (int pass = 0; pass < 2; ++pass) {
-        if (gx::launch_monitor_scan(S, eb.f[nxt], n_in, mon_field, eb.mon, eb.viol, eb.viol_cap,
-                                    eb.viol_ctr, static_cast<uint32_t>(cus), stream) !=
-            hipSuccess)
+        scan.f[nxt] = eb.f[nxt];
+        scan.n = n_in;
+        scan.cur = static_cast<uint32_t>(nxt);
+        scan.out = eb.viol;
+        scan.cap = eb.viol_cap;
+        scan.level = levels.size() - 1;
+        scan.ctl = nullptr;
+        if (gx::launch_monitor_scan(S, scan, static_cast<uint32_t>(cus), stream) != hipSuccess)
           return GX_EDEVICE;
-        uint64_t got = 0;
-        if (hipMemcpyAsync(&got, eb.viol_ctr, sizeof(got), hipMemcpyDeviceToHost, stream) !=
-                hipSuccess ||
-            hipStreamSynchronize(stream) != hipSuccess)
-          return GX_EDEVICE;
-        viol_total = got;
-        if (got <= eb.viol_cap) break;
-        if ((s = grow_buf(&eb.viol, &eb.viol_cap, got, prev, ~0ull)) != GX_OK) return s;
-        if (hipMemcpy(eb.viol_ctr, &prev, sizeof(prev), hipMemcpyHostToDevice) != hipSuccess)
+        if ((s = read_ctr()) != GX_OK) return s;
+        viol_total = ctr(gx::kCtrViol);
+        if (viol_total <= eb.viol_cap) break;
+        if ((s = grow_buf(&eb.viol, &eb.viol_cap, viol_total, prev, ~0ull)) != GX_OK) return s;
+        if (hipMemcpy(eb.ctr + gx::kCtrViol * gx::kCtrSpread, &prev, sizeof(prev),
+                      hipMemcpyHostToDevice) != hipSuccess)
           return GX_EDEVICE;
       }
-      if (viol_total > prev) {
-        if (viol_level == 0xFFFFFFFFu) viol_level = static_cast<uint32_t>(levels.size() - 1);
-        if (opts->stop_on_violation) stop = true;
-      }
+      if (viol_total > prev && opts->stop_on_violation) stop = true;
     }
     cur = nxt;
   }
+  if (monitor && !init_violates && viol_total)
+    viol_level = static_cast<uint32_t>(ctr(gx::kCtrViolLevel) - 1);
   const uint64_t n_dead = ctr(gx::kCtrDead);
   if (n_dead > std::min<uint64_t>(eb.dead_cap, max_dead)) return GX_ENOMEM;
   if (fixed) return gx::finish_fixed(*fixed, levels, n_dead, ctr(gx::kCtrTrans), eb.dead, S, t->w);

@@ -233,7 +233,7 @@ __device__ __forceinline__ uint32_t walk_items(const uint32_t* img, const uint32
 // counters sharing a line would serialise at one L2 atomic unit.
 constexpr uint32_t kCtrSpread = 16;
 enum : uint32_t { kCtrTail = 0, kCtrDead = 1, kCtrTrans = 2, kCtrFlags = 3, kCtrDups = 4,
-                  kCtrTailAlt = 5, kCtrCount = 6 };
+                  kCtrTailAlt = 5, kCtrViol = 6, kCtrViolLevel = 7, kCtrCount = 8 };
 
 __device__ __forceinline__ unsigned long long* ctr_at(uint64_t* ctr, uint32_t k) {
   return reinterpret_cast<unsigned long long*>(ctr + k * kCtrSpread);
@@ -562,7 +562,9 @@ struct LevelCtl {
   // the next level in the other one, so that a workgroup that starts late
   // still finds the entry of its own launch
   struct Entry {
-    uint64_t n_in, cur, n_levels, go;  // go: the device may expand it
+    uint64_t n_in, cur, n_levels;
+    uint32_t go;     // the device may expand it
+    uint32_t fresh;  // found by the launch that wrote the entry
   } entry[2];
   uint64_t levels[kChainLevels];
 };
@@ -620,7 +622,10 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
     if (a.link > 0) {
       const LevelCtl::Entry& e = a.ctl->entry[a.link & 1u];
       if (!e.go) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->entry[(a.link & 1u) ^ 1u] = e;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+          a.ctl->entry[(a.link & 1u) ^ 1u] = e;
+          a.ctl->entry[(a.link & 1u) ^ 1u].fresh = 0;
+        }
         return;
       }
       n_in = uniform64(e.n_in);
@@ -685,6 +690,7 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
     e.n_in = n_next;
     e.cur = cur ^ 1u;
     e.n_levels = n_levels;
+    e.fresh = flags == 0;
     e.go = flags == 0 && n_next > 0 && n_next <= a.limit && n_levels < kChainLevels &&
                    n_next <= a.dead_cap - min(dead, a.dead_cap)
                ? 1u

@@ -47,12 +47,11 @@ struct gx_explore_buffers {
   uint64_t* ctr_host = nullptr;
   uint8_t* status = nullptr;
   uint32_t* key = nullptr;  // the initial state, 4 words (in the control block)
-  // safety monitor: bad-state bitmask, violating states, their running count
+  // safety monitor: bad-state bitmask, violating states
   uint32_t* mon = nullptr;
   uint64_t mon_cap = 0;      // words
   uint32_t* viol = nullptr;
   uint64_t viol_cap = 0;     // states
-  uint64_t* viol_ctr = nullptr;
 };
 
 struct gx_table {
