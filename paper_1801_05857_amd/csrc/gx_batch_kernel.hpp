@@ -208,8 +208,7 @@ __global__ __launch_bounds__(256) void batch_explore_kernel(BatchArgs a) {
     WaveAcc acc;
     // a level of one tile spreads over the workgroup's lanes
     const uint32_t qs = lanes_per_state(j.n_in, 4, 6);
-    const uint32_t per = 64u >> qs;
-    const uint64_t n_tiles = (j.n_in + per - 1) / per;
+    const uint64_t n_tiles = tiles_of(j.n_in, qs);
     const uint64_t own = static_cast<uint64_t>(tile) * 4 + (threadIdx.x >> 6);
     uint32_t sw[S];
     load_tile<S>(j, uniform64(own), qs, sw);

@@ -126,8 +126,8 @@ __device__ __forceinline__ TargetList target_list(const uint32_t* img, uint32_t 
   TargetList t;
   t.first = (e0 & ~kListCounted) + (e0 >> 31);
   t.n = (e1 & ~kListCounted) - t.first;
-  t.total = t.n;
-  if (e0 >> 31) t.total = img[t.first - 1];
+  const uint32_t count = img[t.first - 1];  // (a list's index is never 0)
+  t.total = e0 >> 31 ? count : t.n;
   return t;
 }
 
@@ -177,49 +177,50 @@ __device__ __forceinline__ uint32_t walk_items(const uint32_t* img, const uint32
     const bool valid = has && i < n_items;
     const uint4 it = *reinterpret_cast<const uint4*>(img + 4 + 4 * (i < n_items ? i : 0));
     const TargetList in = target_list(img, it.w, get_field<S>(sw, it.z));
-    const uint32_t b0 = in.first;
-    uint32_t bend = in.first + in.n;
+    const uint32_t b0 = in.first, bend = in.first + in.n;
     uint32_t outer = 1, a0 = 0, total = in.total;
-    if (it.x == kItemGeneral) {
-      const uint32_t np = img[it.y];
-      for (uint32_t k = 0; k < np; ++k) {
-        const uint32_t f = img[it.y + 1 + 2 * k], ob = img[it.y + 2 + 2 * k];
-        const TargetList t = target_list(img, ob, get_field<S>(sw, f));
-        outer *= t.n;
+    if (it.x) {
+      if (it.x != kItemGeneral) {
+        const TargetList t = target_list(img, it.y, get_field<S>(sw, it.x));
+        a0 = t.first;
+        outer = t.n;
         total *= t.total;
+      } else {
+        const uint32_t np = img[it.y];
+        for (uint32_t k = 0; k < np; ++k) {
+          const uint32_t f = img[it.y + 1 + 2 * k], ob = img[it.y + 2 + 2 * k];
+          const TargetList t = target_list(img, ob, get_field<S>(sw, f));
+          outer *= t.n;
+          total *= t.total;
+        }
       }
-    } else if (it.x) {
-      const TargetList t = target_list(img, it.y, get_field<S>(sw, it.x));
-      a0 = t.first;
-      outer = t.n;
-      total *= t.total;
     }
-    const uint32_t n = valid ? in.n * outer : 0u;
+    uint32_t left = valid ? in.n * outer : 0u;  // successors the item has yet to form
     own += valid ? total : 0u;
-    if (n == 0) bend = b0;
     uint32_t mid[S];
 #pragma unroll
     for (int x = 0; x < S; ++x) mid[x] = sw[x];
     put_field<S>(mid, it.z, 0u);
-    if (n && it.x) put_outer<S>(img, it, sw, a0, 0u, mid);
+    if (left && it.x) put_outer<S>(img, it, sw, a0, 0u, mid);
     uint32_t b = b0, c = 0;
-    uint32_t tgt = b < bend ? img[b] : 0u;
+    uint32_t tgt = img[left ? b : 0u];
     while (true) {
-      const uint64_t m = __ballot(b < bend);
+      const uint64_t m = __ballot(left != 0);
       if (!m) break;
-      if (b < bend) {
+      if (left) {
         uint32_t succ[S];
 #pragma unroll
         for (int x = 0; x < S; ++x)
           succ[x] = mid[x] | (S == 1 || (it.z & 0xFF) == static_cast<uint32_t>(x) ? tgt : 0u);
         store_slot<S>(stage + (cnt + lane_rank(m)) * S, succ);
         ++b;
-        if (b == bend && c + 1 < outer) {
+        --left;
+        if (left && b == bend) {
           ++c;
           b = b0;
           put_outer<S>(img, it, sw, a0, c, mid);
         }
-        if (b < bend) tgt = img[b];
+        tgt = img[left ? b : 0u];
       }
       cnt += static_cast<uint32_t>(__popcll(m));
       if (cnt > limit) sink();
@@ -596,9 +597,17 @@ struct LevelArgs {
 
 // log2 of the lanes per state: as many as keep the device's wavefronts busy.
 __host__ __device__ inline uint32_t lanes_per_state(uint64_t n_in, uint32_t waves, uint32_t max_qs) {
-  uint32_t qs = 0;
-  while (qs < max_qs && (n_in << (qs + 1)) <= static_cast<uint64_t>(waves) * 64) ++qs;
-  return qs;
+  const uint32_t all = waves * 64u;
+  if (n_in > all / 2) return 0;
+  const uint32_t n = n_in ? static_cast<uint32_t>(n_in) : 1u;
+  uint32_t qs = static_cast<uint32_t>(__builtin_clz(n) - __builtin_clz(all));
+  if (n << qs > all) --qs;
+  return qs < max_qs ? qs : max_qs;
+}
+
+// Tiles of n states, 2^qs lanes each.
+__host__ __device__ inline uint64_t tiles_of(uint64_t n, uint32_t qs) {
+  return (n + (64u >> qs) - 1) >> (6 - qs);
 }
 
 // One BFS level (or a slice of it).  Levels that need no decision of the host
@@ -636,8 +645,7 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
   }
   constexpr uint32_t kWaves = kLevelBlock / 64;
   const uint32_t qs = lanes_per_state(n_in, a.waves, a.max_qs);
-  const uint32_t per = 64u >> qs;
-  const uint64_t n_tiles = (n_in + per - 1) / per;
+  const uint64_t n_tiles = tiles_of(n_in, qs);
   const uint64_t groups = min(static_cast<uint64_t>(gridDim.x), (n_tiles + kWaves - 1) / kWaves);
   if (blockIdx.x >= groups) return;
   const uint32_t wave = threadIdx.x >> 6;

@@ -53,8 +53,8 @@ constexpr uint32_t kStepBlock = 256;  // threads per workgroup
 
 // Workgroups of a level of n states.
 __host__ __device__ inline uint64_t step_groups(uint64_t n, uint32_t qs) {
-  const uint64_t per = kStepBlock >> qs;
-  return (n + per - 1) / per;
+  static_assert(kStepBlock == 256, "four tiles a group");
+  return (tiles_of(n, qs) + 3) >> 2;
 }
 
 // LDS bytes of a workgroup with room for an image of img_stride words.
@@ -113,8 +113,7 @@ __global__ __launch_bounds__(kStepBlock) void serve_step_kernel(ServeArgs a) {
     j.ctr = uniform_ptr(jb.ctr);
     j.tail = kCtrTail;
     WaveAcc acc;
-    const uint32_t per = 64u >> qs;
-    const uint64_t n_tiles = (j.n_in + per - 1) / per;
+    const uint64_t n_tiles = tiles_of(j.n_in, qs);
     const uint64_t tile = uniform64(static_cast<uint64_t>(group - a.begin[lo]) * (kStepBlock / 64) +
                                     (threadIdx.x >> 6));
     uint32_t sw[S];

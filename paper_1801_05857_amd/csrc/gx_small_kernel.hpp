@@ -36,6 +36,7 @@ struct SmallArgs {
   uint64_t limit;       // largest level this launch expands
   const uint32_t* init_key;  // the level-0 state
   uint32_t set_mask;    // entries of the LDS visited set, minus one (a power of two)
+  uint32_t ring;        // states of a level that LDS holds
   uint32_t max_succ;    // distinct successors a state can form at most
   uint32_t max_qs;      // log2 of the most lanes a state is worth
 };
@@ -62,15 +63,13 @@ __device__ inline bool lds_set_insert(uint32_t* set, uint32_t mask, const uint32
   uint32_t h = dedup_hash<S>(key) & mask;
   if constexpr (S == 1) {
     // one-word entries: the compare-and-swap is the look too
-    while (__ballot(!done)) {
-      if (!done) {
-        uint32_t old = kEmpty;
-        fresh = __hip_atomic_compare_exchange_strong(set + h, &old, key[0], __ATOMIC_RELAXED,
-                                                     __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-        done = fresh || old == key[0];
-        h = (h + 1) & mask;
-      }
+    while (!done) {
+      uint32_t old = kEmpty;
+      fresh = __hip_atomic_compare_exchange_strong(set + h, &old, key[0], __ATOMIC_RELAXED,
+                                                   __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+      done = fresh || old == key[0];
+      h = (h + 1) & mask;
     }
     return fresh;
   }
@@ -166,6 +165,14 @@ __device__ inline void place_log(const SmallArgs& a, uint32_t* fill, const uint3
   flush_stats(a.t, st, nullptr);
 }
 
+// Workgroup barrier that orders LDS accesses only: global stores stay in
+// flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // The first levels of an exploration, while the table holds nothing but what
 // this launch puts there: an LDS set of every state reached so far decides
 // NEW or SEEN exactly, with no table probe.  New states are appended to a log
@@ -177,15 +184,23 @@ __device__ inline void place_log(const SmallArgs& a, uint32_t* fill, const uint3
 // every logged state goes into the table: placed by this workgroup when the
 // table's per-bucket fill counts fit in the LDS the visited set used (see
 // place_log), else by log_insert_kernel, launched after it.
-// Bound: the chain of dependent LDS reads and barriers of a level.  The lanes
-// share the states' items (walk_items), so that a level of a few hundred
-// states has a few items a lane to walk instead of all of them.
+// Bound: the chain of dependent LDS reads and the barrier of a level.  The
+// lanes share the states' items (walk_items), so that a level of a few
+// hundred states has a few items a lane to walk instead of all of them.  No
+// access to global memory is waited for within a level of up to `ring`
+// states: its states are read from LDS, where two rings hold the last two
+// levels beside the log, and every thread works out for itself, from one
+// count, whether and how the levels go on.
 template <int S, int B>
 __global__ __launch_bounds__(small_threads<S>()) void lds_levels_kernel(SmallArgs a) {
   extern __shared__ __align__(16) uint32_t smem[];
   constexpr uint32_t kWaves = small_threads<S>() / 64;
-  __shared__ uint32_t sh_go, sh_levels, sh_log_n, sh_ls, sh_le, sh_dead;
-  __shared__ unsigned long long sh_trans, sh_dead0;
+  // per level in turn: its new states, its deadlocks from bit kDeadShift on
+  // (the next level's count is cleared while the one before last is read)
+  constexpr uint32_t kDeadShift = 18;
+  __shared__ uint32_t sh_lvl[3];
+  __shared__ uint32_t sh_count[kChainLevels];
+  __shared__ unsigned long long sh_trans;
   const uint32_t tid = threadIdx.x;
   const uint32_t wave = tid >> 6;
   const uint32_t lane = __lane_id();
@@ -193,36 +208,33 @@ __global__ __launch_bounds__(small_threads<S>()) void lds_levels_kernel(SmallArg
   uint32_t* set = smem + a.img_stride;
   const uint32_t n_set = a.set_mask + 1;
   uint32_t* stage = set + n_set * S + wave * kSmallStage * S;
+  uint32_t* rings = set + n_set * S + kWaves * kSmallStage * S;
   uint32_t* log = a.log;
   const uint64_t set_cap = static_cast<uint64_t>(n_set) / 4 * 3;
-  for (uint32_t k = tid; k < a.img_words; k += small_threads<S>()) img[k] = a.img[k];
-  for (uint32_t k = tid; k < n_set * S; k += small_threads<S>()) set[k] = kEmpty;
-  __syncthreads();
-  if (wave == 0) {
-    uint32_t key[S];
+  uint32_t init[S];
 #pragma unroll
-    for (int x = 0; x < S; ++x) key[x] = a.init_key[x];
-    (void)lds_set_insert<S>(set, a.set_mask, key, lane == 0);
-    if (lane == 0) {
-      store_slot<S>(log, key);
-      sh_log_n = 1;
-      sh_ls = 0;
-      sh_le = 1;
-      sh_levels = 0;
-      sh_trans = 0;
-      sh_dead = 0;
-      sh_dead0 = __hip_atomic_load(ctr_at(a.ctr, kCtrDead), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-      sh_go = a.limit >= 1 && 1 + static_cast<uint64_t>(a.max_succ) <= min(set_cap, a.log_cap)
-                  ? 1u
-                  : 0u;
-    }
+  for (int x = 0; x < S; ++x) init[x] = a.init_key[x];
+  for (uint32_t k = tid; k < a.img_words; k += small_threads<S>()) img[k] = a.img[k];
+  for (uint32_t k = tid; k < n_set * S / 4; k += small_threads<S>())
+    reinterpret_cast<uint4*>(set)[k] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
+  if (tid == 0) {
+    store_slot<S>(log, init);
+    store_slot<S>(rings, init);
+    sh_lvl[0] = 0;
+    sh_trans = 0;
   }
+  __syncthreads();
+  if (wave == 0) (void)lds_set_insert<S>(set, a.set_mask, init, lane == 0);
+  __syncthreads();
+  // the level: states [ls, le) of the log (the same in every thread, as all
+  // that decides how the levels go on)
+  uint32_t ls = 0, le = 1, levels = 0, dead = 0, turn = 0, parity = 0;
+  bool go = a.limit >= 1 && 1 + static_cast<uint64_t>(a.max_succ) <= min(set_cap, a.log_cap);
   uint64_t trans = 0;  // this lane's
-  while (true) {
-    __syncthreads();
-    if (!sh_go) break;
-    const uint32_t ls = sh_ls, n_in = sh_le - sh_ls;
+  while (go) {
+    const uint32_t n_in = le - ls;
+    const uint32_t* ring_in = rings + parity * a.ring * S;
+    uint32_t* ring_out = rings + (parity ^ 1u) * a.ring * S;
     const uint32_t qs = lanes_per_state(n_in, kWaves, a.max_qs);
     const uint32_t q = 1u << qs, per = 64u >> qs;
     uint32_t cnt = 0;
@@ -240,9 +252,12 @@ __global__ __launch_bounds__(small_threads<S>()) void lds_levels_kernel(SmallArg
       const uint64_t m = __ballot(fresh);
       if (m) {
         uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(&sh_log_n, static_cast<uint32_t>(__popcll(m)));
-        base = uniform32(base);
-        if (fresh) store_slot<S>(log + static_cast<uint64_t>(base + lane_rank(m)) * S, key);
+        if (lane == 0) base = atomicAdd(&sh_lvl[turn], static_cast<uint32_t>(__popcll(m)));
+        const uint32_t k = (uniform32(base) & ((1u << kDeadShift) - 1u)) + lane_rank(m);
+        if (fresh) {
+          store_slot<S>(log + static_cast<uint64_t>(le + k) * S, key);
+          if (k < a.ring) store_slot<S>(ring_out + k * S, key);
+        }
       }
       wave_lds_sync();
     };
@@ -252,51 +267,60 @@ __global__ __launch_bounds__(small_threads<S>()) void lds_levels_kernel(SmallArg
       uint32_t sw[S];
 #pragma unroll
       for (int x = 0; x < S; ++x) sw[x] = 0;
-      if (has) load_slot<S>(log + static_cast<uint64_t>(ls + i) * S, sw);
+      if (n_in <= a.ring) {
+        if (has) load_slot<S>(ring_in + i * S, sw);
+      } else if (has) {
+        load_slot<S>(log + static_cast<uint64_t>(ls + i) * S, sw);
+      }
       const uint32_t own = walk_items<S>(img, sw, has, lane & (q - 1), q, stage, cnt, 63u, take);
       trans += own;
       const uint64_t m = __ballot(own != 0);
       const uint64_t mine = (m >> (lane & ~(q - 1))) & (q == 64 ? ~0ull : (1ull << q) - 1ull);
       if (has && (lane & (q - 1)) == 0 && mine == 0) {
-        const uint64_t d = atomicAdd(ctr_at(a.ctr, kCtrDead), 1ull);
+        const uint64_t d = dead + (atomicAdd(&sh_lvl[turn], 1u << kDeadShift) >> kDeadShift);
         if (d < a.dead_cap) store_slot<S>(a.dead + d * S, sw);
-        atomicAdd(&sh_dead, 1u);
       }
     }
     if (cnt) take();
-    __syncthreads();  // the level's new states are logged
-    if (tid == 0) {
-      const uint32_t le = sh_le, log_n = sh_log_n, n_next = log_n - le;
-      const uint64_t dead = sh_dead0 + sh_dead;
-      if (n_next) a.out->levels[sh_levels++] = n_next;
-      sh_ls = le;
-      sh_le = log_n;
-      const uint64_t worst = log_n + static_cast<uint64_t>(n_next) * a.max_succ;
-      // (n_next <= limit: the level after it fits the frontier buffer, which
-      // receives the current level when the launch ends)
-      sh_go = n_next > 0 && n_next <= a.limit && sh_levels < kChainLevels &&
-                      worst <= min(set_cap, a.log_cap) &&
-                      n_next <= a.dead_cap - min(dead, a.dead_cap)
-                  ? 1u
-                  : 0u;
+    const uint32_t after = turn == 2 ? 0u : turn + 1;
+    if (tid == 0) sh_lvl[after] = 0;
+    lds_barrier();  // the level's new states are logged
+    const uint32_t v = uniform32(sh_lvl[turn]);
+    const uint32_t n_next = v & ((1u << kDeadShift) - 1u);
+    dead += v >> kDeadShift;
+    turn = after;
+    parity ^= 1u;
+    ls = le;
+    le += n_next;
+    if (n_next) {
+      if (tid == 0) sh_count[levels] = n_next;
+      ++levels;
     }
+    // (n_next <= limit: the level after it fits the frontier buffer, which
+    // receives the current level when the launch ends)
+    go = n_next > 0 && n_next <= a.limit && levels < kChainLevels &&
+         le + static_cast<uint64_t>(n_next) * a.max_succ <= min(set_cap, a.log_cap) &&
+         n_next <= a.dead_cap - min(static_cast<uint64_t>(dead), a.dead_cap);
+    if (n_next > a.ring) __syncthreads();  // (the next level is read from the log)
   }
   trans = wave_sum64(trans);
   if (lane == 0 && trans) atomicAdd(&sh_trans, static_cast<unsigned long long>(trans));
   __syncthreads();
   // the current level becomes frontier buffer 0 (when the levels go on)
-  const uint32_t ls = sh_ls, n_cur = sh_le - sh_ls, log_n = sh_log_n;
+  const uint32_t n_cur = le - ls;
   for (uint32_t k = tid; k < n_cur * S; k += small_threads<S>())
     a.f[k] = log[static_cast<uint64_t>(ls) * S + k];
+  for (uint32_t k = tid; k < levels; k += small_threads<S>()) a.out->levels[k] = sh_count[k];
   // the visited set is done with: its LDS holds the bucket fill counts
   const bool placed = a.t.n_buckets <= static_cast<uint64_t>(n_set) * S;
-  if (placed) place_log<S, B>(a, set, log, log_n);
+  if (placed) place_log<S, B>(a, set, log, le);
   if (tid == 0) {
-    a.out->n_levels = sh_levels;
+    a.out->n_levels = levels;
     a.out->n_in = n_cur;  // 0: the last level expanded found nothing new
     a.out->cur = 0;
-    a.out->log_n = placed ? 0 : log_n;  // states left for log_insert_kernel
+    a.out->log_n = placed ? 0 : le;  // states left for log_insert_kernel
     if (sh_trans) atomicAdd(ctr_at(a.ctr, kCtrTrans), sh_trans);
+    if (dead) atomicAdd(ctr_at(a.ctr, kCtrDead), static_cast<unsigned long long>(dead));
   }
 }
 
@@ -371,7 +395,11 @@ hipError_t launch_lds_levels(uint32_t B, SmallArgs a, size_t lds_limit, hipStrea
   while (bits >= 10 && lds_levels_bytes<S>(a.img_stride, bits) > lds_limit) --bits;
   if (bits < 10) return hipErrorInvalidValue;
   a.set_mask = (1u << bits) - 1u;
-  const size_t lds = lds_levels_bytes<S>(a.img_stride, bits);
+  size_t lds = lds_levels_bytes<S>(a.img_stride, bits);
+  // what the set leaves: two levels' states, at most the largest ones expanded
+  a.ring = static_cast<uint32_t>(
+      std::min<uint64_t>(a.limit, (lds_limit - lds) / (2 * S * sizeof(uint32_t))) & ~3ull);
+  lds += size_t(2) * a.ring * S * sizeof(uint32_t);
   switch (B) {
     case 4: return launch_lds_b<S, 4>(a, lds, s);
     case 8: return launch_lds_b<S, 8>(a, lds, s);
