@@ -583,9 +583,14 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
                        hipMemcpyHostToDevice, stream) != hipSuccess)
       return GX_EDEVICE;
   }
-  if (!eb.ctr && (hipMalloc(&eb.ctr, kControlBytes) != hipSuccess ||
-                  hipHostMalloc(&eb.ctr_host, kControlBytes) != hipSuccess ||
-                  hipMalloc(&eb.status, 8) != hipSuccess)) {
+  if (!fixed &&
+      ((!eb.ctr && hipMalloc(&eb.ctr, kControlBytes) != hipSuccess) ||
+       (!eb.ctr_host && hipHostMalloc(&eb.ctr_host, kControlBytes,
+                                      hipHostMallocMapped | hipHostMallocCoherent) !=
+                            hipSuccess) ||
+       (!eb.report && hipHostMalloc(&eb.report, gx::kReports * sizeof(uint64_t),
+                                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) ||
+       (!eb.status && hipMalloc(&eb.status, 8) != hipSuccess))) {
     (void)hipGetLastError();
     return GX_ENOMEM;
   }
@@ -633,6 +638,8 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   const gx::LevelCtl* ctl = reinterpret_cast<const gx::LevelCtl*>(ctr_raw + kCtrWords);
   auto ctr = [&](uint32_t k) { return ctr_raw[k * gx::kCtrSpread]; };
   t->holds_states = true;  // from here on the exploration writes the table
+  if (++t->explorations == 0) t->explorations = 1;
+  if (!fixed) std::memset(eb.report, 0, gx::kReports * sizeof(uint64_t));
   {
     // zeroed counters, the initial state's whole slot (a 3-word state's
     // fourth word is 0) and the image, up in one copy from pinned memory
@@ -704,11 +711,12 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
 
   int cus = 256;
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device);
-  auto read_ctr = [&]() -> gx_status {
-    if (hipMemcpyAsync(ctr_raw, eb.ctr, kBlockWords * sizeof(uint64_t), hipMemcpyDeviceToHost,
-                       stream) !=
-            hipSuccess ||
-        hipStreamSynchronize(stream) != hipSuccess)
+  // the counters and the control block, copied here, or by the stream's last
+  // launch
+  auto read_ctr = [&](bool copied = false) -> gx_status {
+    if (!copied && (hipMemcpyAsync(ctr_raw, eb.ctr, kBlockWords * sizeof(uint64_t),
+                                   hipMemcpyDeviceToHost, stream) != hipSuccess ||
+                    hipStreamSynchronize(stream) != hipSuccess))
       return GX_EDEVICE;
     if (ctr(gx::kCtrFlags) & gx::kFlagTableFull) return GX_ETABLEFULL;
     if (ctr(gx::kCtrFlags) & gx::kFlagFrontierOverflow) return GX_ENOMEM;
@@ -729,6 +737,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   la.tail = gx::kCtrTail;
   la.waves = grid_max * (gx::kLevelBlock / 64);
   la.max_qs = max_qs;
+  la.number = t->explorations;
 
   gx::ScanArgs scan{};
   scan.field = mon_field;
@@ -745,6 +754,105 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   // successors)
   const bool any_fits = !(opts && opts->frontier_capacity);
   const uint64_t slice_states = opts ? opts->slice_states : 0;
+
+  // Levels whose successors fit whatever they are need nothing of the host:
+  // launches follow each other on the stream, each taking the level the one
+  // before left.  The arguments they share; false: level sizes beyond
+  // `limit`, or than the deadlock buffer has room for, need the host.
+  auto string_args = [&](uint64_t n) {
+    la.f[0] = eb.f[0];
+    la.f[1] = eb.f[1];
+    la.cap_out = std::min<uint64_t>(std::min<uint64_t>(eb.f_cap[0], eb.f_cap[1]), max_cap);
+    la.dead = eb.dead;
+    la.dead_cap = std::min<uint64_t>(eb.dead_cap, max_dead);
+    la.first = 0;
+    la.ctl = reinterpret_cast<gx::LevelCtl*>(eb.ctr + kCtrWords);
+    la.limit = any_fits && la.cap_out >= n_slots ? ~0ull : la.cap_out / max_succ;
+    if (slice_states) la.limit = std::min<uint64_t>(la.limit, slice_states);
+    return (!monitor || eb.viol_cap >= n_slots) && n <= la.limit &&
+           la.dead_cap - std::min(dead_known, la.dead_cap) >= n;
+  };
+  auto launch_link = [&]() -> gx_status {
+    if (gx::launch_level_of(t, la, dedup, grid_max, lds, stream) != hipSuccess) return GX_EDEVICE;
+    if (!monitor) return GX_OK;
+    scan.f[0] = eb.f[0];
+    scan.f[1] = eb.f[1];
+    scan.out = eb.viol;
+    scan.cap = eb.viol_cap;
+    scan.level = levels.size();
+    scan.ctl = la.ctl;
+    scan.link = la.link;
+    return gx::launch_monitor_scan(S, scan, static_cast<uint32_t>(cus), stream) == hipSuccess
+               ? GX_OK
+               : GX_EDEVICE;
+  };
+  // A string that goes on until the exploration is over or the host is
+  // needed.  kAhead launches are queued from the one on whose report is waited
+  // for, and every launch says in host memory what it runs on: the device
+  // never waits for the host, and the launches that turn out to have nothing
+  // to do, 2 us each, are that many.  (Strings of 16 launches with a read-back
+  // after each, about 25 us: a ring of 9 processes 654 us, 568 so; a small
+  // random network 182, 151.  More launches ahead gain nothing.)
+  // `given`: the first launch takes the level from la; the sizes of the
+  // levels found go to `found`.
+  constexpr uint32_t kAhead = 2;
+  uint32_t link = 0;  // launches of all strings, the first of each an even one
+  // The last launch's report is waited for, and it has copied the counters
+  // and the control block by then: with a monitor the stream has to drain
+  // (scans follow), else nothing is left that touches them.
+  auto wait_report = [&](uint32_t k, uint64_t* w) -> gx_status {
+    const uint64_t* word = eb.report + k % gx::kReports;
+    const uint64_t want = (k + 1) & 0xFFFFu;
+    for (uint32_t spins = 1;; ++spins) {
+      *w = __hip_atomic_load(word, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (*w >> 48 == want) return GX_OK;
+      // (a stream that has nothing left to do has reported everything; asked
+      // rarely: the question puts a marker into the stream's queue)
+      if (spins % (1u << 22)) continue;
+      const hipError_t q = hipStreamQuery(stream);
+      if (q == hipErrorNotReady) continue;
+      *w = __hip_atomic_load(word, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM);
+      return q == hipSuccess && *w >> 48 == want ? GX_OK : GX_EDEVICE;
+    }
+  };
+  auto run_string = [&](bool given, std::vector<uint64_t>* found) -> gx_status {
+    link += link & 1u;
+    uint32_t seen = link + (given ? 1u : 0u);  // the next launch to report
+    la.report = eb.report;
+    la.host_block = eb.ctr_host;
+    la.block_words = kBlockWords;
+    gx_status r = GX_OK;
+    uint64_t w = 0;
+    for (bool over = false; r == GX_OK && !over; ++seen) {
+      for (; r == GX_OK && link < seen + kAhead; ++link) {
+        la.link = link;
+        la.given = given ? 1u : 0u;
+        given = false;
+        r = launch_link();
+      }
+      if (r != GX_OK || (r = wait_report(seen, &w)) != GX_OK) break;
+      const uint64_t n = w & (gx::kReportFresh - 1);
+      if ((w & gx::kReportFresh) && n) found->push_back(n);
+      over = !(w & gx::kReportGo);
+    }
+    la.report = nullptr;
+    if (r == GX_OK) r = wait_report(link - 1, &w);
+    if ((r != GX_OK || monitor) && hipStreamSynchronize(stream) != hipSuccess) r = GX_EDEVICE;
+    return r;
+  };
+  // what a string has left, read back: the level is in the entry given
+  auto string_done = [&](uint32_t entry) -> gx_status {
+    viol_total = ctr(gx::kCtrViol);
+    if (viol_total && opts->stop_on_violation) stop = true;
+    dead_known = ctr(gx::kCtrDead);
+    if (dead_known > la.dead_cap) return GX_ENOMEM;
+    const gx::LevelCtl::Entry& e = ctl->entry[entry & 1u];
+    n_in = e.n_in;
+    cur = static_cast<int>(e.cur);
+    return GX_OK;
+  };
+  static_assert(kBlockWords <= gx::kLevelBlock, "one word a thread");
+  std::vector<uint64_t> found;
   if (small_limit > 0) {
     // the first levels, LDS-resident while the table holds nothing else
     gx::SmallArgs sa{};
@@ -764,6 +872,29 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     sa.max_succ = static_cast<uint32_t>(max_out);
     sa.max_qs = max_qs;
     const size_t lds_limit = gx::lds_per_workgroup(t->device);
+    // a network of more states than the visited set may take goes on without
+    // a read-back; one that is likely done has it at once
+    uint32_t set_bits = 0;
+    switch (S) {
+      case 1: set_bits = gx::lds_set_bits<1>(img_stride, lds_limit); break;
+      case 2: set_bits = gx::lds_set_bits<2>(img_stride, lds_limit); break;
+      case 4: set_bits = gx::lds_set_bits<4>(img_stride, lds_limit); break;
+    }
+    uint64_t product = 1;
+    for (uint32_t p = 0; p < net->n_procs && product < (uint64_t(1) << 31); ++p)
+      product *= net->procs[p].n_states;
+    const bool goes_on = !fixed && product > (uint64_t(3) << set_bits) / 4 && string_args(1);
+    sa.next_limit = goes_on ? la.limit : 0;
+    const bool placed =
+        !fixed && (S == 1   ? gx::lds_places<1>(t->n_buckets, 1u << set_bits)
+                   : S == 2 ? gx::lds_places<2>(t->n_buckets, 1u << set_bits)
+                            : gx::lds_places<4>(t->n_buckets, 1u << set_bits));
+    if (placed && !goes_on) {
+      sa.report = eb.report;
+      sa.host_block = eb.ctr_host;
+      sa.block_words = kBlockWords;
+    }
+    sa.number = t->explorations;
     hipError_t e = hipErrorInvalidValue;
     switch (S) {
       case 1: e = gx::launch_lds_levels<1>(t->B, sa, lds_limit, stream); break;
@@ -771,7 +902,11 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
       case 4: e = gx::launch_lds_levels<4>(t->B, sa, lds_limit, stream); break;
     }
     if (e != hipSuccess) return GX_EDEVICE;
-    if ((s = read_ctr()) != GX_OK) return s;
+    uint64_t w = 0;
+    if (goes_on && (s = run_string(false, &found)) != GX_OK) return s;
+    if (sa.report && (s = wait_report(0, &w)) != GX_OK) return s;
+    if (sa.report) link = 1;  // (report 0 is used)
+    if ((s = read_ctr(goes_on || placed)) != GX_OK) return s;
     if (ctl->init_status == gx::kFull) return GX_ETABLEFULL;
     if (ctl->init_status != gx::kNew) return GX_EINVAL;
     for (uint64_t k = 0; k < ctl->n_levels; ++k) levels.push(ctl->levels[k]);
@@ -779,6 +914,10 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     if (dead_known > std::min<uint64_t>(eb.dead_cap, max_dead)) return GX_ENOMEM;
     n_in = ctl->n_in;
     cur = static_cast<int>(ctl->cur);
+    if (goes_on) {
+      for (const uint64_t n : found) levels.push(n);
+      if ((s = string_done(link - 1)) != GX_OK) return s;
+    }
   }
 
   // 16384 workgroups' worth of states per launch unless the caller asks for
@@ -787,48 +926,28 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   constexpr uint64_t kMaxRoom = 1ull << 28;  // states of frontier room one slice may claim
   constexpr uint32_t kString = 16;           // launches between read-backs
   while (n_in > 0 && !stop) {
-    // Levels whose successors fit whatever they are: a string of launches,
-    // each taking the level the one before left.
-    const uint64_t f_both = std::min<uint64_t>(std::min<uint64_t>(eb.f_cap[0], eb.f_cap[1]), max_cap);
-    const uint64_t d_cap_now = std::min<uint64_t>(eb.dead_cap, max_dead);
-    uint64_t limit = any_fits && f_both >= n_slots ? ~0ull : f_both / max_succ;
-    if (slice_states) limit = std::min<uint64_t>(limit, slice_states);
-    if ((!monitor || eb.viol_cap >= n_slots) && n_in <= limit && d_cap_now - std::min(dead_known, d_cap_now) >= n_in) {
-      la.f[0] = eb.f[0];
-      la.f[1] = eb.f[1];
-      la.cap_out = f_both;
-      la.dead = eb.dead;
-      la.dead_cap = d_cap_now;
+    if (string_args(n_in)) {
       la.cur = static_cast<uint32_t>(cur);
-      la.first = 0;
       la.n_in = n_in;
-      la.ctl = reinterpret_cast<gx::LevelCtl*>(eb.ctr + kCtrWords);
-      la.limit = limit;
+      if (!fixed) {
+        found.clear();
+        if ((s = run_string(true, &found)) != GX_OK || (s = read_ctr(true)) != GX_OK) return s;
+        for (const uint64_t n : found) levels.push(n);
+        if ((s = string_done(link - 1)) != GX_OK) return s;
+        continue;
+      }
+      // (no memory that the device writes and the host reads: read back after
+      // every kString launches)
       for (la.link = 0; la.link < kString; ++la.link) {
-        if (gx::launch_level_of(t, la, dedup, grid_max, lds, stream) != hipSuccess)
-          return GX_EDEVICE;
-        if (!monitor) continue;
-        scan.f[0] = eb.f[0];
-        scan.f[1] = eb.f[1];
-        scan.out = eb.viol;
-        scan.cap = eb.viol_cap;
-        scan.level = levels.size();
-        scan.ctl = la.ctl;
-        scan.link = la.link;
-        if (gx::launch_monitor_scan(S, scan, static_cast<uint32_t>(cus), stream) != hipSuccess)
-          return GX_EDEVICE;
+        la.given = la.link == 0;
+        if ((s = launch_link()) != GX_OK) return s;
       }
       if ((s = read_ctr()) != GX_OK) return s;
-      viol_total = ctr(gx::kCtrViol);
-      if (viol_total && opts->stop_on_violation) stop = true;
-      const gx::LevelCtl::Entry& e = ctl->entry[kString & 1u];
-      for (uint64_t k = 0; k < e.n_levels; ++k) levels.push(ctl->levels[k]);
-      dead_known = ctr(gx::kCtrDead);
-      if (dead_known > d_cap_now) return GX_ENOMEM;
-      n_in = e.n_in;
-      cur = static_cast<int>(e.cur);
+      for (uint64_t k = 0; k < ctl->entry[kString & 1u].n_levels; ++k) levels.push(ctl->levels[k]);
+      if ((s = string_done(kString)) != GX_OK) return s;
       continue;
     }
+    la.given = 1;
     // Otherwise the level is expanded in slices small enough that even if
     // every successor were new the next frontier could not overflow: slice *
     // max_succ <= free frontier room (and slice <= free deadlock room, one

@@ -564,7 +564,7 @@ struct LevelCtl {
   // still finds the entry of its own launch
   struct Entry {
     uint64_t n_in, cur, n_levels;
-    uint32_t go;     // the device may expand it
+    uint32_t go;     // the exploration's number if the device may expand it, else 0
     uint32_t fresh;  // found by the launch that wrote the entry
   } entry[2];
   uint64_t levels[kChainLevels];
@@ -586,14 +586,46 @@ struct LevelArgs {
   // states [first, first + n_in) of buffer cur
   uint32_t cur;
   uint64_t first, n_in;
-  // ctl set: launch `link` of a string of levels (see LevelCtl); link 0 takes
-  // the level above, the others the control block's.  A level of more than
+  // ctl set: launch `link` of a string of levels (see LevelCtl); with `given`
+  // it takes the level above, else the control block's.  A level of more than
   // `limit` states, or more than the deadlock buffer has room for, is left
   // to the host.
   LevelCtl* ctl;
   uint32_t link;
+  uint32_t given;
+  uint32_t number;  // the exploration's, not 0
   uint64_t limit;
+  // set: kReports words of host memory; a launch that takes its level from
+  // the control block says there, as it starts, which one that is (see
+  // level_report), and the control block keeps no level sizes.  A launch that
+  // has nothing to expand copies the counters and the control block (they
+  // follow them) to host_block, block_words words of host memory.
+  uint64_t* report;
+  uint64_t* host_block;
+  uint32_t block_words;
 };
+
+// What a launch reports: its link plus one (16 bits), whether it expands the
+// level, whether the launch before it found the level, the level's size.
+constexpr uint32_t kReports = 64;
+constexpr uint64_t kReportGo = uint64_t(1) << 47, kReportFresh = uint64_t(1) << 46;
+__device__ __forceinline__ void level_report(uint64_t* report, uint32_t link, uint64_t go,
+                                             uint32_t fresh, uint64_t n_in) {
+  const uint64_t w = static_cast<uint64_t>((link + 1) & 0xFFFFu) << 48 | go |
+                     (fresh ? kReportFresh : 0) | (n_in & (kReportFresh - 1));
+  __hip_atomic_store(report + link % kReports, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The workgroup copies words of device memory to host memory that the host
+// reads once a report of the same workgroup has told it to.
+__device__ inline void copy_to_host(uint64_t* host, const uint64_t* words, uint32_t n) {
+  for (uint32_t k = threadIdx.x; k < n; k += blockDim.x)
+    __hip_atomic_store(host + k,
+                       __hip_atomic_load(words + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+  __syncthreads();
+}
 
 // log2 of the lanes per state: as many as keep the device's wavefronts busy.
 __host__ __device__ inline uint32_t lanes_per_state(uint64_t n_in, uint32_t waves, uint32_t max_qs) {
@@ -614,7 +646,7 @@ __host__ __device__ inline uint64_t tiles_of(uint64_t n, uint32_t qs) {
 // are strung together: launches that take the current level's size and buffer
 // from the control block follow each other on the stream with no read-back
 // between them, and the workgroup that finishes a level last writes the next
-// one's entry (1.6 us from one launch to the next, about 16 for a read-back).
+// one's entry (1.6 us from one launch to the next, about 20 for a read-back).
 // A launch that finds nothing to do, because the exploration is over or the
 // level needs the host, ends at once.
 template <int S, int B, bool kFilter, bool kGlobalImg>
@@ -628,15 +660,26 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
     if (threadIdx.x < a.img_words) head = a.img[threadIdx.x];
   }
   if (a.ctl != nullptr) {
-    if (a.link > 0) {
+    if (!a.given) {
       const LevelCtl::Entry& e = a.ctl->entry[a.link & 1u];
-      if (!e.go) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-          a.ctl->entry[(a.link & 1u) ^ 1u] = e;
-          a.ctl->entry[(a.link & 1u) ^ 1u].fresh = 0;
+      if (e.go != a.number) {
+        // (The host may return on the report of a string's last launch: what
+        // is left of it then are workgroups that read an entry and end.  An
+        // entry written since has another exploration's number.)
+        if (blockIdx.x == 0) {
+          if (threadIdx.x == 0) {
+            a.ctl->entry[(a.link & 1u) ^ 1u] = e;
+            a.ctl->entry[(a.link & 1u) ^ 1u].fresh = 0;
+          }
+          if (a.report != nullptr) {
+            copy_to_host(a.host_block, a.ctr, a.block_words);
+            if (threadIdx.x == 0) level_report(a.report, a.link, 0, e.fresh, e.n_in);
+          }
         }
         return;
       }
+      if (a.report != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
+        level_report(a.report, a.link, kReportGo, e.fresh, e.n_in);
       n_in = uniform64(e.n_in);
       cur = uniform32(static_cast<uint32_t>(e.cur));
     }
@@ -692,16 +735,19 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
     }
     const uint64_t dead = __hip_atomic_load(ctr_at(a.ctr, kCtrDead), __ATOMIC_RELAXED,
                                             __HIP_MEMORY_SCOPE_AGENT);
-    uint64_t n_levels = a.link > 0 ? a.ctl->entry[a.link & 1u].n_levels : 0;
-    if (n_next) a.ctl->levels[n_levels++] = n_next;
+    uint64_t n_levels = a.given ? 0 : a.ctl->entry[a.link & 1u].n_levels;
+    if (n_next) {
+      if (a.report == nullptr) a.ctl->levels[n_levels] = n_next;
+      ++n_levels;
+    }
     LevelCtl::Entry& e = a.ctl->entry[(a.link & 1u) ^ 1u];
     e.n_in = n_next;
     e.cur = cur ^ 1u;
     e.n_levels = n_levels;
     e.fresh = flags == 0;
-    e.go = flags == 0 && n_next > 0 && n_next <= a.limit && n_levels < kChainLevels &&
-                   n_next <= a.dead_cap - min(dead, a.dead_cap)
-               ? 1u
+    e.go = flags == 0 && n_next > 0 && n_next <= a.limit &&
+                   (a.report != nullptr || n_levels < kChainLevels) && n_next <= a.dead_cap - min(dead, a.dead_cap)
+               ? a.number
                : 0u;
   }
 }

@@ -45,6 +45,7 @@ struct gx_explore_buffers {
   // the counters' part read back after every level
   uint64_t* ctr = nullptr;
   uint64_t* ctr_host = nullptr;
+  uint64_t* report = nullptr;  // host memory that level launches write (level_report)
   uint8_t* status = nullptr;
   uint32_t* key = nullptr;  // the initial state, 4 words (in the control block)
   // safety monitor: bad-state bitmask, violating states
@@ -72,6 +73,7 @@ struct gx_table {
   // something was inserted since creation or the last clear: gx_explore, whose
   // first levels place states assuming an empty table, refuses the table
   bool holds_states = false;
+  uint32_t explorations = 0;  // begun on the table (a number for each, never 0)
   gx_explore_buffers eb;
 
   gx::TableDev dev() const {

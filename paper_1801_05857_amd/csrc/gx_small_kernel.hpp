@@ -39,6 +39,14 @@ struct SmallArgs {
   uint32_t ring;        // states of a level that LDS holds
   uint32_t max_succ;    // distinct successors a state can form at most
   uint32_t max_qs;      // log2 of the most lanes a state is worth
+  uint64_t next_limit;  // largest level that level kernels take up right after it
+  uint32_t number;      // the exploration's
+  // report set: once the states are all placed, the counters and the control
+  // block (they follow them), block_words words, are copied to host_block in
+  // host memory and reported as launch 0's (see level_report)
+  uint64_t* report;
+  uint64_t* host_block;
+  uint32_t block_words;
 };
 
 // A table that held states the launch did not put there (reported as
@@ -111,6 +119,13 @@ __device__ inline bool lds_set_insert(uint32_t* set, uint32_t mask, const uint32
     }
   }
   return fresh;
+}
+
+// Whether the launch places its states itself: the fill counts of the table's
+// buckets fit the LDS of a visited set of n_set entries.
+template <int S>
+__host__ __device__ inline bool lds_places(uint64_t n_buckets, uint32_t n_set) {
+  return n_buckets <= static_cast<uint64_t>(n_set) * S;
 }
 
 // The logged states into the table, by the workgroup that logged them, with
@@ -312,15 +327,30 @@ __global__ __launch_bounds__(small_threads<S>()) void lds_levels_kernel(SmallArg
     a.f[k] = log[static_cast<uint64_t>(ls) * S + k];
   for (uint32_t k = tid; k < levels; k += small_threads<S>()) a.out->levels[k] = sh_count[k];
   // the visited set is done with: its LDS holds the bucket fill counts
-  const bool placed = a.t.n_buckets <= static_cast<uint64_t>(n_set) * S;
+  const bool placed = lds_places<S>(a.t.n_buckets, n_set);
   if (placed) place_log<S, B>(a, set, log, le);
   if (tid == 0) {
     a.out->n_levels = levels;
     a.out->n_in = n_cur;  // 0: the last level expanded found nothing new
     a.out->cur = 0;
     a.out->log_n = placed ? 0 : le;  // states left for log_insert_kernel
+    LevelCtl::Entry& e = a.out->entry[0];
+    e.n_in = n_cur;
+    e.cur = 0;
+    e.n_levels = 0;
+    e.go = n_cur > 0 && n_cur <= a.next_limit &&
+                   n_cur <= a.dead_cap - min(static_cast<uint64_t>(dead), a.dead_cap)
+               ? a.number
+               : 0u;
+    e.fresh = 0;  // (the level's size is among those above)
     if (sh_trans) atomicAdd(ctr_at(a.ctr, kCtrTrans), sh_trans);
     if (dead) atomicAdd(ctr_at(a.ctr, kCtrDead), static_cast<unsigned long long>(dead));
+  }
+  if (placed && a.report != nullptr) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    copy_to_host(a.host_block, a.ctr, a.block_words);
+    if (tid == 0) level_report(a.report, 0, 0, 0, n_cur);
   }
 }
 
@@ -376,7 +406,7 @@ hipError_t launch_lds_b(const SmallArgs& a, size_t lds, hipStream_t s) {
   if (e != hipSuccess) return e;
   // the launch places its log itself when the table's fill counts fit the
   // set's LDS (the test place_log's caller makes)
-  if (a.t.n_buckets <= (static_cast<uint64_t>(a.set_mask) + 1) * S) return hipSuccess;
+  if (lds_places<S>(a.t.n_buckets, a.set_mask + 1)) return hipSuccess;
   // else the logged states (at most three quarters of the set) into the table
   const uint32_t grid = static_cast<uint32_t>(
       std::min<uint64_t>(256, (static_cast<uint64_t>(a.set_mask) + 1) / 256 + 1));
@@ -385,14 +415,21 @@ hipError_t launch_lds_b(const SmallArgs& a, size_t lds, hipStream_t s) {
   return hipGetLastError();
 }
 
+// log2 of the entries of the largest visited set that fits (below 10: none).
+template <int S>
+uint32_t lds_set_bits(uint32_t img_stride, size_t lds_limit) {
+  uint32_t bits = 20;
+  while (bits >= 10 && lds_levels_bytes<S>(img_stride, bits) > lds_limit) --bits;
+  return bits;
+}
+
 // Launch the LDS-resident first levels with the largest visited set that fits
 // lds_limit bytes of LDS, then the insertion of the states they logged;
 // returns hipErrorInvalidValue (nothing launched) when not even 2^10 entries
 // fit.
 template <int S>
 hipError_t launch_lds_levels(uint32_t B, SmallArgs a, size_t lds_limit, hipStream_t s) {
-  uint32_t bits = 20;
-  while (bits >= 10 && lds_levels_bytes<S>(a.img_stride, bits) > lds_limit) --bits;
+  const uint32_t bits = lds_set_bits<S>(a.img_stride, lds_limit);
   if (bits < 10) return hipErrorInvalidValue;
   a.set_mask = (1u << bits) - 1u;
   size_t lds = lds_levels_bytes<S>(a.img_stride, bits);

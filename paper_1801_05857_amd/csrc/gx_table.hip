@@ -168,6 +168,7 @@ void free_table(gx_table* t) {
                   static_cast<void*>(e.img_global)})
     if (p) (void)hipFree(p);
   if (e.ctr_host) (void)hipHostFree(e.ctr_host);
+  if (e.report) (void)hipHostFree(e.report);
   delete t;
 }
 

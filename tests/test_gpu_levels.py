@@ -180,3 +180,18 @@ def test_transitions_that_share_a_successor(P, n, copies, rules, dedup):
         (st, got), = b.results()
         assert st == gx.GX_OK
         _same(got, want)
+
+
+@pytest.mark.parametrize("width,tail", [(3, 200), (40, 9), (700, 6)])
+def test_one_table_on_streams_in_turn(width, tail):
+    """The host goes on from what a string's last launch has reported: the next
+    exploration of the table, on another stream, must not meet what is left of
+    the one before (strings of more launches than reports are kept, too)."""
+    net = _star(width, tail)
+    want = oracle.explore(net, want_visited=True)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    with gx.Table(want.words, 16, 2 * want.n_states, max_hashes=64) as t:
+        for k in range(24):
+            s = streams[k % 3]
+            t.clear(stream=s)
+            _same(gx.explore(net, t, stream=s), want, t if k % 6 == 5 else None)
