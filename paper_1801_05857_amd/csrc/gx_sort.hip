@@ -5,8 +5,9 @@
 //
 // The sort is a stable least-significant-digit radix sort of S-word records by
 // 8-bit digits, over the digits in which the records differ (every other one
-// is the same in all of them and is skipped).  A pass is three kernels: counts
-// per digit and chunk, their prefix sum (one workgroup), and the move.  Bound
+// is the same in all of them and is skipped).  A pass is two kernels, counts per
+// digit and chunk and the move, with a third between them, the counts' prefix
+// sum by one workgroup, for lists of more than 512 chunks.  Bound
 // by launches and the move's rounds at the sizes explorations return (258,720
 // one-word states: 4 passes), by memory beyond (a record is read twice and
 // written once per pass).  Copied out unsorted and sorted by one host thread,
@@ -27,6 +28,11 @@ namespace {
 constexpr uint32_t kSortBlock = 256;
 constexpr uint32_t kSortRounds = 8;
 constexpr uint32_t kSortChunk = kSortBlock * kSortRounds;  // records per workgroup
+// Up to this many chunks every workgroup of a move sums up all chunks' counts
+// for itself (a count a thread and chunk, from the L2); beyond, one workgroup
+// forms the prefix sums in between (5 rounds of 4 us at 75 chunks, 20 us of a
+// pass of 34).
+constexpr uint32_t kSumChunks = 512;
 constexpr uint32_t kGatherBlock = 1024;
 constexpr uint32_t kGatherBlocks = 256;  // few: their atomics meet on a line
 
@@ -146,8 +152,9 @@ __global__ __launch_bounds__(kGatherBlock) void bits_kernel(const uint32_t* rec,
   reduce_bits<S>(h, any, all);
 }
 
-// Records per digit value of each chunk: hist[digit * n_chunks + chunk].
-template <int S>
+// Records per digit value of each chunk: hist[chunk * 256 + digit] where the
+// move sums them up itself (kSums), else hist[digit * n_chunks + chunk].
+template <int S, bool kSums>
 __global__ __launch_bounds__(kSortBlock) void count_kernel(const uint32_t* in, uint64_t n,
                                                            uint32_t word, uint32_t shift,
                                                            uint32_t* hist, uint32_t n_chunks) {
@@ -161,7 +168,9 @@ __global__ __launch_bounds__(kSortBlock) void count_kernel(const uint32_t* in, u
     if (i < n) atomicAdd(&cnt[(in[i * S + word] >> shift) & 255u], 1u);
   }
   __syncthreads();
-  hist[static_cast<uint64_t>(threadIdx.x) * n_chunks + blockIdx.x] = cnt[threadIdx.x];
+  const uint64_t at = kSums ? static_cast<uint64_t>(blockIdx.x) * 256 + threadIdx.x
+                            : static_cast<uint64_t>(threadIdx.x) * n_chunks + blockIdx.x;
+  hist[at] = cnt[threadIdx.x];
 }
 
 // Exclusive prefix sum of x[0, n) in place, by one workgroup.
@@ -202,7 +211,7 @@ __global__ __launch_bounds__(1024) void scan_kernel(uint32_t* x, uint32_t n) {
 
 // Every record to its place: the chunk's start for its digit, then the order
 // of the input (rounds, wavefronts, lanes).
-template <int S>
+template <int S, bool kSums>
 __global__ __launch_bounds__(kSortBlock) void move_kernel(const uint32_t* in, uint32_t* out,
                                                           uint64_t n, uint32_t word,
                                                           uint32_t shift, const uint32_t* hist,
@@ -211,7 +220,31 @@ __global__ __launch_bounds__(kSortBlock) void move_kernel(const uint32_t* in, ui
   __shared__ uint32_t start[256];
   __shared__ uint32_t wcnt[kWaves][256];
   const uint32_t wave = threadIdx.x >> 6, lane = __lane_id();
-  start[threadIdx.x] = hist[static_cast<uint64_t>(threadIdx.x) * n_chunks + blockIdx.x];
+  if constexpr (kSums) {
+    // this thread's digit: its records in the chunks before this one, and in
+    // all; then those of the digits before it
+    uint32_t before = 0, all = 0;
+#pragma unroll 8
+    for (uint32_t c = 0; c < n_chunks; ++c) {
+      const uint32_t x = hist[static_cast<uint64_t>(c) * 256 + threadIdx.x];
+      before += c < blockIdx.x ? x : 0u;
+      all += x;
+    }
+    uint32_t inc = all;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(inc, d, 64);
+      if (lane >= static_cast<uint32_t>(d)) inc += y;
+    }
+    if (lane == 63) wcnt[0][wave] = inc;
+    __syncthreads();
+    uint32_t at = before + inc - all;
+    for (uint32_t w = 0; w < wave; ++w) at += wcnt[0][w];
+    start[threadIdx.x] = at;
+    __syncthreads();
+  } else {
+    start[threadIdx.x] = hist[static_cast<uint64_t>(threadIdx.x) * n_chunks + blockIdx.x];
+  }
 #pragma unroll
   for (uint32_t w = 0; w < kWaves; ++w) wcnt[w][threadIdx.x] = 0;
   __syncthreads();
@@ -265,11 +298,20 @@ hipError_t sort_s(uint32_t* a, uint32_t* b, uint64_t n, uint32_t* hist, const So
     const uint32_t vary = bits.any[word] & ~bits.all[word];
     for (uint32_t shift = 0; shift < 32; shift += 8) {
       if (((vary >> shift) & 255u) == 0) continue;
-      hipLaunchKernelGGL(count_kernel<S>, dim3(n_chunks), dim3(kSortBlock), 0, s, a, n,
-                         static_cast<uint32_t>(word), shift, hist, n_chunks);
-      hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, hist, 256u * n_chunks);
-      hipLaunchKernelGGL(move_kernel<S>, dim3(n_chunks), dim3(kSortBlock), 0, s, a, b, n,
-                         static_cast<uint32_t>(word), shift, hist, n_chunks);
+      const uint32_t w = static_cast<uint32_t>(word);
+      const dim3 grid(n_chunks), block(kSortBlock);
+      if (n_chunks <= kSumChunks) {
+        hipLaunchKernelGGL((count_kernel<S, true>), grid, block, 0, s, a, n, w, shift, hist,
+                           n_chunks);
+        hipLaunchKernelGGL((move_kernel<S, true>), grid, block, 0, s, a, b, n, w, shift, hist,
+                           n_chunks);
+      } else {
+        hipLaunchKernelGGL((count_kernel<S, false>), grid, block, 0, s, a, n, w, shift, hist,
+                           n_chunks);
+        hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, hist, 256u * n_chunks);
+        hipLaunchKernelGGL((move_kernel<S, false>), grid, block, 0, s, a, b, n, w, shift, hist,
+                           n_chunks);
+      }
       std::swap(a, b);
     }
   }

@@ -117,3 +117,12 @@ def test_kept_states_of_batches_and_servers(dev):
         for i, w in zip(ids, want):
             st, got, _ = s.poll(i)
             assert st == gx.GX_OK and np.array_equal(got.states, w.visited)
+
+
+@pytest.mark.parametrize("w", [1, 2, 3])
+@pytest.mark.parametrize("n", [512 * 2048, 512 * 2048 + 1])
+def test_dump_at_the_change_of_prefix_sums(dev, w, n):
+    keys = W.distinct_keys(n, w, seed=5 + w)
+    with gx.Table(w, 16, 2 * n, max_hashes=64) as t:
+        _fill(t, keys, dev)
+        assert np.array_equal(t.dump(), _rows(keys))
