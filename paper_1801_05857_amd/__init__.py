@@ -522,7 +522,13 @@ def _copy_out(addr, n: int, dtype) -> np.ndarray:
     """A numpy copy of n elements at a library-owned host address."""
     if not n or not addr:
         return np.zeros(0, dtype)
-    return np.frombuffer(ctypes.string_at(addr, n * np.dtype(dtype).itemsize), dtype=dtype).copy()
+    size = n * np.dtype(dtype).itemsize
+    if size < 1 << 16:
+        return np.frombuffer(ctypes.string_at(addr, size), dtype=dtype).copy()
+    # (a long list in one copy: the pages of a second one cost as much again)
+    out = np.empty(n, dtype)
+    ctypes.memmove(out.ctypes.data, addr, size)
+    return out
 
 
 def _take_result(res: _ExploreResult) -> ExploreResult:
