@@ -86,8 +86,14 @@ hipError_t launch_fop(const FopArgs& a) {
   // bucket; all found: 8 and 13 us).
   const uint64_t flight = G == 4 ? std::min<uint64_t>(a.n, 8 * a.t.n_buckets) : a.n;
   const uint64_t want = (flight + block - 1) / block;
-  uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>(
-      want, static_cast<uint64_t>(a.cus) * static_cast<uint32_t>(per_cu) * (kWideBlock / block)));
+  const uint64_t resident =
+      static_cast<uint64_t>(a.cus) * static_cast<uint32_t>(per_cu) * (kWideBlock / block);
+  // Long launches come as more workgroups than are resident, of 16 rounds or
+  // more each, so that those done early make room for others: 2^27 keys into
+  // 1 GiB of 32-word buckets and 2^27 more take 11.05 ms with the resident
+  // ones alone, 10.87 with 16 times as many; 2e6 keys gain nothing (192 us).
+  const uint64_t turns = std::max<uint64_t>(1, std::min<uint64_t>(16, a.n / (resident * block * 16)));
+  uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>(want, resident * turns));
   if (grid == 0) grid = 1;
   hipLaunchKernelGGL((fop_kernel<S, B, G, U>), dim3(grid), dim3(block), 0, a.stream, a.t, a.keys,
                      a.w, a.n, a.status, a.n_new);
