@@ -331,8 +331,8 @@ typedef struct {
  * demand; later explorations into the same table reuse them.  Tables of up to
  * 256 MiB get frontier and deadlock buffers of as many states as they have
  * slots at once (within the caller's limits): no level can overflow them, and
- * the levels are launched one after the other on opts->hip_stream, 16 between
- * read-backs.  With larger tables a level whose successors might not fit the
+ * the levels are launched one after the other on opts->hip_stream, each taking
+ * the level the one before left.  With larger tables a level whose successors might not fit the
  * next frontier, if every one were new, is expanded in slices that do, the
  * buffers growing between them.  The network image (the transition tables of
  * every process and rule, about one word per local state and transition) is
@@ -420,9 +420,10 @@ const char* gx_status_str(gx_status status);
  * schedules:
  *   stepped (the default): every unfinished instance advances one BFS level
  *     per step; a step is one launch per class over the current levels of
- *     all its unfinished instances, then one read-back of their next-level
- *     sizes.  gx_batch_run drives the steps from the calling thread and
- *     returns when every instance has finished.
+ *     all its unfinished instances, and one that makes their next levels the
+ *     current ones; 16 steps follow each other between read-backs, classes
+ *     on streams of their own.  gx_batch_run drives the steps from the
+ *     calling thread and returns when every instance has finished.
  *   persistent (use_graph or persistent nonzero): one persistent launch per
  *     class, classes concurrently on their own streams; instances advance
  *     independently, workgroups pulling (instance, level, tile) work from a
@@ -545,9 +546,11 @@ gx_status gx_autotune(uint32_t words_per_state, double load_factor, uint32_t* bu
  * power-of-two block of a device arena of budget_bytes that the server
  * allocates once at creation (a buddy allocator: admission allocates
  * nothing; the largest reservation that can ever fit is the largest power
- * of two within the budget).  A host thread runs steps: one launch per slot width
- * expands the current BFS level of every admitted request, so requests that
- * arrive while others run join at the next step (continuous batching).  A
+ * of two within the budget).  A host thread runs steps: one launch per slot
+ * width, on a stream of its own, expands the current BFS level of every
+ * admitted request.  Up to 8 steps (fewer once levels are large) follow each
+ * other on the device; requests that arrive while others run join between
+ * such strings (continuous batching).  A
  * request whose table fills up is retried with four times its bound (at
  * least twice the states found before it filled up; up to 12 attempts, and
  * only while the reservation fits the budget).  Results equal those of gx_explore on the same network.
@@ -573,7 +576,7 @@ typedef struct {
 
 typedef struct {
   uint64_t submitted, completed, failed, retried;
-  uint64_t steps;          /* multi-request launches run                        */
+  uint64_t steps;          /* steps run: those of the slot width that did most  */
   uint64_t active_peak;    /* largest number of requests admitted at once       */
   uint64_t reserved_peak;  /* largest reservation held (bytes)                  */
   uint64_t states;         /* reachable states of completed requests            */

@@ -596,7 +596,6 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   }
   eb.key = reinterpret_cast<uint32_t*>(eb.ctr + kBlockWords);
   eb.img = eb.key + 4;
-  eb.img_cap = gx::kImgStoreWords;
   // A level's NEW states are in the table, so a frontier buffer as large as
   // the table takes any level; likewise the deadlocks.  Tables of up to
   // kRoomyBytes get such buffers at once (the caller's limits aside), others

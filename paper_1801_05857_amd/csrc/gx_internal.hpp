@@ -30,7 +30,6 @@ struct SortSpace {
 struct gx_explore_buffers {
   gx::SortSpace sort;
   uint32_t* img = nullptr;  // network image (in the control block, see ctr)
-  uint64_t img_cap = 0;     // words
   uint32_t* img_global = nullptr;  // an image too large for LDS (own allocation)
   uint64_t img_global_cap = 0;     // words
   uint32_t* f[2] = {nullptr, nullptr};
