@@ -367,28 +367,23 @@ def cpu_batch_all_cores(W, budget_s: float = 10.0):
 
 
 def explore_bytes_per_state(f: float, B: int, S: int) -> float:
-    """Algorithmic HBM bytes per explored state: its f successors each probe
-    one bucket (at least a 64-byte granule), the state is read from its
+    """Algorithmic HBM bytes per explored state: f bucket probes (of at least
+    a 64-byte granule) for its successors, the state is read from its
     frontier and written to the next one (4S bytes each way), and its claim
     writes back one granule."""
     return f * max(4 * B, GRANULE) + 2 * 4 * S + GRANULE
 
 
-def successor_buffer_bytes_per_state(f: float, w: int) -> float:
-    """HBM bytes per explored state that the two-kernel level adds on top of
-    the algorithmic ones: every successor is written to the successor buffer
-    and read back by the probe kernel (its w words each way; without the
-    local duplicate filter the buffer holds w words per successor, not the
-    slot's S).  Overhead of this implementation, not counted in the
-    roofline."""
-    return f * 2 * 4 * w
-
-
-def roofline_of(states: int, bytes_per_state_total: float, seconds: float) -> dict:
+def roofline_of(states: int, bytes_per_state_total: float, seconds: float,
+                per_transition: bool = False) -> dict:
     """Roofline fields of an exploration leg: algorithmic bytes over wall time
-    against the 8 TB/s HBM peak."""
+    against the 8 TB/s HBM peak.  per_transition: the bytes count a bucket per
+    transition (batches and the server keep no probe counts)."""
     gbps = bytes_per_state_total / seconds / 1e9
-    return {"bound": "hbm", "achieved": round(gbps, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    out = {}
+    if per_transition:
+        out["counted"] = "a bucket per transition; equal successors of a state share a probe"
+    return {**out, "bound": "hbm", "achieved": round(gbps, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(gbps / HBM_PEAK_GBS, 4),
             "algorithmic_bytes_per_state": round(bytes_per_state_total / max(1, states), 1)}
 
@@ -418,7 +413,9 @@ def run_explore_leg(gx, torch, W, live=8, slots=None):
     info = t.info
     f = r.n_transitions / r.n_states
     S = info.slot_words
-    bps = explore_bytes_per_state(f, B, S)
+    # (equal successors of a state share a probe: the buckets read, not the
+    # transitions, are what the bytes are counted from)
+    bps = explore_bytes_per_state(st.probes / r.n_states, B, S)
     t.close()
     out = {"workload": (f"random network: 12 processes x 64 declared states ({live} live), "
                         f"out-degree 3, 32 labels, 25% rendezvous, seed 1, sink 0.15; "
@@ -432,8 +429,7 @@ def run_explore_leg(gx, torch, W, live=8, slots=None):
            "successors_per_state": round(f, 2),
            "probes_per_lookup": round(st.probes / max(1, st.lookups), 4),
            "load_factor": round(r.n_states / info.n_slots, 3),
-           "roofline": roofline_of(r.n_states, r.n_states * bps, dt),
-           "successor_buffer_bytes_per_state": round(successor_buffer_bytes_per_state(f, w), 1)}
+           "roofline": roofline_of(r.n_states, r.n_states * bps, dt)}
     traffic = measured_explore_traffic() if live == 8 and slots == W.LARGE_TABLE_SLOTS else None
     out["roofline"]["traffic"] = traffic
     out["roofline"]["traffic_unit"] = ("HBM bytes per exploration (rocprofv3 FETCH_SIZE + WRITE_SIZE, "
@@ -638,7 +634,7 @@ def run_batch(gx, torch, W, n, seed=11, hashes=16, B=0, G=0, U=0):
                     "multi-instance launch per kernel class per BFS level",
         "instances": n, "ok": len(ok), "states": states, "transitions": trans,
         "seconds": round(t_batch, 4), "states_per_s": round(states / t_batch),
-        "roofline": roofline_of(states, algo_bytes, t_batch),
+        "roofline": roofline_of(states, algo_bytes, t_batch, per_transition=True),
         "persistent_graph_seconds": round(t_graph, 4),
         "persistent_graph_states_per_s": round(states / t_graph),
         "persistent_graph_differing": graph_mismatch,
@@ -739,7 +735,7 @@ def run_serve(gx, torch, W, n_req=1000, seed=5, rates=(0.1, 0.25, 0.5, 0.75, 1.0
                              "states_per_s": round(total_states / burst),
                              "wrong_results": bad,
                              "vs_one_call_per_request": round(single / burst, 2),
-                             "roofline": roofline_of(total_states, algo, burst)}
+                             "roofline": roofline_of(total_states, algo, burst, per_transition=True)}
         print(json.dumps({"served": "saturation", **out["saturation"]}), file=sys.stderr,
               flush=True)
         out["rates"] = []
@@ -875,7 +871,7 @@ def main():
                 s = t.stats()
                 per_state = (r.n_transitions / max(1, r.n_states))
                 S = t.info.slot_words
-                bps = explore_bytes_per_state(per_state, args.bucket, S)
+                bps = explore_bytes_per_state(s.probes / max(1, r.n_states), args.bucket, S)
                 print(json.dumps({"net": spec, "words": w, "states": r.n_states,
                                   "transitions": r.n_transitions, "levels": len(r.levels),
                                   "max_level": int(r.levels.max()), "deadlocks": len(r.deadlocks),
