@@ -7,19 +7,12 @@
 #include <cstdint>
 
 #include "gx_explore_kernel.hpp"
+#include "gx_lds_plan.hpp"
 
 namespace gx {
 
 constexpr uint64_t kSmallMaxLevel = 4096;    // largest level the workgroup expands
 constexpr uint64_t kSmallSuccBudget = 4096;  // and at most this many successors (worst case)
-
-// Threads of the workgroup: 16 wavefronts, 8 for four-word slots (a
-// wavefront's stage then takes twice the LDS, and the visited set needs it).
-template <int S>
-__host__ __device__ constexpr uint32_t small_threads() {
-  return S == 4 ? 512u : 1024u;
-}
-constexpr uint32_t kSmallStage = 128;  // staged successors per wavefront
 
 struct SmallArgs {
   TableDev t;
@@ -386,13 +379,6 @@ __global__ __launch_bounds__(256) void log_insert_kernel(TableDev t, const uint3
   flush_stats(t, st, nullptr);
 }
 
-// LDS bytes of an LDS-resident launch with 2^set_bits set entries.
-template <int S>
-size_t lds_levels_bytes(uint32_t img_stride, uint32_t set_bits) {
-  return (static_cast<size_t>(img_stride) + (size_t(S) << set_bits) +
-          small_threads<S>() / 64 * kSmallStage * S) * sizeof(uint32_t);
-}
-
 template <int S, int B>
 hipError_t launch_lds_b(const SmallArgs& a, size_t lds, hipStream_t s) {
   const void* k = reinterpret_cast<const void*>(&lds_levels_kernel<S, B>);
@@ -415,34 +401,22 @@ hipError_t launch_lds_b(const SmallArgs& a, size_t lds, hipStream_t s) {
   return hipGetLastError();
 }
 
-// log2 of the entries of the largest visited set that fits (below 10: none).
-template <int S>
-uint32_t lds_set_bits(uint32_t img_stride, size_t lds_limit) {
-  uint32_t bits = 20;
-  while (bits >= 10 && lds_levels_bytes<S>(img_stride, bits) > lds_limit) --bits;
-  return bits;
-}
-
 // Launch the LDS-resident first levels with the largest visited set that fits
 // lds_limit bytes of LDS, then the insertion of the states they logged;
 // returns hipErrorInvalidValue (nothing launched) when not even 2^10 entries
 // fit.
 template <int S>
 hipError_t launch_lds_levels(uint32_t B, SmallArgs a, size_t lds_limit, hipStream_t s) {
-  const uint32_t bits = lds_set_bits<S>(a.img_stride, lds_limit);
-  if (bits < 10) return hipErrorInvalidValue;
-  a.set_mask = (1u << bits) - 1u;
-  size_t lds = lds_levels_bytes<S>(a.img_stride, bits);
-  // what the set leaves: two levels' states, at most the largest ones expanded
-  a.ring = static_cast<uint32_t>(
-      std::min<uint64_t>(a.limit, (lds_limit - lds) / (2 * S * sizeof(uint32_t))) & ~3ull);
-  lds += size_t(2) * a.ring * S * sizeof(uint32_t);
+  const LdsPlan plan = lds_plan<S>(a.img_stride, a.limit, lds_limit);
+  if (plan.set_bits < 10) return hipErrorInvalidValue;
+  a.set_mask = (1u << plan.set_bits) - 1u;
+  a.ring = plan.ring;
   switch (B) {
-    case 4: return launch_lds_b<S, 4>(a, lds, s);
-    case 8: return launch_lds_b<S, 8>(a, lds, s);
-    case 16: return launch_lds_b<S, 16>(a, lds, s);
-    case 32: return launch_lds_b<S, 32>(a, lds, s);
-    case 64: return launch_lds_b<S, 64>(a, lds, s);
+    case 4: return launch_lds_b<S, 4>(a, plan.bytes, s);
+    case 8: return launch_lds_b<S, 8>(a, plan.bytes, s);
+    case 16: return launch_lds_b<S, 16>(a, plan.bytes, s);
+    case 32: return launch_lds_b<S, 32>(a, plan.bytes, s);
+    case 64: return launch_lds_b<S, 64>(a, plan.bytes, s);
   }
   return hipErrorInvalidValue;
 }
