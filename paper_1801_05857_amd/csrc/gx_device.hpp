@@ -343,13 +343,16 @@ __device__ inline void flush_stats(const TableDev& t, const LaneStats& st, uint6
 // The same for a whole workgroup of a kernel whose wavefronts all come here:
 // one set of atomics per workgroup.  All atomics on one address are carried
 // out one after the other, about 9 ns each, so one per wavefront of a full
-// grid costs a launch 70 us.
-__device__ inline void flush_stats_block(const TableDev& t, const LaneStats& st, uint64_t* n_new) {
+// grid costs a launch 70 us.  wave: the wavefront's number in the workgroup, a
+// scalar: the thread's own number would hold a register of every lane
+// throughout the kernel.
+__device__ inline void flush_stats_block(const TableDev& t, const LaneStats& st, uint64_t* n_new,
+                                         uint32_t wave) {
   __shared__ uint32_t part[16][6];
   const uint32_t probes = wave_sum(st.probes);
   const uint32_t mj = wave_max(st.max_j);
-  const uint32_t wave = threadIdx.x >> 6;
-  if (__lane_id() == 0) {
+  const uint32_t lane = __lane_id();
+  if (lane == 0) {
     part[wave][0] = st.stored;
     part[wave][1] = st.lookups;
     part[wave][2] = probes;
@@ -358,21 +361,21 @@ __device__ inline void flush_stats_block(const TableDev& t, const LaneStats& st,
     part[wave][5] = mj;
   }
   __syncthreads();
-  if (threadIdx.x >= 6) return;
+  if (wave != 0 || lane >= 6) return;
   uint64_t x = 0;
   for (uint32_t w = 0; w < blockDim.x / 64; ++w) {
-    const uint64_t y = part[w][threadIdx.x];
-    x = threadIdx.x == 5 ? (y > x ? y : x) : x + y;
+    const uint64_t y = part[w][lane];
+    x = lane == 5 ? (y > x ? y : x) : x + y;
   }
   if (x == 0) return;
-  if (threadIdx.x == 0 && n_new) atomicAdd(reinterpret_cast<unsigned long long*>(n_new), x);
+  if (lane == 0 && n_new) atomicAdd(reinterpret_cast<unsigned long long*>(n_new), x);
   if (t.counters == nullptr) return;  // a table that keeps no statistics
   static_assert(kCntStored == 0 && kCntLookups == 1 && kCntProbes == 2 && kCntFull == 3 &&
                     kCntInvalid == 4 && kCntMaxJ == 5,
                 "counter order");
   auto* c = reinterpret_cast<unsigned long long*>(
-      t.counters + static_cast<uint64_t>(blockIdx.x % t.ctr_slots) * kNumCounters + threadIdx.x);
-  if (threadIdx.x == 5) atomicMax(c, x);
+      t.counters + static_cast<uint64_t>(blockIdx.x % t.ctr_slots) * kNumCounters + lane);
+  if (lane == 5) atomicMax(c, x);
   else atomicAdd(c, x);
 }
 

@@ -10,7 +10,18 @@
 namespace gx {
 
 constexpr uint32_t kLanesPerCu = 2048;  // 8 wavefronts on each of 4 SIMDs
-constexpr uint32_t kWideBlock = 1024;   // threads per workgroup of a large launch
+
+// Threads per workgroup, at most.  4-lane subgroups take wide workgroups in
+// large launches (their number sets how many atomics meet on n_new).  The
+// others hold up to eight keys' buckets in registers and keep to 256 threads:
+// 1024 leave a lane 128 registers, and a compute unit whole workgroups of 16
+// wavefronts only.  2^23 two-word keys found: buckets of 64 words, eight lanes
+// and eight keys 4930 us at 1024 threads, spilling, and 807 at 256; buckets of
+// 16 words, 16 lanes and two keys 285 and 218 us.
+template <int G>
+constexpr uint32_t fop_block() {
+  return G == 4 ? 1024u : 256u;
+}
 
 template <int S>
 __device__ inline void load_key(const uint32_t* keys, uint32_t w, uint64_t idx,
@@ -41,13 +52,13 @@ __device__ inline void load_key(const uint32_t* keys, uint32_t w, uint64_t idx,
 // One key per lane: a wavefront handles 64 consecutive keys per round (one
 // coalesced read of the keys, one coalesced write of the statuses), its
 // subgroups probing them U at a time.  Grid-stride over rounds.
-// Workgroups are wide in large launches: their number, not the keys', sets
-// how many atomics meet on n_new.
 template <int S, int B, int G, int U>
-__global__ __launch_bounds__(1024) void fop_kernel(TableDev t, const uint32_t* keys, uint32_t w,
-                                                  uint64_t n, uint8_t* status, uint64_t* n_new) {
+__global__ __launch_bounds__(fop_block<G>()) void fop_kernel(TableDev t, const uint32_t* keys,
+                                                             uint32_t w, uint64_t n,
+                                                             uint8_t* status, uint64_t* n_new) {
   const int lane = __lane_id();
-  const uint64_t wave = (static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
+  const uint32_t local = uniform32(threadIdx.x >> 6);
+  const uint64_t wave = static_cast<uint64_t>(blockIdx.x) * (blockDim.x >> 6) + local;
   const uint64_t n_waves = (static_cast<uint64_t>(gridDim.x) * blockDim.x) >> 6;
   LaneStats st;
   for (uint64_t base = wave * 64; base < n; base += n_waves * 64) {
@@ -60,7 +71,7 @@ __global__ __launch_bounds__(1024) void fop_kernel(TableDev t, const uint32_t* k
     const uint8_t r = find_or_put_lanes<S, B, G, U>(t, key, act, st);
     if (act) status[idx] = r;
   }
-  flush_stats_block(t, st, n_new);
+  flush_stats_block(t, st, n_new, local);
 }
 
 
@@ -68,16 +79,17 @@ template <int S, int B, int G, int U>
 hipError_t launch_fop(const FopArgs& a) {
   // as many workgroups as can be resident at once (grid-stride over rounds);
   // narrow ones while they are few, so that a small launch spreads out
+  constexpr uint32_t kBlock = fop_block<G>();
   static int per_cu = 0;
   if (per_cu == 0) {
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, fop_kernel<S, B, G, U>, kWideBlock, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, fop_kernel<S, B, G, U>, kBlock, 0) !=
             hipSuccess ||
         b <= 0)
       b = 1;
     per_cu = b;
   }
-  const uint32_t block = a.n <= static_cast<uint64_t>(a.cus) * 512 ? 256 : kWideBlock;
+  const uint32_t block = a.n <= static_cast<uint64_t>(a.cus) * 512 ? 256 : kBlock;
   // one key per thread per round.  4-lane subgroups, with every key of a
   // round in flight, take at most eight keys a bucket at once: the keys that
   // meet in one bucket of an empty table claim its slots one after the other,
@@ -87,7 +99,7 @@ hipError_t launch_fop(const FopArgs& a) {
   const uint64_t flight = G == 4 ? std::min<uint64_t>(a.n, 8 * a.t.n_buckets) : a.n;
   const uint64_t want = (flight + block - 1) / block;
   const uint64_t resident =
-      static_cast<uint64_t>(a.cus) * static_cast<uint32_t>(per_cu) * (kWideBlock / block);
+      static_cast<uint64_t>(a.cus) * static_cast<uint32_t>(per_cu) * (kBlock / block);
   // Long launches come as more workgroups than are resident, of 16 rounds or
   // more each, so that those done early make room for others: 2^27 keys into
   // 1 GiB of 32-word buckets and 2^27 more take 11.05 ms with the resident
