@@ -604,9 +604,14 @@ __device__ __forceinline__ uint32_t quad_code(const uint4& v, const uint32_t (&k
 // last-level cache) and 27 G/s of random 64-bit claims; with one key in
 // flight per subgroup, four dependent rounds per wavefront, launches of up
 // to a few million keys were bound by the rounds' latency instead.
-template <int S, int B>
+// kTurns, turns (a power of two, minus one): a lane that would claim waits for its
+// turn, one iteration in turns + 1, and looks again past the caches meanwhile.
+// Where many keys meet in a bucket, every claim made at once is made once per
+// EMPTY slot ahead of it; spread over the iterations most of them find the
+// slot taken, or their key there, with a read.  Keys that are found never wait.
+template <int S, int B, bool kTurns = false>
 __device__ inline uint8_t find_or_put_quads(const TableDev& t, const uint32_t (&key)[S], bool act,
-                                            LaneStats& st) {
+                                            LaneStats& st, uint32_t turns = 0) {
   constexpr int PW = B < 16 ? B : 16;  // words of a piece
   constexpr int LQ = PW / 4;           // lanes holding them
   constexpr uint32_t NP = B / PW;      // pieces per bucket
@@ -627,7 +632,7 @@ __device__ inline uint8_t find_or_put_quads(const TableDev& t, const uint32_t (&
   uint32_t j = 0, piece = 0;
   bool fresh = false;
   if (act) ++st.probes;
-  while (__any(act)) {
+  for (uint32_t turn = 0; __any(act); ++turn) {
     uint4 v[4];
     const uint32_t lo = static_cast<uint32_t>(off), hi = static_cast<uint32_t>(off >> 32);
     // 0: no read, 1: plain read, 2: read past the caches
@@ -696,6 +701,9 @@ __device__ inline uint8_t find_or_put_quads(const TableDev& t, const uint32_t (&
         act = false;  // SEEN
       } else if (any & 2u) {
         fresh = true;  // PARTIAL: look again
+        ++st.probes;
+      } else if (kTurns && empty && ((turn + __lane_id()) & turns)) {
+        fresh = true;  // not this lane's turn to claim
         ++st.probes;
       } else {
         // the lowest EMPTY slot; lost to another key, the next one: every
@@ -768,12 +776,12 @@ __device__ inline uint8_t find_or_put_quads(const TableDev& t, const uint32_t (&
 // lane shuffles; the result comes back to the owner lane.  Returns the owner's
 // status (kNew / kSeen / kFull / kInvalid).  Must be reached by the whole
 // wavefront.
-template <int S, int B, int G, int U>
+template <int S, int B, int G, int U, bool kTurns>
 __device__ inline uint8_t find_or_put_lanes(const TableDev& t, const uint32_t (&own)[S],
-                                            bool own_act, LaneStats& st) {
+                                            bool own_act, LaneStats& st, uint32_t turns) {
   static_assert(U >= 1 && U <= G && (G % U) == 0, "keys in flight per subgroup");
   if constexpr (G == 4) {
-    return find_or_put_quads<S, B>(t, own, own_act, st);
+    return find_or_put_quads<S, B, kTurns>(t, own, own_act, st, turns);
   } else {
     const int lane = __lane_id();
     const int li = lane % G;

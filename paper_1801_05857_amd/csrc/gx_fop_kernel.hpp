@@ -10,6 +10,7 @@
 namespace gx {
 
 constexpr uint32_t kLanesPerCu = 2048;  // 8 wavefronts on each of 4 SIMDs
+constexpr uint64_t kMeet = 8;           // keys in a bucket that claim at once
 
 // Threads per workgroup, at most.  4-lane subgroups take wide workgroups in
 // large launches (their number sets how many atomics meet on n_new).  The
@@ -51,11 +52,13 @@ __device__ inline void load_key(const uint32_t* keys, uint32_t w, uint64_t idx,
 
 // One key per lane: a wavefront handles 64 consecutive keys per round (one
 // coalesced read of the keys, one coalesced write of the statuses), its
-// subgroups probing them U at a time.  Grid-stride over rounds.
-template <int S, int B, int G, int U>
+// subgroups probing them U at a time (kTurns: claims in turns, see
+// find_or_put_quads).  Grid-stride over rounds.
+template <int S, int B, int G, int U, bool kTurns>
 __global__ __launch_bounds__(fop_block<G>()) void fop_kernel(TableDev t, const uint32_t* keys,
                                                              uint32_t w, uint64_t n,
-                                                             uint8_t* status, uint64_t* n_new) {
+                                                             uint8_t* status, uint64_t* n_new,
+                                                             uint32_t turns) {
   const int lane = __lane_id();
   const uint32_t local = uniform32(threadIdx.x >> 6);
   const uint64_t wave = static_cast<uint64_t>(blockIdx.x) * (blockDim.x >> 6) + local;
@@ -68,7 +71,7 @@ __global__ __launch_bounds__(fop_block<G>()) void fop_kernel(TableDev t, const u
 #pragma unroll
     for (int x = 0; x < S; ++x) key[x] = 0;
     if (act) load_key<S>(keys, w, idx, key);
-    const uint8_t r = find_or_put_lanes<S, B, G, U>(t, key, act, st);
+    const uint8_t r = find_or_put_lanes<S, B, G, U, kTurns>(t, key, act, st, turns);
     if (act) status[idx] = r;
   }
   flush_stats_block(t, st, n_new, local);
@@ -83,32 +86,40 @@ hipError_t launch_fop(const FopArgs& a) {
   static int per_cu = 0;
   if (per_cu == 0) {
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, fop_kernel<S, B, G, U>, kBlock, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, fop_kernel<S, B, G, U, false>, kBlock, 0) !=
             hipSuccess ||
         b <= 0)
       b = 1;
     per_cu = b;
   }
   const uint32_t block = a.n <= static_cast<uint64_t>(a.cus) * 512 ? 256 : kBlock;
-  // one key per thread per round.  4-lane subgroups, with every key of a
-  // round in flight, take at most eight keys a bucket at once: the keys that
-  // meet in one bucket of an empty table claim its slots one after the other,
-  // and each claims every slot that another took before it (2^19 one-word
-  // keys into 2^15 buckets of 32 words: 140 us all at once, 66 us at four a
-  // bucket; all found: 8 and 13 us).
-  const uint64_t flight = G == 4 ? std::min<uint64_t>(a.n, 8 * a.t.n_buckets) : a.n;
-  const uint64_t want = (flight + block - 1) / block;
+  const uint64_t want = (a.n + block - 1) / block;  // one key per thread per round
   const uint64_t resident =
       static_cast<uint64_t>(a.cus) * static_cast<uint32_t>(per_cu) * (kBlock / block);
   // Long launches come as more workgroups than are resident, of 16 rounds or
   // more each, so that those done early make room for others: 2^27 keys into
   // 1 GiB of 32-word buckets and 2^27 more take 11.05 ms with the resident
   // ones alone, 10.87 with 16 times as many; 2e6 keys gain nothing (192 us).
-  const uint64_t turns = std::max<uint64_t>(1, std::min<uint64_t>(16, a.n / (resident * block * 16)));
-  uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>(want, resident * turns));
+  const uint64_t over = std::max<uint64_t>(1, std::min<uint64_t>(16, a.n / (resident * block * 16)));
+  uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>(want, resident * over));
   if (grid == 0) grid = 1;
-  hipLaunchKernelGGL((fop_kernel<S, B, G, U>), dim3(grid), dim3(block), 0, a.stream, a.t, a.keys,
-                     a.w, a.n, a.status, a.n_new);
+  // 4-lane subgroups, with every key of a round in flight, claim in turns
+  // (see find_or_put_quads) once more than kMeet keys of a round meet in a
+  // bucket.  2^19 one-word keys into 2^15 empty buckets of 32 words: 147 us
+  // all at once, 100 so (146 at 16 keys a bucket, 104 at four); 2^19 two-word
+  // keys, 1024 different ones, into 128 buckets: 487 and 160 us; found there
+  // 8.6 either way.  (Fewer workgroups instead, as many as bring eight keys a
+  // bucket, keep most of the device idle where keys are found: 1475 us.)
+  const uint64_t flight = std::min<uint64_t>(a.n, resident * block);
+  uint32_t turns = 1;
+  while (G == 4 && turns < 64 && flight > turns * kMeet * a.t.n_buckets) turns *= 2;
+  // (a kernel of its own: the test for the turn costs the others 1%)
+  if (turns > 1)
+    hipLaunchKernelGGL((fop_kernel<S, B, G, U, G == 4>), dim3(grid), dim3(block), 0, a.stream, a.t,
+                       a.keys, a.w, a.n, a.status, a.n_new, turns - 1);
+  else
+    hipLaunchKernelGGL((fop_kernel<S, B, G, U, false>), dim3(grid), dim3(block), 0, a.stream, a.t,
+                       a.keys, a.w, a.n, a.status, a.n_new, 0u);
   return hipGetLastError();
 }
 
