@@ -879,6 +879,8 @@ gx_status gx_batch_run(gx_batch* b, void* hip_stream) {
 
 gx_status gx_batch_results(gx_batch* b, gx_explore_result* outs, gx_status* inst_status) {
   if (!b || !outs || !inst_status || !b->ran) return GX_EINVAL;
+  const gx::DeviceGuard on(b->device);
+  if (!on.ok()) return GX_EDEVICE;
   if (hipDeviceSynchronize() != hipSuccess) return GX_EDEVICE;
   for (uint32_t i = 0; i < b->n; ++i) {
     std::memset(&outs[i], 0, sizeof(gx_explore_result));

@@ -11,6 +11,27 @@
 
 namespace gx {
 
+// Makes `device` the calling thread's current one while it lives: for calls
+// that allocate memory or launch on the null stream for an object that may
+// belong to another device than the current one.
+class DeviceGuard {
+ public:
+  explicit DeviceGuard(int device) {
+    ok_ = hipGetDevice(&before_) == hipSuccess;
+    if (ok_ && before_ != device) switched_ = ok_ = hipSetDevice(device) == hipSuccess;
+  }
+  ~DeviceGuard() {
+    if (switched_) (void)hipSetDevice(before_);
+  }
+  DeviceGuard(const DeviceGuard&) = delete;
+  DeviceGuard& operator=(const DeviceGuard&) = delete;
+  bool ok() const { return ok_; }
+
+ private:
+  int before_ = -1;
+  bool ok_ = false, switched_ = false;
+};
+
 // Device workspace of the sorted lists (see gx_sort.hip); grow-only, freed
 // with its owner.
 struct SortSpace {

@@ -463,6 +463,7 @@ hipError_t enqueue_steps(gx_server* s, uint32_t S, uint32_t cus, uint64_t all_st
 }
 
 void step_loop(gx_server* s) {
+  (void)hipSetDevice(s->device);  // a new thread starts with device 0
   const uint32_t cus = resident_grid(s->device, 1);
   while (true) {
     {

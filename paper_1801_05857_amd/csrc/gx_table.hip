@@ -439,6 +439,8 @@ gx_status gx_table_copy_raw(gx_table* t, uint32_t* dev_words, uint64_t first, ui
 
 gx_status gx_table_dump(gx_table* t, uint32_t* host_keys, uint64_t cap, uint64_t* n_out) {
   if (!t || !n_out) return GX_EINVAL;
+  const gx::DeviceGuard on(t->device);
+  if (!on.ok()) return GX_EDEVICE;
   uint64_t count = 0;
   const uint64_t n_slots = t->n_buckets * (t->B / t->S);
   if (n_slots * t->S >= gx::kGatherMin) {
