@@ -328,13 +328,14 @@ typedef struct {
  *
  * Device buffers (frontiers, deadlock list, the log of the first levels,
  * network image) are owned by the table, allocated on first use and grown on
- * demand; later explorations into the same table reuse them.  Tables of up to
- * 256 MiB get frontier and deadlock buffers of as many states as they have
- * slots at once (within the caller's limits): no level can overflow them, and
- * the levels are launched one after the other on opts->hip_stream, each taking
- * the level the one before left.  With larger tables a level whose successors might not fit the
- * next frontier, if every one were new, is expanded in slices that do, the
- * buffers growing between them.  The network image (the transition tables of
+ * demand; later explorations into the same table reuse them.  They begin with
+ * 65536 states each (within the caller's limits); levels whose successors fit
+ * whatever they are follow each other on opts->hip_stream, each launch taking
+ * the level the one before left.  With a table of up to 256 MiB, a level that
+ * might not fit makes the frontier and deadlock buffers grow to as many states
+ * as the table has slots (or the network's local states have combinations, if
+ * fewer), which any level fits; with a larger one it is expanded in slices
+ * that do fit, the buffers growing between them.  The network image (the transition tables of
  * every process and rule, about one word per local state and transition) is
  * read from LDS when the tables fit 11776 words (46 KiB), else from global
  * memory (up to 2^26 words).

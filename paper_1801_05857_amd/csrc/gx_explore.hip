@@ -258,7 +258,7 @@ namespace {
 // counter and, below cap, copied to out (S words each); the first one ever
 // leaves its level, plus one, in kCtrViolLevel.  With ctl (a string of levels,
 // see LevelCtl) the level is the one that launch `link` has left, if it left
-// one; `stop` then ends the string at a violation.  One atomic add per
+// one whose records fit; `stop` then ends the string at a violation.  One atomic add per
 // workgroup and round that finds any.
 struct ScanArgs {
   const uint32_t* f[2];
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(256) void monitor_scan_kernel(ScanArgs a) {
   LevelCtl::Entry* e = nullptr;
   if (a.ctl != nullptr) {
     e = &a.ctl->entry[(a.link & 1u) ^ 1u];
-    if (!e->fresh) return;
+    if (e->scan != kScanHere) return;
     n = uniform64(e->n_in);
     cur = uniform32(static_cast<uint32_t>(e->cur));
     level = a.level + e->n_levels - 1;
@@ -596,22 +596,21 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   }
   eb.key = reinterpret_cast<uint32_t*>(eb.ctr + kBlockWords);
   eb.img = eb.key + 4;
-  // A level's NEW states are in the table, so a frontier buffer as large as
-  // the table takes any level; likewise the deadlocks.  Tables of up to
-  // kRoomyBytes get such buffers at once (the caller's limits aside), others
-  // ones that grow with the levels.
+  // A level's NEW states are in the table, and there are no more states than
+  // the product of the local ones: a frontier buffer that holds the smaller of
+  // the two takes any level; likewise the deadlocks.  With tables of up to
+  // kRoomyBytes buffers may grow to that, as the levels need it (see
+  // make_room), so that levels follow each other on the device; with others
+  // they grow with the levels.
   constexpr uint64_t kRoomyBytes = 256ull << 20;
   const uint64_t n_slots = t->n_buckets * (t->B / S);
-  const bool roomy = !fixed && n_slots * state_bytes <= kRoomyBytes;
-  auto first_buf = [&](uint32_t** p, uint64_t* cap, uint64_t limit) -> gx_status {
-    const uint64_t want = roomy ? std::min<uint64_t>(n_slots, limit) : 1;
-    gx_status r = grow_buf(p, cap, want, 0, limit);
-    if (r == GX_ENOMEM && want > 1) r = grow_buf(p, cap, 1, 0, limit);
-    return r;
-  };
+  uint64_t most = 1;
+  for (uint32_t p = 0; p < net->n_procs; ++p)
+    most = net->procs[p].n_states > n_slots / most ? n_slots : most * net->procs[p].n_states;
+  bool roomy = !fixed && n_slots * state_bytes <= kRoomyBytes;
   for (int k = 0; k < 2; ++k)
-    if ((s = first_buf(&eb.f[k], &eb.f_cap[k], max_cap)) != GX_OK) return s;
-  if ((s = first_buf(&eb.dead, &eb.dead_cap, max_dead)) != GX_OK) return s;
+    if ((s = grow_buf(&eb.f[k], &eb.f_cap[k], 1, 0, max_cap)) != GX_OK) return s;
+  if ((s = grow_buf(&eb.dead, &eb.dead_cap, 1, 0, max_dead)) != GX_OK) return s;
   // a state's successors never exceed a preallocated buffer
   if (fixed && max_succ > eb.succ_cap) return GX_ENOMEM;
   // The first levels run on one workgroup (lds_levels_kernel) while a level
@@ -697,9 +696,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     if (hipMemcpy(eb.mon, mon_mask.data(), mon_mask.size() * sizeof(uint32_t),
                   hipMemcpyHostToDevice) != hipSuccess)
       return GX_EDEVICE;
-    // (room for every state of a table that has buffers of its own size)
-    if (roomy && grow_buf(&eb.viol, &eb.viol_cap, n_slots, 0, ~0ull) == GX_EDEVICE)
-      return GX_EDEVICE;
+    if (roomy && (s = grow_buf(&eb.viol, &eb.viol_cap, 1, 0, ~0ull)) != GX_OK) return s;
     mon_field = ni.field[mp];
     if (opts->monitor_bad[ni.initial[mp]]) {
       init_violates = true;
@@ -766,10 +763,51 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     la.dead_cap = std::min<uint64_t>(eb.dead_cap, max_dead);
     la.first = 0;
     la.ctl = reinterpret_cast<gx::LevelCtl*>(eb.ctr + kCtrWords);
-    la.limit = any_fits && la.cap_out >= n_slots ? ~0ull : la.cap_out / max_succ;
+    la.limit = any_fits && la.cap_out >= most ? ~0ull : la.cap_out / max_succ;
     if (slice_states) la.limit = std::min<uint64_t>(la.limit, slice_states);
-    return (!monitor || eb.viol_cap >= n_slots) && n <= la.limit &&
+    la.viol_cap = monitor ? static_cast<uint32_t>(std::min<uint64_t>(eb.viol_cap, gx::kNoMonitor - 1))
+                          : gx::kNoMonitor;
+    return (!monitor || eb.viol_cap) && n <= la.limit &&
            la.dead_cap - std::min(dead_known, la.dead_cap) >= n;
+  };
+  // Buffers that any level fits, once a level has outgrown the first ones (2^16
+  // states): in one step, as every allocation takes longer than a level (a
+  // first exploration of 3 M states: 1.70 ms with buffers of this size from
+  // the start, 1.76 so, 3.4 in steps of four times the need).  False: no memory
+  // for them.
+  auto make_room = [&]() -> bool {
+    const uint64_t f_want = std::min(most, max_cap), d_want = std::min(most, max_dead);
+    return grow_buf(&eb.f[cur], &eb.f_cap[cur], f_want, n_in, max_cap) == GX_OK &&
+           grow_buf(&eb.f[cur ^ 1], &eb.f_cap[cur ^ 1], f_want, 0, max_cap) == GX_OK &&
+           grow_buf(&eb.dead, &eb.dead_cap, d_want, std::min(dead_known, eb.dead_cap), max_dead) ==
+               GX_OK;
+  };
+  // Searches the level just completed, n_in states of buffer `buf`; if the
+  // record buffer was short, grows it (keeping earlier levels' records) and
+  // searches the level again.
+  auto scan_level = [&](int buf) -> gx_status {
+    const uint64_t prev = viol_total;
+    for (int pass = 0; pass < 2; ++pass) {
+      scan.f[buf] = eb.f[buf];
+      scan.n = n_in;
+      scan.cur = static_cast<uint32_t>(buf);
+      scan.out = eb.viol;
+      scan.cap = eb.viol_cap;
+      scan.level = levels.size() - 1;
+      scan.ctl = nullptr;
+      if (gx::launch_monitor_scan(S, scan, static_cast<uint32_t>(cus), stream) != hipSuccess)
+        return GX_EDEVICE;
+      gx_status r = read_ctr();
+      if (r != GX_OK) return r;
+      viol_total = ctr(gx::kCtrViol);
+      if (viol_total <= eb.viol_cap) break;
+      if ((r = grow_buf(&eb.viol, &eb.viol_cap, viol_total, prev, ~0ull)) != GX_OK) return r;
+      if (hipMemcpy(eb.ctr + gx::kCtrViol * gx::kCtrSpread, &prev, sizeof(prev),
+                    hipMemcpyHostToDevice) != hipSuccess)
+        return GX_EDEVICE;
+    }
+    if (viol_total > prev && opts->stop_on_violation) stop = true;
+    return GX_OK;
   };
   auto launch_link = [&]() -> gx_status {
     if (gx::launch_level_of(t, la, dedup, grid_max, lds, stream) != hipSuccess) return GX_EDEVICE;
@@ -848,7 +886,10 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     const gx::LevelCtl::Entry& e = ctl->entry[entry & 1u];
     n_in = e.n_in;
     cur = static_cast<int>(e.cur);
-    return GX_OK;
+    if (e.scan != gx::kScanHost) return GX_OK;
+    // (room for the levels to come as well, where there is memory for it)
+    if (grow_buf(&eb.viol, &eb.viol_cap, most, viol_total, ~0ull) == GX_EDEVICE) return GX_EDEVICE;
+    return scan_level(cur);
   };
   static_assert(kBlockWords <= gx::kLevelBlock, "one word a thread");
   std::vector<uint64_t> found;
@@ -925,6 +966,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   constexpr uint64_t kMaxRoom = 1ull << 28;  // states of frontier room one slice may claim
   constexpr uint32_t kString = 16;           // launches between read-backs
   while (n_in > 0 && !stop) {
+    if (roomy && !string_args(n_in) && !(slice_states && n_in > slice_states)) roomy = make_room();
     if (string_args(n_in)) {
       la.cur = static_cast<uint32_t>(cur);
       la.n_in = n_in;
@@ -965,7 +1007,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
       auto f_cap = [&]() { return std::min<uint64_t>(eb.f_cap[nxt], max_cap); };
       auto d_cap = [&]() { return std::min<uint64_t>(eb.dead_cap, max_dead); };
       auto f_room = [&]() {
-        return any_fits && f_cap() >= n_slots ? ~0ull : (f_cap() - bound) / max_succ;
+        return any_fits && f_cap() >= most ? ~0ull : (f_cap() - bound) / max_succ;
       };
       // a deadlock buffer at its limit no longer bounds the slice: records
       // past it are counted, not stored, and the call ends with GX_ENOMEM
@@ -979,7 +1021,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
         if (f_room() < want) {
           const uint64_t need = bound + want * max_succ;
           s = grow_buf(&eb.f[nxt], &eb.f_cap[nxt],
-                       any_fits ? std::min<uint64_t>(need, n_slots) : need, tail_known, max_cap);
+                       any_fits ? std::min<uint64_t>(need, most) : need, tail_known, max_cap);
           if (s == GX_ENOMEM)  // no room for a full slice: settle for one state
             s = grow_buf(&eb.f[nxt], &eb.f_cap[nxt], bound + max_succ, tail_known,
                          std::min<uint64_t>(max_cap, bound + max_succ));
@@ -1008,7 +1050,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
           std::min<uint64_t>(grid_max, (run + per_group - 1) / per_group));
       if (gx::launch_level_of(t, la, dedup, grid, lds, stream) != hipSuccess) return GX_EDEVICE;
       pos += run;
-      bound += std::min<uint64_t>(run * max_succ, n_slots);
+      bound += std::min<uint64_t>(run * max_succ, most);
       dead_bound += run;
     }
     if ((s = read_ctr()) != GX_OK) return s;
@@ -1017,30 +1059,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     // (the level's launches have cleared the other tail for the next one)
     la.tail = la.tail == gx::kCtrTail ? gx::kCtrTailAlt : gx::kCtrTail;
     if (n_in) levels.push(n_in);
-    if (monitor && n_in) {
-      // scan the level just completed; if the record buffer was short, grow
-      // it (keeping earlier levels' records) and scan the level again
-      const uint64_t prev = viol_total;
-      for (int pass = 0; pass < 2; ++pass) {
-        scan.f[nxt] = eb.f[nxt];
-        scan.n = n_in;
-        scan.cur = static_cast<uint32_t>(nxt);
-        scan.out = eb.viol;
-        scan.cap = eb.viol_cap;
-        scan.level = levels.size() - 1;
-        scan.ctl = nullptr;
-        if (gx::launch_monitor_scan(S, scan, static_cast<uint32_t>(cus), stream) != hipSuccess)
-          return GX_EDEVICE;
-        if ((s = read_ctr()) != GX_OK) return s;
-        viol_total = ctr(gx::kCtrViol);
-        if (viol_total <= eb.viol_cap) break;
-        if ((s = grow_buf(&eb.viol, &eb.viol_cap, viol_total, prev, ~0ull)) != GX_OK) return s;
-        if (hipMemcpy(eb.ctr + gx::kCtrViol * gx::kCtrSpread, &prev, sizeof(prev),
-                      hipMemcpyHostToDevice) != hipSuccess)
-          return GX_EDEVICE;
-      }
-      if (viol_total > prev && opts->stop_on_violation) stop = true;
-    }
+    if (monitor && n_in && (s = scan_level(nxt)) != GX_OK) return s;
     cur = nxt;
   }
   if (monitor && !init_violates && viol_total)
@@ -1186,7 +1205,7 @@ gx_status gx_explore_noalloc(const gx_network* net, gx_table* t, const gx_explor
   constexpr uint64_t kRegion = (GX_NOALLOC_SCRATCH_BYTES - kCtl - 256) / 4 / 256 * 256;
   static_assert(kCtl + 256 + 4 * kRegion <= GX_NOALLOC_SCRATCH_BYTES, "scratch layout");
   const uint64_t cap = kRegion / (t->S * sizeof(uint32_t));
-  static thread_local uint64_t host_block[(gx::kControlBytes + 7) / 8];
+  alignas(64) static thread_local uint64_t host_block[(gx::kControlBytes + 7) / 8];
   gx_explore_buffers eb;  // views of the scratch array; never grown
   eb.ctr = reinterpret_cast<uint64_t*>(base);
   eb.ctr_host = host_block;

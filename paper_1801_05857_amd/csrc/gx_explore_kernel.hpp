@@ -550,6 +550,11 @@ static_assert(kCntStored == 0 && kCntLookups == 1 && kCntProbes == 2 && kCntFull
 constexpr uint32_t kLevelBlock = 512;  // threads per workgroup
 constexpr uint32_t kChainLevels = 64;  // level sizes a control block holds
 
+// A level yet to be searched for violations: by the scan that follows the
+// launch, or (more states than the buffer has room for records) by the host.
+constexpr uint32_t kScanHere = 1, kScanHost = 2;
+constexpr uint32_t kNoMonitor = 0xFFFFFFFFu;
+
 // What the device leaves for the host between read-backs (after the level
 // counters).
 struct LevelCtl {
@@ -558,14 +563,14 @@ struct LevelCtl {
   uint64_t cur;          // the frontier buffer holding it
   uint64_t init_status;  // find-or-put status of the initial state (when inserted)
   uint64_t log_n;        // LDS-resident launch: states it logged (they go into the table)
-  uint64_t pad[3];
   // levels strung together: launch k of a string reads entry k & 1 and leaves
   // the next level in the other one, so that a workgroup that starts late
-  // still finds the entry of its own launch
-  struct Entry {
+  // still finds the entry of its own launch (read in one piece)
+  struct alignas(64) Entry {
     uint64_t n_in, cur, n_levels;
     uint32_t go;     // the exploration's number if the device may expand it, else 0
     uint32_t fresh;  // found by the launch that wrote the entry
+    uint32_t scan;   // with a monitor, who searches the level: kScanHere, kScanHost or 0
   } entry[2];
   uint64_t levels[kChainLevels];
 };
@@ -603,6 +608,7 @@ struct LevelArgs {
   uint64_t* report;
   uint64_t* host_block;
   uint32_t block_words;
+  uint32_t viol_cap;  // records the violation buffer takes; kNoMonitor: no monitor
 };
 
 // What a launch reports: its link plus one (16 bits), whether it expands the
@@ -668,8 +674,10 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
         // entry written since has another exploration's number.)
         if (blockIdx.x == 0) {
           if (threadIdx.x == 0) {
-            a.ctl->entry[(a.link & 1u) ^ 1u] = e;
-            a.ctl->entry[(a.link & 1u) ^ 1u].fresh = 0;
+            LevelCtl::Entry& next = a.ctl->entry[(a.link & 1u) ^ 1u];
+            next = e;
+            next.fresh = 0;
+            if (e.scan == kScanHere) next.scan = 0;
           }
           if (a.report != nullptr) {
             copy_to_host(a.host_block, a.ctr, a.block_words);
@@ -727,15 +735,20 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
     auto* tail = ctr_at(a.ctr, a.tail);
     const uint64_t n_next = (before & kTailMask) + n_new;
     __hip_atomic_store(tail, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    uint64_t flags = __hip_atomic_load(ctr_at(a.ctr, kCtrFlags), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+    auto counter = [&](uint32_t k) {
+      return __hip_atomic_load(ctr_at(a.ctr, k), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    uint64_t flags = counter(kCtrFlags);
+    const uint64_t dead = counter(kCtrDead);
+    const bool monitor = a.viol_cap != kNoMonitor;
+    const uint64_t viol = monitor ? counter(kCtrViol) : 0;
+    uint64_t n_levels = a.ctl->entry[a.link & 1u].n_levels;
+    if (a.given) n_levels = 0;
     if (n_next > a.cap_out) {
       atomicOr(ctr_at(a.ctr, kCtrFlags), static_cast<unsigned long long>(kFlagFrontierOverflow));
       flags |= kFlagFrontierOverflow;
     }
-    const uint64_t dead = __hip_atomic_load(ctr_at(a.ctr, kCtrDead), __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT);
-    uint64_t n_levels = a.given ? 0 : a.ctl->entry[a.link & 1u].n_levels;
+    const bool recorded = !monitor || viol + n_next <= a.viol_cap;
     if (n_next) {
       if (a.report == nullptr) a.ctl->levels[n_levels] = n_next;
       ++n_levels;
@@ -745,7 +758,8 @@ __global__ __launch_bounds__(kLevelBlock) void level_kernel(LevelArgs a) {
     e.cur = cur ^ 1u;
     e.n_levels = n_levels;
     e.fresh = flags == 0;
-    e.go = flags == 0 && n_next > 0 && n_next <= a.limit &&
+    e.scan = !monitor || flags != 0 || n_next == 0 ? 0u : recorded ? kScanHere : kScanHost;
+    e.go = flags == 0 && n_next > 0 && n_next <= a.limit && recorded &&
                    (a.report != nullptr || n_levels < kChainLevels) && n_next <= a.dead_cap - min(dead, a.dead_cap)
                ? a.number
                : 0u;

@@ -336,6 +336,7 @@ __global__ __launch_bounds__(small_threads<S>()) void lds_levels_kernel(SmallArg
                ? a.number
                : 0u;
     e.fresh = 0;  // (the level's size is among those above)
+    e.scan = 0;   // (no monitor)
     if (sh_trans) atomicAdd(ctr_at(a.ctr, kCtrTrans), sh_trans);
     if (dead) atomicAdd(ctr_at(a.ctr, kCtrDead), static_cast<unsigned long long>(dead));
   }

@@ -453,21 +453,25 @@ gx_status gx_table_dump(gx_table* t, uint32_t* host_keys, uint64_t cap, uint64_t
         *n_out = count;
         return GX_ENOMEM;
       }
-      // (the frontier buffers, which no exploration is using)
+      // the frontier buffers, which no exploration is using, where they are
+      // large enough, else memory for the call alone
+      uint32_t* list[2] = {nullptr, nullptr};
+      bool own[2] = {false, false};
       bool room = count < (uint64_t(1) << 32);
       for (int k = 0; k < 2 && room; ++k) {
-        if (e.f_cap[k] >= count && e.f[k]) continue;
-        if (e.f[k]) (void)hipFree(e.f[k]);
-        e.f[k] = nullptr;
-        e.f_cap[k] = 0;
-        room = hipMalloc(&e.f[k], std::max<uint64_t>(count, 1) * t->S * sizeof(uint32_t)) ==
-               hipSuccess;
-        if (room) e.f_cap[k] = std::max<uint64_t>(count, 1);
-        else (void)hipGetLastError();
+        if (e.f_cap[k] >= count && e.f[k]) {
+          list[k] = e.f[k];
+          continue;
+        }
+        own[k] = room = hipMalloc(&list[k], std::max<uint64_t>(count, 1) * t->S *
+                                                sizeof(uint32_t)) == hipSuccess;
+        if (!room) (void)hipGetLastError();
       }
-      if (room) s = gx::gather_keys(t->S, t->words, n_slots, e.f[0], count, e.sort, &count, nullptr);
+      if (room) s = gx::gather_keys(t->S, t->words, n_slots, list[0], count, e.sort, &count, nullptr);
       if (room && s == GX_OK)
-        s = gx::sort_gathered(t->S, t->w, e.f[0], e.f[1], count, e.sort, host_keys, nullptr);
+        s = gx::sort_gathered(t->S, t->w, list[0], list[1], count, e.sort, host_keys, nullptr);
+      for (int k = 0; k < 2; ++k)
+        if (own[k]) (void)hipFree(list[k]);
       if (room && s == GX_OK) {
         *n_out = count;
         return GX_OK;
