@@ -417,7 +417,7 @@ const char* gx_status_str(gx_status status);
  * with its own table partition carved from one allocation per kernel class.
  * Every instance follows exactly the single-exploration semantics of
  * gx_explore (Sec. 3).  Instances that share a kernel configuration (slot
- * words, bucket words, subgroup, keys per subgroup) form a class.  Two
+ * words and bucket words) form a class.  Two
  * schedules:
  *   stepped (the default): every unfinished instance advances one BFS level
  *     per step; a step is one launch per class over the current levels of
@@ -447,7 +447,9 @@ typedef struct {
                                  else 8|16|32|64                              */
   uint32_t subgroup;          /* 0 -> autotuned per instance, else 4|8|16
                                  (4 with buckets of at most 32 words; an
-                                 explicit 4 caps an autotuned bucket at 32)   */
+                                 explicit 4 caps an autotuned bucket at 32).
+                                 As keys_per_subgroup only reported: batches
+                                 probe with 4 lanes, four keys in flight      */
   uint32_t keys_per_subgroup; /* 0 -> 1, else 1|2                             */
   uint32_t use_graph;         /* nonzero: the persistent schedule, and
                                  gx_batch_create captures a whole run (clears,
@@ -502,26 +504,27 @@ gx_status gx_explore_batch(const gx_network* nets, uint32_t n, const gx_batch_op
                            gx_explore_result* outs, gx_status* inst_status);
 
 /*
- * Autotuner: the kernel configuration (bucket words, subgroup; one key in
- * flight per subgroup, as the exploration kernels keep) for tables of
- * words_per_state-word states filled to load_factor (0 < load_factor <=
+ * Autotuner: the bucket size, and the narrowest subgroup it allows, for tables
+ * of words_per_state-word states filled to load_factor (0 < load_factor <=
  * 0.95), per size class of the table's capacity (up to 2^16, 2^20, 2^24
  * states, and larger: the class decides whether its buckets live in an
  * XCD's L2, the last-level cache or HBM).  The first call for a (slot words,
- * load, size class) times every candidate (B in 8..64, subgroup 4 (B <= 32),
- * 8 or 16) on a stream shaped like an exploration's successor lookups (every
- * distinct key about 8 times, shuffled; at least 2^25 keys per measurement,
- * the median of three) into a table at the top of the class, and picks the
- * fastest, except that the default (B = 16, subgroup 4) is kept when it is
+ * load, size class) times every bucket size (8..64 words) with the probes of
+ * explorations, batches and the server (4 lanes, four keys in flight, whatever
+ * a table's subgroup is) on a stream shaped like an exploration's successor
+ * lookups (every distinct key about 8 times, shuffled; at least 2^25 keys per
+ * measurement, the median of three) into a table at the top of the class, and
+ * picks the fastest, except that the default (16 words) is kept when it is
  * within 3% of the fastest; later calls return the cached choice.
  * Synchronous.
  */
 typedef struct {
   uint32_t bucket_words, subgroup, keys_per_subgroup;
-  uint32_t candidates;         /* configurations timed                        */
+  uint32_t candidates;         /* configurations compared (those of one bucket
+                                  size share a time)                          */
   double ns_per_key;           /* the pick's time per key                     */
   double ns_per_key_default;   /* the default's (B = 16, subgroup 4)          */
-  double ns_per_key_runner_up; /* the fastest candidate other than the pick:
+  double ns_per_key_runner_up; /* the fastest other bucket size:
                                   the decision margin is runner_up / pick - 1
                                   (negative when a near-tie kept the default) */
   uint64_t table_slots;        /* size of the timed table                     */
@@ -567,8 +570,9 @@ typedef struct {
   uint64_t hash_seed;         /* 0 -> the default seed                         */
   uint32_t bucket_words;      /* 0 -> autotuned per slot width, else 8..64     */
   uint32_t subgroup;          /* 0 -> autotuned, else 4|8|16 (4 with buckets
-                                 of at most 32 words)                         */
-  uint32_t keys_per_subgroup; /* 0 -> 1, else 1|2                             */
+                                 of at most 32 words); checked, but the server
+                                 probes with 4 lanes, four keys in flight     */
+  uint32_t keys_per_subgroup; /* 0 -> 1, else 1|2; as subgroup                */
   uint32_t keep_states;       /* nonzero: a completed request's result also
                                  holds its reachable states (its table's
                                  contents, read before the table is released)

@@ -93,7 +93,7 @@ struct TuneKey {
 };
 std::map<TuneKey, gx_tune_info> g_tuned;
 std::mutex g_tune_mutex;
-constexpr uint32_t kDefaultB = 16, kDefaultG = 4;  // kept unless beaten by > 3%
+constexpr uint32_t kDefaultB = 16;  // kept unless beaten by > 3%
 
 __global__ void tune_keys_kernel(uint32_t* keys, uint32_t S, uint64_t n, uint64_t n_distinct,
                                  uint64_t seed) {
@@ -114,7 +114,7 @@ constexpr uint32_t kSteps = 16;  // steps of a class between read-backs
 
 struct gx_batch {
   struct Class {
-    uint32_t S = 0, B = 0, G = 0, U = 0;
+    uint32_t S = 0, B = 0;
     std::vector<uint32_t> members;  // instance ids
     // device
     gx::BatchInst* inst = nullptr;
@@ -157,7 +157,7 @@ struct gx_batch {
   uint64_t seed = 0;
   uint32_t H = 8;
   std::vector<uint32_t> w, cls;  // per instance: words, class index
-  std::vector<uint32_t> Bi, Gi, Ui;
+  std::vector<uint32_t> Bi, Gi, Ui;  // the configuration reported per instance
   std::vector<uint64_t> tab_off, tab_words;  // per instance: its table partition in its class
   bool keep_states = false;
   gx::SortSpace sort;
@@ -431,16 +431,16 @@ bool valid_pow2(uint32_t x, uint32_t lo, uint32_t hi) {
   return x >= lo && x <= hi && (x & (x - 1)) == 0;
 }
 
-// Times every candidate (B in 8..64 words, subgroup 4 (B <= 32), 8 or 16; one
-// key in flight per subgroup, as the exploration kernels keep) on a stream
-// shaped like an exploration's successor lookups: every distinct key about
-// dup times, shuffled, into a table of the class's size filled to `load` by
-// the end.  One measurement runs the stream r times back to back (clearing
-// the table before each run; the clears are timed alone and subtracted), at
-// least 2^25 keys in all; a candidate's time is the median of three
-// measurements.  The pick is the fastest candidate, unless the default
-// (B = 16, subgroup 4) is within 3% of it: near-ties keep the default, so
-// that run-to-run noise does not flip the choice.
+// Times every bucket size (8..64 words) with the probes that explorations,
+// batches and the server make whatever a table's subgroup is: 4 lanes, four
+// keys in flight, buckets read 64 bytes at a time.  The stream is shaped like
+// an exploration's successor lookups: every distinct key about dup times,
+// shuffled, into a table of the class's size filled to `load` by the end.  One
+// measurement runs the stream r times back to back (clearing the table before
+// each run; the clears are timed alone and subtracted), at least 2^25 keys in
+// all; a bucket size's time is the median of three measurements.  The pick is
+// the fastest, unless the default (16 words) is within 3% of it: near-ties
+// keep the default, so that run-to-run noise does not flip the choice.
 gx_status tune_class(uint32_t S, double load, uint32_t sc, gx_tune_info* out) {
   // capacity (states) of the timed table: the top of the class (2^25 for the
   // open-ended last class)
@@ -484,41 +484,41 @@ gx_status tune_class(uint32_t S, double load, uint32_t sc, gx_tune_info* out) {
            hipEventElapsedTime(ms, e0, e1) == hipSuccess;
   };
   struct Cand {
-    uint32_t B, G;
+    uint32_t B;
     double ns;
   };
+  uint32_t configs = 0;  // (bucket, subgroup) pairs the times stand for
   std::vector<Cand> cands;
   gx_status st = GX_OK;
   for (uint32_t B : {8u, 16u, 32u, 64u}) {
     if (B < S * 2) continue;
-    for (uint32_t G : {4u, 8u, 16u}) {
-      if (G == 4 && B > 32) continue;
-      gx_table_opts o{0, 64, G, 1, 0};
-      gx_table* t = nullptr;
-      if (gx_table_create(S, B, slots, &o, &t) != GX_OK) {
-        st = GX_ENOMEM;
-        continue;
-      }
-      float clear_ms = 0, ms[3] = {0, 0, 0};
-      bool ok = time_runs(t, false, &ms[0]);  // warm-up
-      ok = ok && time_runs(t, true, &clear_ms);
-      for (int m = 0; m < 3 && ok; ++m) ok = time_runs(t, false, &ms[m]);
-      gx_table_destroy(t);
-      if (!ok) {
-        st = GX_EDEVICE;
-        continue;
-      }
-      std::sort(ms, ms + 3);
-      const double work = std::max(1e-6, static_cast<double>(ms[1] - clear_ms));
-      cands.push_back({B, G, work * 1e6 / static_cast<double>(reps * n)});
+    gx_table_opts o{0, 64, 8, 1, 0};
+    gx_table* t = nullptr;
+    if (gx_table_create(S, B, slots, &o, &t) != GX_OK) {
+      st = GX_ENOMEM;
+      continue;
     }
+    t->G = 4;
+    float clear_ms = 0, ms[3] = {0, 0, 0};
+    bool ok = time_runs(t, false, &ms[0]);  // warm-up
+    ok = ok && time_runs(t, true, &clear_ms);
+    for (int m = 0; m < 3 && ok; ++m) ok = time_runs(t, false, &ms[m]);
+    gx_table_destroy(t);
+    if (!ok) {
+      st = GX_EDEVICE;
+      continue;
+    }
+    std::sort(ms, ms + 3);
+    const double work = std::max(1e-6, static_cast<double>(ms[1] - clear_ms));
+    cands.push_back({B, work * 1e6 / static_cast<double>(reps * n)});
+    configs += B <= 32 ? 3 : 2;  // subgroups of 4 (not with 64 words), 8 and 16
   }
   cleanup();
   if (cands.empty()) return st == GX_OK ? GX_EDEVICE : st;
   size_t best = 0, def = cands.size();
   for (size_t k = 0; k < cands.size(); ++k) {
     if (cands[k].ns < cands[best].ns) best = k;
-    if (cands[k].B == kDefaultB && cands[k].G == kDefaultG) def = k;
+    if (cands[k].B == kDefaultB) def = k;
   }
   size_t pick = best;
   if (def < cands.size() && cands[def].ns <= cands[best].ns * 1.03) pick = def;
@@ -526,9 +526,9 @@ gx_status tune_class(uint32_t S, double load, uint32_t sc, gx_tune_info* out) {
   for (size_t k = 0; k < cands.size(); ++k)
     if (k != pick && (runner == 0 || cands[k].ns < runner)) runner = cands[k].ns;
   out->bucket_words = cands[pick].B;
-  out->subgroup = cands[pick].G;
+  out->subgroup = cands[pick].B <= 32 ? 4 : 8;  // (the narrowest a table may have)
   out->keys_per_subgroup = 1;
-  out->candidates = static_cast<uint32_t>(cands.size());
+  out->candidates = configs;
   out->ns_per_key = cands[pick].ns;
   out->ns_per_key_default = def < cands.size() ? cands[def].ns : 0.0;
   out->ns_per_key_runner_up = runner;
@@ -638,8 +638,6 @@ gx_status gx_batch_create(const gx_network* nets, uint32_t n, const gx_batch_opt
       }
       B = B ? B : ti.bucket_words;
       G = G ? G : ti.subgroup;
-      // one key in flight per subgroup unless asked: more keys in flight cost
-      // the exploration kernels a wave per SIMD of occupancy
       U = U ? U : 1;
       gx::fit_subgroup(&B, &G, opts->bucket_words != 0);
     }
@@ -651,15 +649,13 @@ gx_status gx_batch_create(const gx_network* nets, uint32_t n, const gx_batch_opt
     uint32_t k = 0;
     for (; k < b->classes.size(); ++k) {
       const auto& c = b->classes[k];
-      if (c.S == S && c.B == B && c.G == G && c.U == U) break;
+      if (c.S == S && c.B == B) break;
     }
     if (k == b->classes.size()) {
       b->classes.emplace_back();
       auto& c = b->classes.back();
       c.S = S;
       c.B = B;
-      c.G = G;
-      c.U = U;
     }
     b->classes[k].members.push_back(i);
     b->cls[i] = k;

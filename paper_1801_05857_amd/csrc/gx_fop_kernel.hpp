@@ -152,9 +152,7 @@ hipError_t dispatch_g(uint32_t G, uint32_t U, const FopArgs& a) {
   // load 0.5: 5.2 -> 9.8 us for 4096 keys).
   if (B <= 32 && a.n <= static_cast<uint64_t>(a.cus) * kLanesPerCu) G = 4;
   switch (G) {
-    case 4:
-      if constexpr (B <= 32) return dispatch_u<S, B, 4>(U, a);
-      break;
+    case 4: return dispatch_u<S, B, 4>(U, a);  // (64-word buckets: the autotuner only)
     case 8: return dispatch_u<S, B, 8>(U, a);
     case 16: return dispatch_u<S, B, 16>(U, a);
     case 32: return dispatch_u<S, B, 32>(U, a);

@@ -623,10 +623,6 @@ gx_status gx_server_create(const gx_server_opts* opts, gx_server** out) {
       }
       B = B ? B : tb;
       G = G ? G : tg;
-      // one key in flight per subgroup unless asked: the autotuner times the
-      // isolated find-or-put, where more keys in flight pay off, but in the
-      // exploration kernels they cost a wave per SIMD of occupancy
-      (void)tu;
       U = U ? U : 1;
       gx::fit_subgroup(&B, &G, opts->bucket_words != 0);
     }

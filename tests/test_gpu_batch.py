@@ -224,3 +224,16 @@ def test_batch_tunes_for_the_combined_footprint(dev):
             assert b.instance_config(i) == (t["bucket_words"], t["subgroup"], 1)
         b.run()
         _check(b.results(), [oracle.explore(n) for n in nets])
+
+
+@pytest.mark.parametrize("w", [1, 2, 3])
+@pytest.mark.parametrize("cap", [1 << 14, 1 << 19, 1 << 23])
+def test_autotune_compares_bucket_sizes(dev, w, cap):
+    """Explorations probe with four lanes whatever a table's subgroup is, so a
+    pick is a bucket size with the narrowest subgroup a table of it may have,
+    and the runner-up is another bucket size: a time of its own."""
+    t = gx.autotune_capacity(w, cap)
+    assert t["subgroup"] == (4 if t["bucket_words"] <= 32 else 8)
+    assert t["ns_per_key_runner_up"] != t["ns_per_key"]
+    if t["bucket_words"] == 16:
+        assert t["ns_per_key_runner_up"] * 1.03 >= t["ns_per_key"]
