@@ -4,11 +4,12 @@
 // instances are not synchronised with each other.
 //
 // Work queue: an append-only array of level entries {instance, tiles}.  A
-// workgroup claims one tile (256 frontier states) of the oldest entry that
-// still has unclaimed tiles, expands it (the same per-wavefront routine as
-// the single-exploration level kernel) and counts it finished; the workgroup
-// that finishes the last tile of a level publishes the instance's next level
-// as a new entry (or marks the instance done).  Frontier data written by many
+// workgroup claims one tile (256 frontier states), or up to eight at once of a
+// level that has many, of the oldest entry that still has unclaimed ones,
+// expands them (the same per-wavefront routine as the single-exploration level
+// kernel) and counts them finished; the workgroup that finishes the last tile
+// of a level publishes the instance's next level as a new entry (or marks the
+// instance done).  Frontier data written by many
 // workgroups is published with agent-scope release fences before the finish
 // count and read after agent-scope acquire fences.
 //

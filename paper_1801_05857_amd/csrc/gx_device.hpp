@@ -8,9 +8,13 @@
 // kEmpty, so a slot is EMPTY (every word kEmpty), FINAL (no word kEmpty) or,
 // transiently, PARTIAL.
 //
-// Probe (one subgroup of G lanes per key, G in {8,16,32,64}; the paper uses a
-// warp of 32 per bucket of 32 integers, and groups of B threads for buckets of
-// B integers, Sec. 4.2):
+// Probe.  Explorations, batches, the server, small find-or-put launches and
+// tables of subgroup 4 probe with 4 lanes, the four keys of a subgroup in
+// flight together and a bucket read 64 bytes at a time (find_or_put_quads).
+// Large find-or-put launches on wider tables take a subgroup of G lanes, G in
+// {8,16,32,64}, for each key, and 1 to 8 keys in flight (find_or_put; the paper
+// uses a warp of 32 per bucket of 32 integers, and groups of B threads for
+// buckets of B integers, Sec. 4.2):
 //   * the first GE = min(G, B) lanes each load K = B/GE consecutive words of
 //     the bucket (one coalesced access of B*4 bytes per bucket);
 //   * every lane compares its words with the key; ballots give per-slot
@@ -18,9 +22,10 @@
 //   * match -> SEEN.  Otherwise the lane owning the lowest EMPTY slot tries a
 //     compare-and-swap of the key into it (32-bit for S = 1, 64-bit for S = 2,
 //     64-bit on words 0-1 for S = 4 followed by a store of words 2-3); a
-//     failed CAS that returned the key -> SEEN, any other failure -> re-read
-//     the bucket; no EMPTY slot -> next hash function (Sec. 4.1); after H
-//     buckets -> FULL.
+//     failed CAS that returned the key -> SEEN, any other failure -> the next
+//     EMPTY slot of the view; no EMPTY slot -> next hash function (Sec. 4.1);
+//     after H buckets -> FULL.
+// Both claim by the same rules, so their keys may meet in one table.
 //
 // Memory-model argument (why relaxed atomics are enough): every slot word is
 // written exactly once, from kEmpty to its final value, and no reader derives
@@ -145,7 +150,7 @@ template <int S, int B, int G>
 struct Geo {
   static_assert(S == 1 || S == 2 || S == 4, "slot words");
   static_assert(B == 4 || B == 8 || B == 16 || B == 32 || B == 64, "bucket words");
-  static_assert(G == 4 || G == 8 || G == 16 || G == 32 || G == 64, "subgroup width");
+  static_assert(G == 8 || G == 16 || G == 32 || G == 64, "subgroup width");
   static_assert(B / (G < B ? G : B) <= 8, "at most 8 bucket words per lane");
   static constexpr int GE = G < B ? G : B;          // lanes holding bucket words
   static constexpr int K = B / GE;                  // words per lane

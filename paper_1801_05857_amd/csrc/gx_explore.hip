@@ -612,7 +612,7 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     if ((s = grow_buf(&eb.f[k], &eb.f_cap[k], 1, 0, max_cap)) != GX_OK) return s;
   if ((s = grow_buf(&eb.dead, &eb.dead_cap, 1, 0, max_dead)) != GX_OK) return s;
   // a state's successors never exceed a preallocated buffer
-  if (fixed && max_succ > eb.succ_cap) return GX_ENOMEM;
+  if (fixed && max_succ > eb.log_cap) return GX_ENOMEM;
   // The first levels run on one workgroup (lds_levels_kernel) while a level
   // of `small_limit` states has room for all its successors in the frontier
   // buffer and the log; not with a safety monitor or the local duplicate
@@ -620,10 +620,10 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
   const bool dedup = opts && opts->local_dedup;
   uint64_t small_limit = 0;
   if (!monitor && !dedup && !global_img) {
-    if ((s = grow_buf(&eb.succ, &eb.succ_cap, 1, 0, ~0ull)) != GX_OK) return s;
+    if ((s = grow_buf(&eb.log, &eb.log_cap, 1, 0, ~0ull)) != GX_OK) return s;
     const uint64_t room = std::min<uint64_t>(
         std::min<uint64_t>(eb.f_cap[0], eb.f_cap[1]),
-        std::min<uint64_t>(eb.succ_cap, max_cap));
+        std::min<uint64_t>(eb.log_cap, max_cap));
     small_limit = std::min<uint64_t>(
         gx::kSmallMaxLevel, std::min<uint64_t>(room, gx::kSmallSuccBudget) / max_out);
   }
@@ -901,8 +901,8 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     sa.img_words = img_words;
     sa.img_stride = img_stride;
     sa.f = eb.f[0];
-    sa.log = eb.succ;
-    sa.log_cap = eb.succ_cap;
+    sa.log = eb.log;
+    sa.log_cap = eb.log_cap;
     sa.dead = eb.dead;
     sa.dead_cap = std::min<uint64_t>(eb.dead_cap, max_dead);
     sa.ctr = eb.ctr;
@@ -1200,7 +1200,7 @@ gx_status gx_explore_noalloc(const gx_network* net, gx_table* t, const gx_explor
   if (dev != t->device) return GX_EINVAL;
   char* base = static_cast<char*>(gx::scratch_address(dev));
   if (!base) return GX_EDEVICE;
-  // control block | status | frontier 0 | frontier 1 | successors | deadlocks
+  // control block | status | frontier 0 | frontier 1 | log | deadlocks
   constexpr uint64_t kCtl = (gx::kControlBytes + 65535) / 65536 * 65536;
   constexpr uint64_t kRegion = (GX_NOALLOC_SCRATCH_BYTES - kCtl - 256) / 4 / 256 * 256;
   static_assert(kCtl + 256 + 4 * kRegion <= GX_NOALLOC_SCRATCH_BYTES, "scratch layout");
@@ -1213,9 +1213,9 @@ gx_status gx_explore_noalloc(const gx_network* net, gx_table* t, const gx_explor
   char* r = base + kCtl + 256;
   eb.f[0] = reinterpret_cast<uint32_t*>(r);
   eb.f[1] = reinterpret_cast<uint32_t*>(r + kRegion);
-  eb.succ = reinterpret_cast<uint32_t*>(r + 2 * kRegion);
+  eb.log = reinterpret_cast<uint32_t*>(r + 2 * kRegion);
   eb.dead = reinterpret_cast<uint32_t*>(r + 3 * kRegion);
-  eb.f_cap[0] = eb.f_cap[1] = eb.succ_cap = eb.dead_cap = cap;
+  eb.f_cap[0] = eb.f_cap[1] = eb.log_cap = eb.dead_cap = cap;
   gx::FixedOut f{level_counts, max_levels, deadlocks, max_deadlocks, out};
   gx_explore_result unused{};
   return explore_impl(net, t, opts, eb, &f, &unused);

@@ -97,9 +97,11 @@ hipError_t launch_fop(const FopArgs& a) {
   const uint64_t resident =
       static_cast<uint64_t>(a.cus) * static_cast<uint32_t>(per_cu) * (kBlock / block);
   // Long launches come as more workgroups than are resident, of 16 rounds or
-  // more each, so that those done early make room for others: 2^27 keys into
-  // 1 GiB of 32-word buckets and 2^27 more take 11.05 ms with the resident
-  // ones alone, 10.87 with 16 times as many; 2e6 keys gain nothing (192 us).
+  // more each, so that those done early make room for others: keys with long
+  // hash chains hold up their wavefront.  2^26 two-word keys found in 32-word
+  // buckets by 4 lanes, resident workgroups alone and 16 times as many: 1515
+  // and 1447 us half full, 6.4 and 4.2 ms full; by 8 lanes 1537 and 1494 us, 9.6
+  // and 7.5 ms.  2e6 keys gain nothing (192 us).
   const uint64_t over = std::max<uint64_t>(1, std::min<uint64_t>(16, a.n / (resident * block * 16)));
   uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>(want, resident * over));
   if (grid == 0) grid = 1;

@@ -57,12 +57,13 @@ struct gx_explore_buffers {
   uint64_t f_cap[2] = {0, 0};  // states
   uint32_t* dead = nullptr;
   uint64_t dead_cap = 0;  // states
-  uint32_t* succ = nullptr;  // successors of a level slice, before the table probe
-  uint64_t succ_cap = 0;     // states
+  uint32_t* log = nullptr;   // the first levels' states, as one workgroup found them
+  uint64_t log_cap = 0;      // states
   // control block (device) and its pinned host mirror: the level counters
-  // (one cache line each) and what a small-level launch reports, then the
-  // initial state's slot and the network image; one copy up per exploration,
-  // the counters' part read back after every level
+  // (one cache line each) and what the device leaves for the host (LevelCtl),
+  // then the initial state's slot and the network image; one copy up per
+  // exploration, the counters' part copied back by the last launch of a string
+  // of levels (or read back where the host launches a level's slices)
   uint64_t* ctr = nullptr;
   uint64_t* ctr_host = nullptr;
   uint64_t* report = nullptr;  // host memory that level launches write (level_report)

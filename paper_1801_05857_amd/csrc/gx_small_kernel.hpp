@@ -72,30 +72,26 @@ __device__ inline bool lds_set_insert(uint32_t* set, uint32_t mask, const uint32
       done = fresh || old == key[0];
       h = (h + 1) & mask;
     }
-    return fresh;
-  }
-  while (__ballot(!done)) {
-    if (!done) {
-      uint32_t* e = set + h * S;
-      const uint32_t w0 = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      if (w0 == kEmpty) {
-        uint32_t expect = kEmpty;
-        if (__hip_atomic_compare_exchange_strong(e, &expect, S == 1 ? key[0] : kLocked,
-                                                 __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_WORKGROUP)) {
-          if constexpr (S > 1) {
+  } else {
+    while (__ballot(!done)) {
+      if (!done) {
+        uint32_t* e = set + h * S;
+        const uint32_t w0 = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (w0 == kEmpty) {
+          uint32_t expect = kEmpty;
+          if (__hip_atomic_compare_exchange_strong(e, &expect, kLocked, __ATOMIC_RELAXED,
+                                                   __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP)) {
 #pragma unroll
             for (int x = 1; x < S; ++x)
               __hip_atomic_store(e + x, key[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             __hip_atomic_store(e, key[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            fresh = true;
+            done = true;
           }
-          fresh = true;
-          done = true;
-        }
-      } else if (w0 != kLocked) {
-        bool same = w0 == key[0];
-        if constexpr (S > 1) {
+        } else if (w0 != kLocked) {
+          bool same = w0 == key[0];
           if (same) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 #pragma unroll
@@ -103,11 +99,11 @@ __device__ inline bool lds_set_insert(uint32_t* set, uint32_t mask, const uint32
               same &= __hip_atomic_load(e + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) ==
                       key[x];
           }
+          if (same)
+            done = true;
+          else
+            h = (h + 1) & mask;
         }
-        if (same)
-          done = true;
-        else
-          h = (h + 1) & mask;
       }
     }
   }

@@ -162,7 +162,7 @@ void free_table(gx_table* t) {
   gx_explore_buffers& e = t->eb;
   // (e.key and e.img live in e.ctr's allocation, the control block)
   for (void* p : {static_cast<void*>(e.f[0]), static_cast<void*>(e.f[1]),
-                  static_cast<void*>(e.dead), static_cast<void*>(e.succ),
+                  static_cast<void*>(e.dead), static_cast<void*>(e.log),
                   static_cast<void*>(e.ctr), static_cast<void*>(e.status),
                   static_cast<void*>(e.mon), static_cast<void*>(e.viol),
                   static_cast<void*>(e.img_global)})
