@@ -86,10 +86,19 @@ def parse():
     return ap.parse_args()
 
 
-def algorithmic_bytes_per_op(w: int, B: int, probes_per_op: float, new_frac: float) -> float:
-    """Key read + status write + one granule-rounded bucket read per probe +
-    the write-back of the claimed granule for new keys."""
-    return 4 * w + 1 + probes_per_op * max(4 * B, GRANULE) + new_frac * GRANULE
+def probe_bytes(B: int, G: int = 4) -> int:
+    """Bytes a probe of a bucket of B words cannot do without: 4-lane probes
+    (every exploration's, whatever the table's subgroup) read a bucket 64
+    bytes at a time and most end in the first piece, which is what is counted;
+    wider subgroups read it whole."""
+    return GRANULE if G == 4 else max(4 * B, GRANULE)
+
+
+def algorithmic_bytes_per_op(w: int, B: int, G: int, probes_per_op: float,
+                             new_frac: float) -> float:
+    """Key read + status write + the bucket reads + the write-back of the
+    claimed granule for new keys."""
+    return 4 * w + 1 + probes_per_op * probe_bytes(B, G) + new_frac * GRANULE
 
 
 def run_fop_sub_batches(gx, torch, keys, n_distinct, B, G, U, alpha, H, sub):
@@ -367,11 +376,10 @@ def cpu_batch_all_cores(W, budget_s: float = 10.0):
 
 
 def explore_bytes_per_state(f: float, B: int, S: int) -> float:
-    """Algorithmic HBM bytes per explored state: f bucket probes (of at least
-    a 64-byte granule) for its successors, the state is read from its
-    frontier and written to the next one (4S bytes each way), and its claim
-    writes back one granule."""
-    return f * max(4 * B, GRANULE) + 2 * 4 * S + GRANULE
+    """Algorithmic HBM bytes per explored state: f bucket probes for its
+    successors, the state is read from its frontier and written to the next
+    one (4S bytes each way), and its claim writes back one granule."""
+    return f * probe_bytes(B) + 2 * 4 * S + GRANULE
 
 
 def roofline_of(states: int, bytes_per_state_total: float, seconds: float,
@@ -425,9 +433,10 @@ def run_explore_leg(gx, torch, W, live=8, slots=None):
            "states": r.n_states, "transitions": r.n_transitions, "levels": len(r.levels),
            "seconds": round(dt, 4), "cold_seconds": round(cold, 4),
            "states_per_s": round(r.n_states / dt),
-           "lookups_per_s": round(r.n_transitions / dt),
+           "transitions_per_s": round(r.n_transitions / dt),
+           "bucket_reads_per_s": round(st.probes / dt),
            "successors_per_state": round(f, 2),
-           "probes_per_lookup": round(st.probes / max(1, st.lookups), 4),
+           "bucket_reads_per_transition": round(st.probes / max(1, r.n_transitions), 4),
            "load_factor": round(r.n_states / info.n_slots, 3),
            "roofline": roofline_of(r.n_states, r.n_states * bps, dt)}
     traffic = measured_explore_traffic() if live == 8 and slots == W.LARGE_TABLE_SLOTS else None
@@ -878,7 +887,8 @@ def main():
                                   "seconds": round(dt, 4), "cold_seconds": round(cold, 4),
                                   "states_per_s": round(r.n_states / dt),
                                   "succ_per_state": round(per_state, 2),
-                                  "probes_per_lookup": round(s.probes / max(1, s.lookups), 4),
+                                  "bucket_reads_per_transition":
+                                      round(s.probes / max(1, r.n_transitions), 4),
                                   "algo_GBps": round(r.n_states * bps / dt / 1e9, 1),
                                   "load": round(r.n_states / t.info.n_slots, 3),
                                   "B": args.bucket, "G": args.subgroup, "U": args.kps,
@@ -905,7 +915,7 @@ def main():
                         if U > G or (G == 4 and B > 32):
                             continue
                         r = run_fop(gx, torch, keys, n_distinct, B, G, U, alpha, H, 2, 1)
-                        bpo = algorithmic_bytes_per_op(2, B, r["probes_per_op"], 0.5)
+                        bpo = algorithmic_bytes_per_op(2, B, G, r["probes_per_op"], 0.5)
                         r["Mops_per_s"] = n / r["fop_ms"] / 1e3
                         r["algo_GBps"] = n * bpo / r["fop_ms"] / 1e6
                         r["roofline_frac"] = r["algo_GBps"] / HBM_PEAK_GBS
@@ -917,7 +927,7 @@ def main():
                 H, args.steps, args.warmup)
     if r["new"] != n_distinct or r["full"] != 0:
         raise SystemExit(f"result check failed: {r['new']} new, {r['full']} full")
-    bpo = algorithmic_bytes_per_op(2, args.bucket, r["probes_per_op"], 0.5)
+    bpo = algorithmic_bytes_per_op(2, args.bucket, args.subgroup, r["probes_per_op"], 0.5)
     achieved = n * bpo / (r["fop_ms"] * 1e-3) / 1e9
     value = n / (r["ms_per_step"] * 1e-3) / 1e6
     out = {
@@ -961,11 +971,12 @@ def main():
     if args.fop_only:
         print(json.dumps(out), flush=True)
         return
-    # the achievable random-read rate at the bucket's size, the second
+    # the achievable random-read rate at the size a probe reads, the second
     # denominator of the roofline
-    ceil = random_read_ceiling(gx, torch, max(4 * args.bucket, GRANULE))
+    granule = probe_bytes(args.bucket, args.subgroup)
+    ceil = random_read_ceiling(gx, torch, granule)
     out["roofline"]["random_read_ceiling"] = {
-        "granule_bytes": max(4 * args.bucket, GRANULE), "G_reads_per_s": round(ceil / 1e9, 2),
+        "granule_bytes": granule, "G_reads_per_s": round(ceil / 1e9, 2),
         "probes_per_s_frac": round(n * r["probes_per_op"] / (r["fop_ms"] * 1e-3) / ceil, 4)}
     # what the claims cost: device-scope compare-and-swaps alone, and the
     # read-then-claim mix of a stream whose keys are half new, on a buffer

@@ -138,8 +138,13 @@ gx_status gx_table_get_info(const gx_table* table, gx_table_info* out);
 
 typedef struct {
   uint64_t stored;      /* keys stored since the last clear (GX_NEW results)   */
-  uint64_t lookups;     /* keys processed since the last clear                 */
-  uint64_t probes;      /* bucket reads (first reads and re-reads)             */
+  uint64_t lookups;     /* keys processed since the last clear; an
+                           exploration counts one for every transition, also
+                           where several of a state lead to one successor,
+                           which is looked up once (its first levels, expanded
+                           by one workgroup: one for every state found)       */
+  uint64_t probes;      /* buckets read (first reads and re-reads; a bucket
+                           read 64 bytes at a time counts once)               */
   uint64_t full;        /* GX_FULL results                                     */
   uint64_t invalid;     /* GX_INVALID results                                  */
   uint32_t max_hash_index; /* largest hash index j used by a stored/found key */
