@@ -23,6 +23,15 @@ template <int G>
 constexpr uint32_t fop_block() {
   return G == 4 ? 1024u : 256u;
 }
+// Wavefronts a SIMD must be able to hold: all eight where one key's bucket is
+// kept in registers and it is not spread over few lanes.  The compiler counts
+// 88 scalar registers as eight wavefronts; from 81 on there are fewer (2^24
+// four-word keys found in 8-word buckets by 4 lanes: 459 us at 82, 412 at 78;
+// in 16-word buckets by 16 lanes, 2^23 keys, 526 and 330).
+template <int S, int B, int G, int U>
+constexpr uint32_t fop_waves() {
+  return G == 4 || (U == 1 && B / (G < B ? G : B) < 8) ? 8u : 1u;
+}
 
 template <int S>
 __device__ inline void load_key(const uint32_t* keys, uint32_t w, uint64_t idx,
@@ -55,10 +64,9 @@ __device__ inline void load_key(const uint32_t* keys, uint32_t w, uint64_t idx,
 // subgroups probing them U at a time (kTurns: claims in turns, see
 // find_or_put_quads).  Grid-stride over rounds.
 template <int S, int B, int G, int U, bool kTurns>
-__global__ __launch_bounds__(fop_block<G>()) void fop_kernel(TableDev t, const uint32_t* keys,
-                                                             uint32_t w, uint64_t n,
-                                                             uint8_t* status, uint64_t* n_new,
-                                                             uint32_t turns) {
+__global__ __launch_bounds__(fop_block<G>(), (fop_waves<S, B, G, U>())) void fop_kernel(
+    TableDev t, const uint32_t* keys, uint32_t w, uint64_t n, uint8_t* status, uint64_t* n_new,
+    uint32_t turns) {
   const int lane = __lane_id();
   const uint32_t local = uniform32(threadIdx.x >> 6);
   const uint64_t wave = static_cast<uint64_t>(blockIdx.x) * (blockDim.x >> 6) + local;

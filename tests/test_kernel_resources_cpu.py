@@ -59,3 +59,15 @@ def test_no_kernel_spills(kernels):
     bad = {k: (f["vgpr_spill_count"], f["private_segment_fixed_size"]) for k, f in kernels.items()
            if int(f["vgpr_spill_count"]) or int(f["private_segment_fixed_size"])}
     assert not bad
+
+
+def test_find_or_put_of_one_key_fits_eight_wavefronts(kernels):
+    """One key in flight, or 4-lane subgroups, and at most 64 vector registers:
+    eight wavefronts a SIMD need at most 80 scalar registers as well."""
+    seen = 0
+    for name, f in kernels.items():
+        m = re.search(r"fop_kernelILi\d+ELi\d+ELi\d+ELi1E", name)
+        if m and int(f["vgpr_count"]) <= 64:
+            seen += 1
+            assert int(f["sgpr_count"]) <= 80, name
+    assert seen > 60
