@@ -887,8 +887,9 @@ static gx_status explore_impl(const gx_network* net, gx_table* t, const gx_explo
     n_in = e.n_in;
     cur = static_cast<int>(e.cur);
     if (e.scan != gx::kScanHost) return GX_OK;
-    // (room for the levels to come as well, where there is memory for it)
-    if (grow_buf(&eb.viol, &eb.viol_cap, most, viol_total, ~0ull) == GX_EDEVICE) return GX_EDEVICE;
+    // (with room for the levels to come as well, where there is memory for it)
+    const uint64_t want = roomy ? most : viol_total + n_in;
+    if (grow_buf(&eb.viol, &eb.viol_cap, want, viol_total, ~0ull) == GX_EDEVICE) return GX_EDEVICE;
     return scan_level(cur);
   };
   static_assert(kBlockWords <= gx::kLevelBlock, "one word a thread");

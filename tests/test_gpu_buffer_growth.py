@@ -47,7 +47,8 @@ def test_dump_keeps_no_lists():
 
 
 @pytest.mark.parametrize("opts", [{}, {"local_dedup": True}, {"slice_states": 5000}])
-def test_levels_and_violations_outgrow_the_buffers(opts):
+@pytest.mark.parametrize("slots", [0, 1 << 25])  # (2^25 slots are 512 MiB: buffers grow by need)
+def test_levels_and_violations_outgrow_the_buffers(opts, slots):
     """Hundreds of thousands of states, levels of tens of thousands with tens
     of successors a state, half of them violating; explored twice."""
     net = W.large_random_network(4)
@@ -58,10 +59,13 @@ def test_levels_and_violations_outgrow_the_buffers(opts):
     bad[hit] = 1
     expect = want.visited[np.isin(locals0, hit)]
     assert len(expect) > 1 << 16 and want.levels.max() > 1 << 14
-    with gx.Table(want.words, 16, 2 * want.n_states, max_hashes=64) as t:
+    with gx.Table(want.words, 16, slots or 2 * want.n_states, max_hashes=64) as t:
+        before = _used()
         for _ in range(2):
             t.clear()
             got = gx.explore(net, t, monitor=(0, bad), **opts)
+            # (no buffer of a large table's size)
+            assert slots == 0 or _used() - before < 384 << 20
             assert got.levels.tolist() == want.levels.tolist()
             assert got.n_transitions == want.n_transitions
             assert np.array_equal(got.deadlocks, want.deadlocks)
